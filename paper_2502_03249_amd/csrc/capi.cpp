@@ -241,15 +241,17 @@ lqs_status lqs_gauge_create(lqs_ctx *ctx, const int32_t dims[4], const double *l
             g->vh = g->g.vh;
             g->temporal = temporal;
             g->pitch = temporal ? g->vh + TEMPORAL_PAD : g->vh;
+            LinkOut packed;
             for (int prec = 0; prec < 3; ++prec)
                 for (int rc = 0; rc < 2; ++rc) {
                     const int recon = rc ? 12 : 18;
                     if (!(formats & LQS_FMT(prec, recon))) continue;
                     const size_t bytes = (size_t)link_block_bytes_per_site(prec, recon) * g->pitch * 8;
                     LQS_HIP(hipMalloc(&g->fmt[prec][rc], bytes));
-                    launch_pack_links(g->g, links, prec, recon, g->pitch, g->fmt[prec][rc], as_stream(stream));
+                    packed.fmt[prec][rc] = (char *)g->fmt[prec][rc];
                     if (temporal) launch_unit_link(g->g, prec, recon, g->pitch, g->fmt[prec][rc], as_stream(stream));
                 }
+            launch_pack_links(g->g, links, packed, g->pitch, as_stream(stream));
         } catch (...) {
             delete g;
             throw;

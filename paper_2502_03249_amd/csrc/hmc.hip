@@ -44,40 +44,54 @@ __device__ __forceinline__ void mat_store(double2 *p, const Mat &m)
         for (int j = 0; j < 3; ++j) p[3 * i + j] = make_double2(m.e[i][j].re, m.e[i][j].im);
 }
 
-// a b, a b^dag, a^dag b
-template <bool DA, bool DB> __device__ __forceinline__ Mat mat_mul(const Mat &a, const Mat &b)
+// a b, a b^dag, a^dag b (each component summed k = 0, 1, 2 in fused multiply-adds)
+template <bool DA, bool DB> __device__ __forceinline__ void mat_mac(Mat &c, const Mat &a, const Mat &b)
 {
-    Mat c;
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            Cd s = {0.0, 0.0};
+            Cd s = c.e[i][j];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                Cd x = DA ? Cd{a.e[k][i].re, -a.e[k][i].im} : a.e[i][k];
-                Cd y = DB ? Cd{b.e[j][k].re, -b.e[j][k].im} : b.e[k][j];
-                s = cadd(s, cmul(x, y));
+                const Cd x = DA ? Cd{a.e[k][i].re, -a.e[k][i].im} : a.e[i][k];
+                const Cd y = DB ? Cd{b.e[j][k].re, -b.e[j][k].im} : b.e[k][j];
+                s.re = fused(-x.im, y.im, fused(x.re, y.re, s.re));
+                s.im = fused(x.im, y.re, fused(x.re, y.im, s.im));
             }
             c.e[i][j] = s;
         }
+}
+
+__device__ __forceinline__ Mat mat_zero()
+{
+    Mat m;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) m.e[i][j] = {0.0, 0.0};
+    return m;
+}
+
+template <bool DA, bool DB> __device__ __forceinline__ Mat mat_mul(const Mat &a, const Mat &b)
+{
+    Mat c = mat_zero();
+    mat_mac<DA, DB>(c, a, b);
     return c;
 }
 
-// Lexicographic index of x + step * mu-hat (periodic).
-__device__ __forceinline__ int nbr(const Geom &g, int lex, int mu, int step)
+// TA(W) = (W - W^dag)/2 - tr(W - W^dag)/6
+__device__ __forceinline__ Mat mat_ta(const Mat &w)
 {
-    int c[4];
-    int l = lex;
+    Mat t;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        c[i] = l % g.n[i];
-        l /= g.n[i];
-    }
-    c[mu] += step;
-    if (c[mu] < 0) c[mu] += g.n[mu];
-    if (c[mu] >= g.n[mu]) c[mu] -= g.n[mu];
-    return c[0] + g.n[0] * (c[1] + g.n[1] * (c[2] + g.n[2] * c[3]));
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) t.e[i][j] = {0.5 * (w.e[i][j].re - w.e[j][i].re), 0.5 * (w.e[i][j].im + w.e[j][i].im)};
+    const double tri = (t.e[0][0].im + t.e[1][1].im + t.e[2][2].im) / 3.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) t.e[i][i].im -= tri;
+    return t;
 }
 
 __device__ __forceinline__ const double2 *link_at(const double2 *U, int vol, int mu, int lex)
@@ -87,34 +101,6 @@ __device__ __forceinline__ const double2 *link_at(const double2 *U, int vol, int
 
 constexpr int HMC_BLOCK = 256;
 constexpr int HMC_MAX_PARTIALS = 4096;
-
-// sum over sites of sum_{mu<nu} Re tr P_{mu nu}(x); one partial per block
-__global__ void __launch_bounds__(HMC_BLOCK) plaquette_kernel(Geom g, int vol, const double2 *U, double *partials)
-{
-    double s = 0.0;
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < vol; x += gridDim.x * blockDim.x) {
-#pragma unroll
-        for (int mu = 0; mu < 3; ++mu) {
-            const Mat um = mat_load(link_at(U, vol, mu, x));
-            const int xm = nbr(g, x, mu, 1);
-            for (int nu = mu + 1; nu < 4; ++nu) {
-                const int xn = nbr(g, x, nu, 1);
-                // P = U_mu(x) U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-                const Mat a = mat_mul<false, false>(um, mat_load(link_at(U, vol, nu, xm)));
-                const Mat b = mat_mul<false, false>(mat_load(link_at(U, vol, nu, x)), mat_load(link_at(U, vol, mu, xn)));
-                // Re tr P = Re tr(a b^dag), b = U_nu(x) U_mu(x+nu)
-                double t = 0.0;
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) t += a.e[i][k].re * b.e[i][k].re + a.e[i][k].im * b.e[i][k].im;
-                s += t;
-            }
-        }
-    }
-    s = block_sum(s);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s;
-}
 
 // -sum_links tr Q^2; one partial per block
 __global__ void __launch_bounds__(HMC_BLOCK) kinetic_kernel(int64_t nlinks, const double2 *Q, double *partials)
@@ -142,109 +128,327 @@ __global__ void __launch_bounds__(1024) hmc_finalize(const double *partials, int
     if (threadIdx.x == 0) out[slot] = scale * (offset + s);
 }
 
-// F_g = (beta/3) TA(U V) on link (x, mu); mode 0: out = coeff F_g, 1: out += coeff F_g.
-// Three threads per link: thread slot k of a block handles the direction
-// nu_k != mu (its upper and lower staple, four SU(3) products), the three
-// staple sums meet in LDS, and the slot-0 wave forms U V and its traceless
-// anti-Hermitian part.  A block covers 64 consecutive sites of one mu (one
-// wave per slot), so every load of a wave is a contiguous run of links.
-// PK: the links are read from the word-major FP64 18-real copy of the same
-// links (block 2 mu + parity, word k of checkerboard site cb at k * pitch +
-// cb), where a wave's load of one word is two contiguous 512-byte runs
-// instead of 64 loads 144 bytes apart; the output stays canonical.
-constexpr int GF_SITES = 64;
+// The force on every link, added to (mode 1) or written over (mode 0) a
+// canonical array Q:
+//   Q (+)= c TA(U V'),  V' = gb V - Pi
+// V: the sum of the six staples of the link; Pi: the fermion's outer products
+// (force.hip, with X = Y = chi and psi = D_oe chi), left out without FERM.
+// WM: the links are read from their word-major FP64 18-real copy (block
+// 2 mu + parity, word k of checkerboard site cb at k Vh + cb), else from the
+// canonical array.
+//
+// One thread per link; the four waves of a block take the four directions of
+// the same 64 sites and keep the links U_d(x) and U_d(x-d) in LDS for each
+// other (14 link loads per force instead of 19), and blocks follow each other
+// plane by plane in runs of time slices (SweepMap), so that what is loaded more
+// than once comes from the XCD's L2.  Bound by the vector memory path (TA and
+// TD busy 88-92 % of the time); the loads of the next staple are in flight
+// while one is multiplied (at 220 VGPRs, two waves per SIMD: more of them with
+// the compiler's own order, one or two loads at a time, were slower).  24^4:
+// 214 us in a trajectory, canonical Q read and written (the bytes at the card's
+// copy rate: 121 us); three threads per link without the LDS share took 437-450.
+struct SweepMap {
+    int tiles;   // blocks per parity (64 sites each, the last of a chunk may be partly filled)
+    int per;     // tiles per XCD
+    int chunk;   // sites (of one parity) of one chunk: nz_c z planes of one time slice
+    int tpc;     // tiles per chunk
+    int nzc;     // chunks per time slice
+    int nt, run; // time slices, and how many of them an XCD takes per chunk position
+};
 
-template <bool PK>
-__device__ __forceinline__ Mat gf_link(const double2 *U, int vol, const double2 *P, int pitch, int mu, int parity,
-                                       int lex)
+// first site and number of sites of tile o in sweep order: runs of time slices,
+// inside them the chunks in z order, inside those the slices of the run
+__host__ __device__ __forceinline__ int sweep_tile(const SweepMap &m, int o, int &count)
 {
-    if constexpr (!PK) return mat_load(link_at(U, vol, mu, lex));
-    const double2 *b = P + (int64_t)(2 * mu + parity) * 9 * pitch + (lex >> 1);
+    const int c = o / m.tpc, piece = o - c * m.tpc;
+    const int rb = c / (m.nzc * m.run), r = c - rb * m.nzc * m.run;
+    const int len = m.run < m.nt - rb * m.run ? m.run : m.nt - rb * m.run;
+    const int zc = r / len, t = rb * m.run + (r - zc * len);
+    const int left = m.chunk - piece * 64;
+    count = left < 64 ? left : 64;
+    return (t * m.nzc + zc) * m.chunk + piece * 64;
+}
+
+static SweepMap sweep_map(const Geom &g, int run)
+{
+    SweepMap m;
+    const int plane = g.n[0] * g.n[1] / 2, nz = g.n[2];
+    int k = 1;
+    for (int c = 1; c <= 8 && c <= nz; ++c)
+        if (nz % c == 0 && (c * plane) % 64 == 0) {
+            k = c;
+            break;
+        }
+    if ((k * plane) % 64 != 0)
+        for (int c = 1; c <= nz; ++c)  // no exact fit: at least four tiles per chunk, or the slice
+            if (nz % c == 0 && (c * plane >= 256 || c == nz)) {
+                k = c;
+                break;
+            }
+    m.chunk = k * plane;
+    m.tpc = (m.chunk + 63) / 64;
+    m.nzc = nz / k;
+    m.nt = g.n[3];
+    m.run = run < m.nt ? run : m.nt;
+    m.tiles = m.tpc * m.nzc * m.nt;
+    m.per = (m.tiles + 7) / 8;
+    return m;
+}
+
+// word-major FP64 18-real matrix of block blk (2 mu + parity, uniform over the
+// wave).  The word planes' addresses are scalar and the site is a 32-bit byte
+// offset: Vh < 2^28, as the links of a larger lattice (309 GB) exceed the
+// device's memory.
+__device__ __forceinline__ Mat wm_load(const double2 *a, int vh, int blk, int cb)
+{
+    const uint32_t off = 16u * (uint32_t)cb;
+    // opaque, so that the compiler forms the nine addresses here and does not
+    // keep those of every matrix of a kernel in (spilled) scalar registers
+    int64_t plane = 16 * (int64_t)vh;
+    asm volatile("" : "+s"(plane));
+    const char *base = (const char *)a + blk * 9 * plane;
     Mat m;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        const double2 d = b[(int64_t)k * pitch];
+        const double2 d = *(const double2 *)(base + k * plane + off);
         m.e[k / 3][k % 3] = {d.x, d.y};
     }
     return m;
 }
 
-template <bool PK>
-__global__ void __launch_bounds__(3 * GF_SITES) gauge_force_kernel(Geom g, int vol, const double2 *U, const double2 *P,
-                                                                   int pitch, double beta, double coeff, int mode,
-                                                                   double2 *out)
+template <bool WM>
+__device__ __forceinline__ Mat gf_link(const double2 *U, int vh, int mu, int parity, int lex)
 {
-    __shared__ double2 part[3][9][GF_SITES];
-    const int mu = blockIdx.y;
-    const int slot = threadIdx.x / GF_SITES, lane = threadIdx.x % GF_SITES;
-    const int x = blockIdx.x * GF_SITES + lane;
-    const bool valid = x < vol;
-    // parity of x; its one-step neighbours have the other parity, x + mu - nu the same
-    int par = 0;
-    if (PK && valid) {
-        int l = x;
+    if constexpr (WM) return wm_load(U, vh, 2 * mu + parity, lex >> 1);
+    else return mat_load(link_at(U, 2 * vh, mu, lex));
+}
+
+// The site with checkerboard index cb: its coordinates, and the offsets to its
+// forward and backward neighbours in the directions mu ^ k.
+struct LinkSite {
+    int lex, c[4], fw[4], bw[4];
+};
+__device__ __forceinline__ void exchange(bool on, int &p, int &r)
+{
+    const int t = p;
+    p = on ? r : p;
+    r = on ? t : r;
+}
+__device__ __forceinline__ LinkSite link_site(const Geom &g, int cb, int par, int mu)
+{
+    LinkSite s;
+    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    int l = 2 * cb / nx;
+    s.c[0] = 2 * cb - l * nx;
+    s.c[1] = l % ny;
+    l /= ny;
+    s.c[2] = l % nz;
+    s.c[3] = l / nz;
+    const int odd = (s.c[1] + s.c[2] + s.c[3] + par) & 1;
+    s.c[0] += odd;
+    s.lex = 2 * cb + odd;
+    const int w[4] = {1, nx, nx * ny, nx * ny * nz};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            par += l % g.n[i];
-            l /= g.n[i];
-        }
-        par &= 1;
+    for (int d = 0; d < 4; ++d) {
+        s.fw[d] = s.c[d] == g.n[d] - 1 ? -(g.n[d] - 1) * w[d] : w[d];
+        s.bw[d] = s.c[d] == 0 ? (g.n[d] - 1) * w[d] : -w[d];
     }
-    if (valid) {
-        const int nu = slot + (slot >= mu ? 1 : 0);
-        const int xm = nbr(g, x, mu, 1);
-        // upper staple U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-        const int xn = nbr(g, x, nu, 1);
-        Mat a = mat_mul<false, true>(gf_link<PK>(U, vol, P, pitch, nu, par ^ 1, xm),
-                                     gf_link<PK>(U, vol, P, pitch, mu, par ^ 1, xn));
-        a = mat_mul<false, true>(a, gf_link<PK>(U, vol, P, pitch, nu, par, x));
-        // lower staple U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
-        const int xd = nbr(g, x, nu, -1), xmd = nbr(g, xm, nu, -1);
-        Mat b = mat_mul<true, true>(gf_link<PK>(U, vol, P, pitch, nu, par, xmd),
-                                    gf_link<PK>(U, vol, P, pitch, mu, par ^ 1, xd));
-        b = mat_mul<false, false>(b, gf_link<PK>(U, vol, P, pitch, nu, par ^ 1, xd));
+#pragma unroll
+    for (int d = 0; d < 4; d += 2) {
+        exchange(mu & 1, s.fw[d], s.fw[d + 1]);
+        exchange(mu & 1, s.bw[d], s.bw[d + 1]);
+    }
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        exchange(mu & 2, s.fw[d], s.fw[d + 2]);
+        exchange(mu & 2, s.bw[d], s.bw[d + 2]);
+    }
+    return s;
+}
+
+// a wave's matrices in LDS, one word of 64 sites after the other
+__device__ __forceinline__ void lds_put(double2 *to, int slot, const Mat &m)
+{
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        to[(slot * 9 + k) * 64 + (threadIdx.x & 63)] = make_double2(m.e[k / 3][k % 3].re, m.e[k / 3][k % 3].im);
+}
+__device__ __forceinline__ Mat lds_get(const double2 *from, int slot)
+{
+    Mat m;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const double2 e = from[(slot * 9 + k) * 64 + (threadIdx.x & 63)];
+        m.e[k / 3][k % 3] = {e.x, e.y};
+    }
+    return m;
+}
+
+// sum over sites of sum_{mu<nu} Re tr P_{mu nu}(x), one partial per tile and
+// parity.  Re tr P = Re tr(a b^dag) with a = U_mu(x) U_nu(x+mu) and
+// b = U_nu(x) U_mu(x+nu): the wave of direction mu forms its three products a,
+// and the waves of a plane's two directions meet in LDS, so that a site's
+// plaquettes take 16 link reads.  24^4: 67 us; one thread per site with its own
+// 24 link reads took 94 us.
+template <bool WM>
+__global__ void __launch_bounds__(256) plaquette_kernel(Geom g, SweepMap sm, const double2 *U, double *partials)
+{
+    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+    const int par = q & 1, o = xcd * sm.per + (q >> 1);
+    if (o >= sm.tiles) return;
+    int count;
+    const int c0 = sweep_tile(sm, o, count);
+    __shared__ double2 ex[4 * 9 * 64];
+    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int cb = c0 + (lane < count ? lane : count - 1);  // idle lanes repeat the last site, not counted
+    const LinkSite ls = link_site(g, cb, par, mu);
+    const int vh = g.vh, x = ls.lex;
+    const Mat u = gf_link<WM>(U, vh, mu, par, x);
+    Mat f[3];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) f[k - 1] = gf_link<WM>(U, vh, mu ^ k, par ^ 1, x + ls.fw[0]);
+    double s = 0.0;
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+        const Mat a = mat_mul<false, false>(u, f[k - 1]);
+        __syncthreads();
+        lds_put(ex, mu, a);
+        __syncthreads();
+        if (mu > (mu ^ k)) continue;
+        const Mat b = lds_get(ex, mu ^ k);
 #pragma unroll
         for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int j = 0; j < 3; ++j)
-                part[slot][3 * i + j][lane] = make_double2(a.e[i][j].re + b.e[i][j].re, a.e[i][j].im + b.e[i][j].im);
+            for (int j = 0; j < 3; ++j) s = fused(a.e[i][j].im, b.e[i][j].im, fused(a.e[i][j].re, b.e[i][j].re, s));
     }
+    s = block_sum(lane < count ? s : 0.0);
+    if (threadIdx.x == 0) partials[2 * o + par] = s;
+}
+
+// Orders the arithmetic behind m before what follows: without it the compiler
+// emits products next to their last use and moves the loads in front of them.
+__device__ __forceinline__ void pin(Mat &m)
+{
+#pragma unroll
+    for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(m.e[k / 3][k % 3].re), "+v"(m.e[k / 3][k % 3].im));
+}
+
+template <bool WM, bool FERM>
+__global__ void __launch_bounds__(256) link_force_kernel(Geom g, SweepMap sm, const double2 *U, const char *chi,
+                                                         const char *psi, double gb, double c, int mode, double2 *Q)
+{
+    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+    const int par = q & 1, o = xcd * sm.per + (q >> 1);
+    if (o >= sm.tiles) return;
+    int count;
+    const int c0 = sweep_tile(sm, o, count);
+    __shared__ double2 own[4 * 9 * 64], back[4 * 9 * 64];
+    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int cb = c0 + (lane < count ? lane : count - 1);  // idle lanes repeat the last site, without a store
+    const int vh = g.vh;
+    const LinkSite ls = link_site(g, cb, par, mu);
+    const int x = ls.lex, *fw = ls.fw, *bw = ls.bw;
+    const int fm = fw[0];
+    // Staple s (0..5): nu = mu ^ (s / 2 + 1), so that the waves of a plane's two
+    // directions ask for its links together.
+    //   even s, upper: (U_nu(x+mu) (U_nu(x) U_mu(x+nu))^dag)
+    //   odd s,  lower: ((U_mu(x-nu) U_nu(x+mu-nu))^dag U_nu(x-nu))
+    // a, b: the inner product's factors, z: the outer one.  The scheduling
+    // barriers keep all 27 loads of a staple in flight while the one before it
+    // is multiplied; left alone the compiler waits after every one or two.
+    Mat v = mat_zero(), a, b, z;
+    // the links U_d(x) and U_d(x-d) of the block's sites, shared by its four waves
+    lds_put(own, mu, gf_link<WM>(U, vh, mu, par, x));
+    lds_put(back, mu, gf_link<WM>(U, vh, mu, par ^ 1, x + bw[0]));
+    auto load_ab = [&](int s) {
+        const int k = s / 2 + 1, nu = mu ^ k, d = s & 1 ? bw[k] : fw[k];
+        a = s & 1 ? gf_link<WM>(U, vh, mu, par ^ 1, x + d) : lds_get(own, nu);
+        b = s & 1 ? gf_link<WM>(U, vh, nu, par, x + fm + d) : gf_link<WM>(U, vh, mu, par ^ 1, x + d);
+    };
+    auto load_z = [&](int s) {
+        const int k = s / 2 + 1;
+        z = s & 1 ? lds_get(back, mu ^ k) : gf_link<WM>(U, vh, mu ^ k, par ^ 1, x + fm);
+    };
     __syncthreads();
-    if (slot != 0 || !valid) return;
-    double2 *o = out + 9 * ((int64_t)mu * vol + x);
-    // accumulate mode: fetch the old record before the arithmetic (see force.hip)
+    load_ab(0);
+    load_z(0);
+    // The records of Q are read and written as the 16-byte pieces j = 64 k + lane
+    // of the wave's 64 records (a lane's own record would be 64 separate lines
+    // per access): piece j is word j % 9 of the record of lane j / 9.
     double2 prev[9];
+    double2 *at[9];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) prev[k] = mode == 1 ? o[k] : make_double2(0.0, 0.0);
-    Mat v;
+    for (int k = 0; k < 9; ++k) {
+        const int j = 64 * k + lane, r = j / 9;
+        const int xr = __shfl(x, r, 64);  // by every lane: an idle source lane would hold no value
+        at[k] = r < count ? Q + 9 * ((int64_t)mu * 2 * vh + xr) + (j - 9 * r) : nullptr;
+    }
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int s = 0; s < 6; ++s) {
+        __builtin_amdgcn_sched_barrier(0);
+        Mat ab = mat_mul<false, false>(a, b);
+        pin(ab);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s < 5) {
+            load_ab(s + 1);
+        } else {  // the link itself and the old records
+            a = lds_get(own, mu);
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const double2 p0 = part[0][3 * i + j][lane], p1 = part[1][3 * i + j][lane], p2 = part[2][3 * i + j][lane];
-            v.e[i][j] = {(p0.x + p1.x) + p2.x, (p0.y + p1.y) + p2.y};
+            for (int k = 0; k < 9; ++k) prev[k] = mode == 1 && at[k] ? *at[k] : make_double2(0.0, 0.0);
         }
-    const Mat w = mat_mul<false, false>(gf_link<PK>(U, vol, P, pitch, mu, par, x), v);
-    // TA(W) = (W - W^dag)/2 - tr(W - W^dag)/6
-    Mat t;
+        __builtin_amdgcn_sched_barrier(0);
+        if (s & 1) mat_mac<true, false>(v, ab, z);
+        else mat_mac<false, true>(v, z, ab);
+        pin(v);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s < 5) load_z(s + 1);
+    }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) t.e[i][j] = {0.5 * (w.e[i][j].re - w.e[j][i].re), 0.5 * (w.e[i][j].im + w.e[j][i].im)};
-    const double tri = (t.e[0][0].im + t.e[1][1].im + t.e[2][2].im) / 3.0;
+        for (int j = 0; j < 3; ++j) v.e[i][j] = {gb * v.e[i][j].re, gb * v.e[i][j].im};
+    if constexpr (FERM) {
+        // y even: Pi = 2 e psi(y+mu) chi(y)^dag; y odd: Pi = -2 e chi(y+mu) psi(y)^dag
+        const int *cc = ls.c;
+        const int sg = mu == 0 ? 0 : mu == 1 ? cc[0] : mu == 2 ? cc[0] + cc[1] : cc[0] + cc[1] + cc[2];
+        const bool neg = ((sg & 1) != 0) != (mu == 3 && cc[3] == g.n[3] - 1);
+        const double e = (neg ? -2.0 : 2.0) * (par == 0 ? 1.0 : -1.0);
+        const V3<double> far = SpinorIO<F64>::load(par == 0 ? psi : chi, vh, (x + fm) >> 1);
+        const V3<double> own = SpinorIO<F64>::load(par == 0 ? chi : psi, vh, cb);
 #pragma unroll
-    for (int i = 0; i < 3; ++i) t.e[i][i].im -= tri;
-    const double c = coeff * beta / 3.0;
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+            for (int j = 0; j < 3; ++j) {
+                const Cd a = {e * far.c[i].re, e * far.c[i].im}, b = own.c[j];
+                v.e[i][j].re -= fused(a.im, b.im, a.re * b.re);
+                v.e[i][j].im -= fused(-a.re, b.im, a.im * b.re);
+            }
+    }
+    const Mat t = mat_ta(mat_mul<false, false>(a, v));
+    __syncthreads();  // every wave has read its links: the array takes the result
+    double2 *rec = own + mu * 9 * 64;
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
-            o[3 * i + j] = make_double2(prev[3 * i + j].x + c * t.e[i][j].re, prev[3 * i + j].y + c * t.e[i][j].im);
+    for (int k = 0; k < 9; ++k) rec[9 * lane + k] = make_double2(t.e[k / 3][k % 3].re, t.e[k / 3][k % 3].im);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const double2 f = rec[64 * k + lane];
+        if (at[k]) *at[k] = make_double2(fused(c, f.x, prev[k].x), fused(c, f.y, prev[k].y));
+    }
+}
+
+__device__ __forceinline__ Cd cfma(Cd a, Cd b, Cd c)
+{
+    return {fused(-a.im, b.im, fused(a.re, b.re, c.re)), fused(a.im, b.re, fused(a.re, b.im, c.im))};
 }
 
 // exp(A) for a 3x3 complex A: A is scaled by 2^-s so that its max-row-sum
 // norm is at most 1/4, the Taylor polynomial of degree 16 is evaluated in
 // Horner form (truncation below 1e-24), and the result squared s times.
+// Every polynomial in A is held as c0 + c1 A + c2 A^2 (Cayley-Hamilton:
+// A^3 = t A^2 - w A + d, with t = tr A, w = (t^2 - tr A^2) / 2, d = det A), so
+// a Horner step takes three complex products instead of the 27 of a matrix
+// product, and the matrix products left are A^2 and the caller's.
 __device__ __forceinline__ Mat mat_exp(const Mat &a0)
 {
     double nrm = 0.0;
@@ -266,36 +470,121 @@ __device__ __forceinline__ Mat mat_exp(const Mat &a0)
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) a.e[i][j] = {a0.e[i][j].re * sc, a0.e[i][j].im * sc};
+    const Mat a2 = mat_mul<false, false>(a, a);
+    const Cd t = {a.e[0][0].re + a.e[1][1].re + a.e[2][2].re, a.e[0][0].im + a.e[1][1].im + a.e[2][2].im};
+    const Cd t2 = {a2.e[0][0].re + a2.e[1][1].re + a2.e[2][2].re, a2.e[0][0].im + a2.e[1][1].im + a2.e[2][2].im};
+    const Cd tt = cmul(t, t);
+    const Cd nw = {0.5 * (t2.re - tt.re), 0.5 * (t2.im - tt.im)};  // -w
+    Cd d = {0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int j = (i + 1) % 3, k = (i + 2) % 3;
+        d = cfma(a.e[0][i], csub(cmul(a.e[1][j], a.e[2][k]), cmul(a.e[1][k], a.e[2][j])), d);
+    }
     // Horner: E = I + a/1 (I + a/2 (I + ... (I + a/16)))
+    Cd c0 = {1.0, 0.0}, c1 = {0.0, 0.0}, c2 = {0.0, 0.0};
+#pragma unroll 4
+    for (int k = 16; k >= 1; --k) {
+        const double inv = 1.0 / k;
+        const Cd n0 = cmul(d, c2), n1 = cfma(nw, c2, c0), n2 = cfma(t, c2, c1);
+        c0 = {fused(n0.re, inv, 1.0), n0.im * inv};
+        c1 = {n1.re * inv, n1.im * inv};
+        c2 = {n2.re * inv, n2.im * inv};
+    }
+    for (int k = 0; k < s; ++k) {
+        // (c0 + c1 A + c2 A^2)^2 = c0^2 + 2 c0 c1 A + (c1^2 + 2 c0 c2) A^2 + 2 c1 c2 A^3 + c2^2 A^4,
+        // reduced by A^4 = t A^3 - w A^2 + d A and then A^3
+        const Cd q4 = cmul(c2, c2), h = cmul(c1, c2);
+        const Cd q3 = cfma(t, q4, Cd{2.0 * h.re, 2.0 * h.im});
+        const Cd c02 = cmul(c0, c2), c01 = cmul(c0, c1);
+        const Cd q2 = cfma(nw, q4, cfma(c1, c1, Cd{2.0 * c02.re, 2.0 * c02.im}));
+        const Cd q1 = cfma(d, q4, Cd{2.0 * c01.re, 2.0 * c01.im});
+        c0 = cfma(d, q3, cmul(c0, c0));
+        c1 = cfma(nw, q3, q1);
+        c2 = cfma(t, q3, q2);
+    }
     Mat e;
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) e.e[i][j] = {i == j ? 1.0 : 0.0, 0.0};
-    for (int k = 16; k >= 1; --k) {
-        Mat t = mat_mul<false, false>(a, e);
-        const double inv = 1.0 / k;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) e.e[i][j] = {(i == j ? 1.0 : 0.0) + t.e[i][j].re * inv, t.e[i][j].im * inv};
-    }
-    for (int k = 0; k < s; ++k) e = mat_mul<false, false>(e, e);
+        for (int j = 0; j < 3; ++j) {
+            const Cd diag = i == j ? c0 : Cd{0.0, 0.0};
+            e.e[i][j] = cfma(c2, a2.e[i][j], cfma(c1, a.e[i][j], diag));
+        }
     return e;
 }
 
-// U = exp(eps Q) U on every link
-__global__ void __launch_bounds__(HMC_BLOCK) link_update_kernel(int64_t nlinks, double2 *U, const double2 *Q, double eps)
+// U = exp(eps Q) U on every link.  A block takes 128 consecutive sites of one
+// direction (64 of each parity) and moves the canonical records through LDS in
+// contiguous runs (see pack.hip).  WM: U is the word-major FP64 18-real array
+// (Q canonical) and the updated links are written in the formats of `out` as
+// well.  Bound by memory: 127 us at 24^4 for 573 MB, the card's copy rate; 174 us
+// with a matrix product per Horner step and a lane reading its own 144-byte record.
+constexpr int LU_SITES = 128;
+
+__device__ __forceinline__ void lu_stage(double2 *sh, const double2 *src, int n)
 {
-    const int64_t l = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (l >= nlinks) return;
-    Mat q = mat_load(Q + 9 * l);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const int i = threadIdx.x + k * LU_SITES;
+        if (i < n) sh[i] = src[i];
+    }
+    __syncthreads();
+}
+
+template <int P, int R> __device__ __forceinline__ void lu_store(const Mat &u, char *out, int blk, int64_t pitch, int cb)
+{
+    typedef typename RealOf<P>::type T;
+    if (!out) return;
+    M3<T> v;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) v.e[k / 3][k % 3] = {(T)u.e[k / 3][k % 3].re, (T)u.e[k / 3][k % 3].im};
+    LinkIO<P, R>::store(out + blk * (int64_t)link_block_bytes_per_site(P, R) * pitch, pitch, cb, v);
+}
+
+template <bool WM>
+__global__ void __launch_bounds__(LU_SITES) link_update_kernel(Geom g, double2 *U, const double2 *Q, double eps, LinkOut out)
+{
+    __shared__ double2 sh[9 * LU_SITES];
+    const int64_t V = 2 * (int64_t)g.vh, first = (int64_t)blockIdx.x * LU_SITES;
+    const int mu = blockIdx.y;
+    const int n = 9 * (int)(V - first < LU_SITES ? V - first : LU_SITES);
+    const int64_t rec = 9 * (mu * V + first);
+    const int parity = threadIdx.x >> 6, cb = (int)(first >> 1) + (threadIdx.x & 63);
+    const bool valid = cb < g.vh;
+    double2 *own = sh + (valid ? 9 * (lex_of(g, cb, parity) - (int)first) : 0);
+    Mat u = mat_zero();
+    if (WM && valid) u = wm_load(U, g.vh, 2 * mu + parity, cb);
+    lu_stage(sh, Q + rec, n);
+    Mat q = mat_load(own);
+    if constexpr (!WM) {
+        __syncthreads();
+        lu_stage(sh, U + rec, n);
+        u = mat_load(own);
+    }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) q.e[i][j] = {eps * q.e[i][j].re, eps * q.e[i][j].im};
-    const Mat e = mat_exp(q);
-    mat_store(U + 9 * l, mat_mul<false, false>(e, mat_load(U + 9 * l)));
+    const Mat w = mat_mul<false, false>(mat_exp(q), u);
+    if constexpr (WM) {
+        if (!valid) return;
+        const int blk = 2 * mu + parity;
+        lu_store<F64, 18>(w, (char *)U, blk, g.vh, cb);
+        lu_store<F64, 12>(w, out.fmt[F64][1], blk, g.vh, cb);
+        lu_store<F32, 18>(w, out.fmt[F32][0], blk, g.vh, cb);
+        lu_store<F32, 12>(w, out.fmt[F32][1], blk, g.vh, cb);
+        lu_store<F16, 18>(w, out.fmt[F16][0], blk, g.vh, cb);
+        lu_store<F16, 12>(w, out.fmt[F16][1], blk, g.vh, cb);
+    } else {
+        if (valid) mat_store(own, w);  // own record only: read by this thread alone
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            const int i = threadIdx.x + k * LU_SITES;
+            if (i < n) U[rec + i] = sh[i];
+        }
+    }
 }
 
 // phi = m eta_e - t (FP64 single-parity fields, double2[3][vh])
@@ -326,20 +615,6 @@ static int reduce_blocks(int64_t n)
     return (int)(b > HMC_MAX_PARTIALS ? HMC_MAX_PARTIALS : (b < 1 ? 1 : b));
 }
 
-// out[slot] (device) = beta * sum_x sum_{mu<nu} (1 - Re tr P / 3)
-void launch_gauge_action(Ctx &ctx, const Geom &g, const double *U, double beta, double *out, int slot, hipStream_t s)
-{
-    const int vol = 2 * g.vh;
-    double *part = (double *)ctx.workspace("hmc.partials.a", sizeof(double) * HMC_MAX_PARTIALS);
-    const int nb = reduce_blocks(vol);
-    hipLaunchKernelGGL(plaquette_kernel, dim3(nb), dim3(HMC_BLOCK), 0, s, g, vol, (const double2 *)U, part);
-    LQS_HIP(hipGetLastError());
-    // beta * (6 V - sum / 3) = (-beta/3) * (-18 V + sum)
-    hipLaunchKernelGGL(hmc_finalize, dim3(1), dim3(1024), 0, s, (const double *)part, nb, -18.0 * vol, -beta / 3.0,
-                       out, slot);
-    LQS_HIP(hipGetLastError());
-}
-
 void launch_kinetic(Ctx &ctx, const Geom &g, const double *Q, double *out, int slot, hipStream_t s)
 {
     const int64_t nl = 4 * 2 * (int64_t)g.vh;
@@ -351,39 +626,57 @@ void launch_kinetic(Ctx &ctx, const Geom &g, const double *Q, double *out, int s
     LQS_HIP(hipGetLastError());
 }
 
-void launch_gauge_force(const Geom &g, const double *U, double beta, double coeff, int accumulate, double *out,
-                        hipStream_t s, const LinkRef *packed)
+// Time slices an XCD takes at one chunk position before its next chunk.
+constexpr int SWEEP_RUN = 3;
+
+// out[slot] (device) = beta * sum_x sum_{mu<nu} (1 - Re tr P / 3)
+template <bool WM>
+static void launch_action(Ctx &ctx, const Geom &g, const double *U, double beta, double *out, int slot, hipStream_t s)
 {
-    const int vol = 2 * g.vh;
-    dim3 grid((vol + GF_SITES - 1) / GF_SITES, 4);
-    if (packed) {
-        LQS_REQUIRE(!packed->temporal && packed->pitch >= g.vh && packed->block_bytes == 144 * (int64_t)packed->pitch,
-                    LQS_EINVAL, "gauge force: packed links must be the plain FP64 18-real format");
-        hipLaunchKernelGGL(gauge_force_kernel<true>, grid, dim3(3 * GF_SITES), 0, s, g, vol, (const double2 *)U,
-                           (const double2 *)packed->base, (int)packed->pitch, beta, coeff, accumulate ? 1 : 0,
-                           (double2 *)out);
-    } else {
-        hipLaunchKernelGGL(gauge_force_kernel<false>, grid, dim3(3 * GF_SITES), 0, s, g, vol, (const double2 *)U,
-                           (const double2 *)nullptr, 0, beta, coeff, accumulate ? 1 : 0, (double2 *)out);
-    }
+    const double vol = 2.0 * g.vh;
+    const SweepMap sm = sweep_map(g, SWEEP_RUN);
+    double *part = (double *)ctx.workspace("hmc.partials.a", sizeof(double) * 2 * (size_t)sm.tiles);
+    hipLaunchKernelGGL(plaquette_kernel<WM>, dim3(8u * sm.per * 2), dim3(256), 0, s, g, sm, (const double2 *)U, part);
     LQS_HIP(hipGetLastError());
+    // beta * (6 V - sum / 3) = (-beta/3) * (-18 V + sum)
+    hipLaunchKernelGGL(hmc_finalize, dim3(1), dim3(1024), 0, s, (const double *)part, 2 * sm.tiles, -18.0 * vol, -beta / 3.0,
+                       out, slot);
+    LQS_HIP(hipGetLastError());
+}
+
+void launch_gauge_action(Ctx &ctx, const Geom &g, const double *U, double beta, double *out, int slot, hipStream_t s)
+{
+    launch_action<false>(ctx, g, U, beta, out, slot, s);
+}
+
+template <bool WM, bool FERM>
+static void launch_link_force(const Geom &g, const double *U, const double *chi, const double *psi, double gb, double c,
+                              int mode, double *Q, hipStream_t s)
+{
+    const SweepMap sm = sweep_map(g, SWEEP_RUN);
+    hipLaunchKernelGGL((link_force_kernel<WM, FERM>), dim3(8u * sm.per * 2), dim3(256), 0, s, g, sm, (const double2 *)U,
+                       (const char *)chi, (const char *)psi, gb, c, mode, (double2 *)Q);
+    LQS_HIP(hipGetLastError());
+}
+
+void launch_gauge_force(const Geom &g, const double *U, double beta, double coeff, int accumulate, double *out,
+                        hipStream_t s)
+{
+    launch_link_force<false, false>(g, U, nullptr, nullptr, 1.0, coeff * beta / 3.0, accumulate ? 1 : 0, out, s);
+}
+
+static void link_update_grid(const Geom &g, dim3 &grid)
+{
+    grid = dim3((unsigned)((2 * (int64_t)g.vh + LU_SITES - 1) / LU_SITES), 4);
 }
 
 void launch_link_update(const Geom &g, double *U, const double *Q, double eps, hipStream_t s)
 {
-    const int64_t nl = 4 * 2 * (int64_t)g.vh;
-    hipLaunchKernelGGL(link_update_kernel, dim3((unsigned)((nl + HMC_BLOCK - 1) / HMC_BLOCK)), dim3(HMC_BLOCK), 0, s,
-                       nl, (double2 *)U, (const double2 *)Q, eps);
+    dim3 grid;
+    link_update_grid(g, grid);
+    hipLaunchKernelGGL(link_update_kernel<false>, grid, dim3(LU_SITES), 0, s, g, (double2 *)U, (const double2 *)Q, eps,
+                       LinkOut());
     LQS_HIP(hipGetLastError());
-}
-
-// Repack every format the gauge holds from canonical links.
-void gauge_repack(Gauge &gauge, const double *U, hipStream_t s)
-{
-    for (int prec = 0; prec < 3; ++prec)
-        for (int rc = 0; rc < 2; ++rc)
-            if (gauge.fmt[prec][rc])
-                launch_pack_links(gauge.g, U, prec, rc ? 12 : 18, gauge.pitch, gauge.fmt[prec][rc], s);
 }
 
 // ---------------------------------------------------------------------------
@@ -427,16 +720,20 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
 {
     auto t0 = std::chrono::steady_clock::now();
     const int64_t vol = 2 * (int64_t)g.vh;
-    const size_t link_bytes = sizeof(double) * 18 * 4 * (size_t)vol;
     const int64_t f64 = field_bytes(g, F64, 1);
-    double *U1 = (double *)ctx.workspace("hmc.U1", link_bytes);
     double *scal = (double *)ctx.workspace("hmc.scalars", sizeof(double) * 16);
-    LQS_HIP(hipMemcpyAsync(U1, links, link_bytes, hipMemcpyDeviceToDevice, s));
     const bool ferm = prm.fermions != 0;
+    // the links of the trajectory live in the word-major FP64 18-real format
+    // alone (U1), which the force, the link update and the solver's FP64 hops
+    // read; the inner format is written along with each link update
     WsGauge wg(ctx, g, prm.cg.inner_prec, prm.cg.inner_recon);
     Gauge &gauge = wg.g;
-    if (ferm) gauge_repack(gauge, U1, s);
     const LinkRef L64 = gauge.ref(F64, 18);
+    double *U1 = (double *)gauge.fmt[F64][0];
+    LinkOut fmts;
+    for (int prec = 0; prec < 3; ++prec)
+        for (int rc = 0; rc < 2; ++rc) fmts.fmt[prec][rc] = (char *)gauge.fmt[prec][rc];
+    launch_pack_links(g, links, fmts, g.vh, s);
     const LaunchShape sh = default_hop_shape(L64, 1);
 
     double *phi = nullptr, *chi = nullptr, *psx = nullptr, *chi_prev = nullptr;
@@ -492,24 +789,29 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
         cg_iters += cs.iters;
         if (cs.status != LQS_OK && (worst == LQS_OK || cs.status < worst)) worst = cs.status;
     };
-    // mom -= eps F / 2, the fermion part from chi on the current links; the
-    // solve on the final links (last) also gives S_f at the end
+    // mom -= eps F / 2 with F_g = (beta/3) TA(U V) and F_f = -TA(U Pi), the
+    // fermion part from chi on the current links; the solve on the final links
+    // (last) also gives S_f at the end
     auto momentum = [&](double eps, bool have_chi, bool last) {
-        // with fermions the word-major FP64 18-real copy of U1 is current here
-        launch_gauge_force(g, U1, prm.beta, -0.5 * eps, 1, mom, s, ferm ? &L64 : nullptr);
-        if (!ferm) return;
+        if (!ferm) {
+            launch_link_force<true, false>(g, U1, nullptr, nullptr, prm.beta / 3.0, -0.5 * eps, 1, mom, s);
+            return;
+        }
         if (!have_chi) solve(last);
         launch_hop_gated(g, L64, F64, 18, 0, 1, 1, chi, psx, nullptr, 0, sh, s);
-        launch_force(g, L64, chi, chi, psx, psx, -0.5 * eps, 2, mom, s);
+        launch_link_force<true, true>(g, U1, chi, psx, prm.beta / 3.0, -0.5 * eps, 1, mom, s);
     };
     auto links_step = [&](double eps) {
-        launch_link_update(g, U1, mom, eps, s);
-        if (ferm) gauge_repack(gauge, U1, s);
+        dim3 grid;
+        link_update_grid(g, grid);
+        hipLaunchKernelGGL(link_update_kernel<true>, grid, dim3(LU_SITES), 0, s, g, (double2 *)U1, (const double2 *)mom,
+                           eps, fmts);
+        LQS_HIP(hipGetLastError());
     };
 
-    // H at the start: scal[0..2] = K0, Sg0, Sf0
+    // H at the start: scal[0..1] = K0, Sg0 / beta, scal[8] = Sf0
     launch_kinetic(ctx, g, mom, scal, 0, s);
-    launch_gauge_action(ctx, g, U1, prm.beta, scal, 1, s);
+    launch_action<true>(ctx, g, U1, 1.0, scal, 1, s);
     if (ferm) {
         solve(true);
         launch_field_dot(ctx, g, 1, phi, chi, scal + 8, s);
@@ -539,29 +841,27 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
     }
     // H at the end: chi is the solve on the final links (last momentum step)
     launch_kinetic(ctx, g, mom, scal, 3, s);
-    launch_gauge_action(ctx, g, U1, prm.beta, scal, 4, s);
+    launch_action<true>(ctx, g, U1, 1.0, scal, 4, s);
     if (ferm) launch_field_dot(ctx, g, 1, phi, chi, scal + 10, s);
     double hs[16];
     LQS_HIP(hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, s));
     LQS_HIP(hipStreamSynchronize(s));
     st.k0 = hs[0];
-    st.sg0 = hs[1];
+    st.sg0 = prm.beta * hs[1];
     st.sf0 = ferm ? hs[8] : 0.0;
     st.k1 = hs[3];
-    st.sg1 = hs[4];
+    st.sg1 = prm.beta * hs[4];
     st.sf1 = ferm ? hs[10] : 0.0;
     st.dH = (st.k1 + st.sg1 + st.sf1) - (st.k0 + st.sg0 + st.sf0);
     st.accepted = (std::isfinite(st.dH) && u < std::exp(-st.dH)) ? 1 : 0;
     st.cg_solves = cg_solves;
     st.cg_iters = cg_iters;
     st.status = worst;
-    if (proposal) LQS_HIP(hipMemcpyAsync(proposal, U1, link_bytes, hipMemcpyDeviceToDevice, s));
-    if (st.accepted) LQS_HIP(hipMemcpyAsync(links, U1, link_bytes, hipMemcpyDeviceToDevice, s));
+    if (proposal) launch_unpack_links(g, U1, proposal, s);
+    if (st.accepted) launch_unpack_links(g, U1, links, s);
     // plaquette of the links returned: S_g = beta * 6V (1 - <P>) at beta = 1
-    launch_gauge_action(ctx, g, links, 1.0, scal, 5, s);
-    LQS_HIP(hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, s));
+    st.plaquette = 1.0 - hs[st.accepted ? 4 : 1] / (6.0 * (double)vol);
     LQS_HIP(hipStreamSynchronize(s));
-    st.plaquette = 1.0 - hs[5] / (6.0 * (double)vol);
     st.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
 }
 

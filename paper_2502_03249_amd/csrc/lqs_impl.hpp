@@ -161,8 +161,13 @@ int64_t field_bytes(const Geom &g, int prec, int nrhs);
 // launch entry points (one kernel file each)
 
 // pack.hip
-void launch_pack_links(const Geom &g, const double *canon, int prec, int recon, int64_t pitch, void *out,
-                       hipStream_t s);
+// the link formats a packing pass writes, [prec][recon == 12] (null: not written)
+struct LinkOut {
+    char *fmt[3][2] = {{nullptr, nullptr}, {nullptr, nullptr}, {nullptr, nullptr}};
+};
+void launch_pack_links(const Geom &g, const double *canon, const LinkOut &out, int64_t pitch, hipStream_t s);
+// FP64 18-real words of pitch Vh (links or momenta) into the canonical layout
+void launch_unpack_links(const Geom &g, const double *packed, double *canon, hipStream_t s);
 // the unit link at index vh of the two t-link blocks of a temporal-gauge format
 void launch_unit_link(const Geom &g, int prec, int recon, int64_t pitch, void *links, hipStream_t s);
 void launch_field_pack(const Geom &g, const double *lex, const lqs_field &out, hipStream_t s);
@@ -254,9 +259,8 @@ void cg_solve_concurrent(Ctx &ctx, int nprob, const lqs_problem *probs, const lq
 // hmc.hip (canonical [4][V][3][3] complex128 links and momenta)
 void launch_gauge_action(Ctx &ctx, const Geom &g, const double *U, double beta, double *out, int slot, hipStream_t s);
 void launch_kinetic(Ctx &ctx, const Geom &g, const double *Q, double *out, int slot, hipStream_t s);
-// packed: optional word-major FP64 18-real copy of U (read instead of U)
 void launch_gauge_force(const Geom &g, const double *U, double beta, double coeff, int accumulate, double *out,
-                        hipStream_t s, const LinkRef *packed = nullptr);
+                        hipStream_t s);
 void launch_link_update(const Geom &g, double *U, const double *Q, double eps, hipStream_t s);
 void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, const double *pf, double u,
                          const lqs_hmc_params &prm, lqs_hmc_stats &st, double *proposal, double *phi_out,
