@@ -2,23 +2,31 @@
 // M = m^2 - D_eo D_oe (the inversion of Sec. 4.2), in FP64 or with a
 // low-precision inner iteration and FP64 residual updates.
 //
-// Per iteration four kernels run back to back on one stream:
+// Per iteration three or four kernels run back to back on one stream:
 //   1. t = D_oe p                                      (hop)
-//   2. q = m^2 p - D_eo t and <p,q>                     (hop + fused dot)
-//   3. r -= alpha q and |r|^2                           (fused update + norm)
-//   4. x += alpha p, p = r + beta p                     (one read of the old p)
-// The dot products are reduced in two fixed-order stages (wave shuffles and
-// LDS inside a block, then the last block to finish sums the block partials)
-// and alpha, beta stay on the device; the host only polls the state record.
-// Every few iterations a gated FP64 group runs between kernels 3 and 4:
-//   x += alpha p                                        (the step 4 owes)
+//   2. q = m^2 p - D_eo t, <p,q> and <q,q>              (hop + fused dots)
+//   3. the scalars of the step                          (one block per side)
+//   4. x += alpha p, r -= alpha q, p = r + beta p, |r|^2 (one pass)
+// beta and the stop decision need the norm of the residual before kernel 4 has
+// formed it.  It is predicted from the dots at hand,
+//   |r - alpha q|^2 = |r|^2 - 2 alpha <r,q> + alpha^2 <q,q> = alpha^2 <q,q> - |r|^2
+// (<r,q> = <p,q> as the directions are conjugate, alpha = |r|^2 / <p,q>), and
+// |r|^2 of the next step is the one kernel 4 sums from the residual it stores,
+// so the prediction's rounding does not accumulate: the predict-and-recompute
+// conjugate gradient of Chen and Carson (SIAM J. Matrix Anal. Appl. 2020).
+// The x, r and p updates then share one kernel and one read of each vector.
+// The dot products are reduced in two fixed-order stages and alpha, beta stay
+// on the device; the host only polls the state record.
+// Every few iterations a gated FP64 group runs after kernel 4:
 //   x += x_lo, x_lo = 0                                 (mixed precision)
 //   t64 = D_oe x, r_hi = b - (m^2 x - D_eo t64), |r_hi|^2, r = r_hi
+//   p = r + beta p                                      (kernel 4 left it out)
 // It does nothing unless the state asks for it: after the iterated residual
 // met the target (then it decides convergence on the FP64 residual), at the
 // iteration cap, or in mixed precision every K iterations or when |r| fell
 // below delta * max|r| (the reliable update of the mixed-precision solvers the
 // paper cites, Clark et al. 2010).
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <mutex>
@@ -28,39 +36,48 @@
 namespace lqs {
 
 static constexpr int BLAS_BLOCK = 256;
-static constexpr int MIN_HOP_BLOCK = 64;
-// largest number of <p,q> partials the update kernel sums in every block
-// (measured: folding pays on 32^4 and below, not on 64^3 x 16 with 8192)
-static constexpr int FOLD_ALPHA_MAX = 2048;
-
 // ---------------------------------------------------------------------------
-// scalar bookkeeping, run by one thread of a one-block finalize kernel
+// Scalars of one iteration from its dots (rr: |r|^2 as the last step summed it,
+// unused while S.rho holds a measured one).  `live`: this iteration's update is
+// due; `p_due`: the direction update is left to the FP64 group that closes the
+// round (`last`: the group follows this iteration).
 
-__device__ void fin_alpha(CgState &S, double pq)
+__device__ void cg_step_scalars(CgState &S, double pq, double qq, double rr, int last)
 {
-    if (!isfinite(pq)) S.phase = CG_NONFINITE;
-    else if (!(pq > 0.0)) S.phase = CG_BREAKDOWN;
-    else S.alpha = S.rho / pq;
-}
-
-__device__ void fin_update(CgState &S, double r2)
-{
-    S.rho_old = S.rho;
-    S.rho = r2;
-    S.beta = r2 / S.rho_old;
+    if (S.rho_known) rr = S.rho;
+    S.live = 0;
+    S.p_due = 0;
+    if (!isfinite(pq)) {
+        S.phase = CG_NONFINITE;
+        return;
+    }
+    if (!(pq > 0.0)) {
+        S.phase = CG_BREAKDOWN;
+        return;
+    }
+    S.alpha = rr / pq;
+    double r2 = fma(S.alpha * S.alpha, qq, -rr);
+    if (r2 < 0.0) r2 = 0.0;  // rounding, when the step removes the residual altogether
+    S.rho_known = 0;
     S.iters += 1;
     S.since_rel += 1;
     if (!isfinite(r2)) {
         S.phase = CG_NONFINITE;
         return;
     }
+    S.rho_old = rr;
+    S.rho = r2;
+    S.beta = rr > 0.0 ? r2 / rr : 0.0;
+    S.live = 1;
     if (r2 > S.max_rho) S.max_rho = r2;
     if (r2 <= S.stop2 || S.iters >= S.max_iter) {
         S.phase = CG_INNER_DONE;
         S.reliable_pending = 1;
+        S.p_due = 1;
         return;
     }
     if (S.rel_interval > 0 && (S.since_rel >= S.rel_interval || r2 < S.delta2 * S.max_rho)) S.reliable_pending = 1;
+    if (last && S.reliable_pending) S.p_due = 1;
 }
 
 // mode: 0 reliable update inside the iteration, 1 initial residual, 2 measure
@@ -75,6 +92,7 @@ __device__ void fin_residual(CgState &S, double r2, int mode)
         S.phase = CG_INNER_DONE;
         return;
     }
+    S.rho_known = 1;  // wherever the iteration goes on, S.rho is set below
     if (mode == 1) {
         S.rho = r2;
         S.max_rho = r2;
@@ -99,7 +117,7 @@ __device__ void fin_residual(CgState &S, double r2, int mode)
         S.phase = CG_RUNNING;
     } else {
         // mixed precision: continue with the FP64 residual, keep p
-        S.beta = r2 / S.rho_old;
+        S.beta = S.rho_old > 0.0 ? r2 / S.rho_old : 0.0;
         S.rho = r2;
         S.max_rho = r2;
         S.phase = CG_RUNNING;
@@ -125,7 +143,7 @@ __device__ __forceinline__ V3<typename RealOf<PA>::type> direction_of(const V3<t
 }
 
 // ---------------------------------------------------------------------------
-// 2. q = m^2 p - D_eo t, <p, q>  (output parity even; t odd)
+// 2. q = m^2 p - D_eo t, <p,q> and <q,q> (output parity even; t odd)
 
 // FP16 storage: left alone the compiler gives the one-vector kernel 120 VGPRs
 // (4 waves per SIMD); held to 6 waves it needs 62, without spills, and the
@@ -134,9 +152,8 @@ __device__ __forceinline__ V3<typename RealOf<PA>::type> direction_of(const V3<t
 template <int P, int R, int K, int LF>
 __global__ void __launch_bounds__(512)
 __attribute__((amdgpu_waves_per_eu((P == F16 && (LF & LF_PREFETCH) == 0) ? 6 : 1)))
-normal_dot_kernel(Geom g, LinkRef L, const char *t, const char *p, char *q,
-                                                         int64_t stride, CgState *st, double *partials,
-                                                         int max_blocks, int nrhs, int ngroups, TileMap tmap)
+normal_dot_kernel(Geom g, LinkRef L, const char *t, const char *p, char *q, int64_t stride, const CgState *st,
+                  double *partials, int max_blocks, int nrhs, int ngroups, TileMap tmap)
 {
     typedef typename RealOf<P>::type T;
     int grp;
@@ -159,7 +176,7 @@ normal_dot_kernel(Geom g, LinkRef L, const char *t, const char *p, char *q,
     const int wstride = lds_window_stride(g, P);
     if (LF & LF_LDS)
         stage_block_window<P, K>(g, tile * blockDim.x, t + r0 * stride, stride, blk, win, wstride, w0, wlen);
-    double dot[K];
+    double dot[2 * K];  // <p,q>, <q,q> of each side
     V3<T> acc[K];
     // LF_PREFETCH with one vector: the site's own p is requested with the hop's words
     constexpr bool PF1 = (LF & LF_PREFETCH) != 0 && K == 1;
@@ -171,169 +188,151 @@ normal_dot_kernel(Geom g, LinkRef L, const char *t, const char *p, char *q,
     }
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-        dot[j] = 0.0;
-        if (!act[j]) continue;
-        const V3<T> pv = PF1 ? SpinorIO<P>::decode(praw) : SpinorIO<P>::load(p + (r0 + j) * stride, g.vh, cb);
-        const T m2 = (T)st[r0 + j].m2;
-        V3<T> qv;
+        double pq = 0.0, qq = 0.0;
+        if (act[j]) {
+            const V3<T> pv = PF1 ? SpinorIO<P>::decode(praw) : SpinorIO<P>::load(p + (r0 + j) * stride, g.vh, cb);
+            const T m2 = (T)st[r0 + j].m2;
+            V3<T> qv;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            qv.c[a].re = m2 * pv.c[a].re - acc[j].c[a].re;
-            qv.c[a].im = m2 * pv.c[a].im - acc[j].c[a].im;
-            dot[j] += (double)pv.c[a].re * (double)qv.c[a].re + (double)pv.c[a].im * (double)qv.c[a].im;
+            for (int a = 0; a < 3; ++a) {
+                qv.c[a].re = m2 * pv.c[a].re - acc[j].c[a].re;
+                qv.c[a].im = m2 * pv.c[a].im - acc[j].c[a].im;
+                const double pr = pv.c[a].re, pi = pv.c[a].im, qr = qv.c[a].re, qi = qv.c[a].im;
+                pq += pr * qr + pi * qi;
+                qq += qr * qr + qi * qi;
+            }
+            SpinorIO<P>::store(q + (r0 + j) * stride, g.vh, cb, qv);
         }
-        SpinorIO<P>::store(q + (r0 + j) * stride, g.vh, cb, qv);
+        dot[2 * j] = pq;
+        dot[2 * j + 1] = qq;
     }
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-        if (!blk[j]) continue;
-        const int r = r0 + j;
-        const double s = block_sum(dot[j]);
-        if (threadIdx.x == 0) partials[(int64_t)r * max_blocks + tile] = s;
-    }
+    __shared__ double red[8][2 * K];
+    block_sums<2 * K>(dot, red);
+    // thread 2 j + d holds sum d of side j
+    const int j = threadIdx.x >> 1;
+    if (j < K && r0 + j < nrhs && st[r0 + j].phase == CG_RUNNING)
+        partials[(int64_t)(r0 + j) * max_blocks + 2 * tile + (threadIdx.x & 1)] = dot[0];
 }
 
 // ---------------------------------------------------------------------------
-// 3. alpha = rho / <p, q>; r -= alpha q, |r|^2
-//    (grid-stride, blockIdx.y = rhs; x += alpha p is left to the p-update,
-//    which reads p anyway, or to the FP64 group's flush when that runs first)
-//
-// With nd_blocks > 0 every block sums the normal kernel's <p, q> partials
-// itself, in the same order, so all blocks hold the same alpha without a
-// separate reduction kernel (used while the partials are few; beyond
-// FOLD_ALPHA_MAX of them the redundant sums cost more than the finalize
-// kernel they replace, and FIN_DOT sets alpha instead).  Within this kernel
-// no block reads a state field that another block writes: rho and phase are
-// read, block 0 writes alpha and, on a breakdown (which every block detects
-// by itself), the phase.  A thread requests the operands of its first site
-// before the gate and the alpha reduction, whose memory round trips then
-// overlap with them (on small lattices that is its only site).
+// 3. the scalars, one block per right-hand side.  (Summing the partials in
+// every block of the step kernel instead, with the state record double
+// buffered, was slower: 20 us for that kernel at 32^3 x 8 in FP64 against 4.8
+// for this one and 9.3 for the step.)
 
-template <int PA, int PI>
-__global__ void __launch_bounds__(BLAS_BLOCK) update_kernel(int vh, char *r, const char *q, int64_t sa, int64_t si,
-                                                            CgState *st, const double *pq_partials, int nd_blocks,
-                                                            double *partials, int max_blocks)
+__global__ void __launch_bounds__(1024) step_finalize_kernel(CgState *st, const double *partials,
+                                                            const double *rr_partials, int max_blocks, int nblocks,
+                                                            int nr_blocks, int last)
+{
+    const int r = blockIdx.x;
+    const double2 *pp = (const double2 *)(partials + (int64_t)r * max_blocks);
+    const double *rp = rr_partials + (int64_t)r * max_blocks;
+    CgState S = st[r];
+    // (v[3]: padding to a power of two)
+    double v[4] = {0.0, 0.0, (int)threadIdx.x < nr_blocks ? rp[threadIdx.x] : 0.0, 0.0};  // nr_blocks <= 1024
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nblocks; i += blockDim.x) {
+        const double2 a = pp[i];
+        v[0] += a.x;
+        v[1] += a.y;
+    }
+    __shared__ double red[16][4];
+    block_sums_all<4>(v, red);
+    if (threadIdx.x != 0) return;
+    if (S.phase == CG_RUNNING) cg_step_scalars(S, v[0], v[1], v[2], last);
+    else S.live = 0;
+    st[r] = S;
+}
+
+// ---------------------------------------------------------------------------
+// 4. x += alpha p (x_lo in mixed precision), r -= alpha q, p = r + beta p, and
+//    the block partials of |r|^2 (grid-stride, blockIdx.y = rhs)
+//
+// EARLY (one right-hand side, one site per thread): the site's four vectors are
+// requested together with the state record, one memory round trip instead of
+// two; otherwise a right-hand side that has converged reads only its record.
+// Bound by HBM, or on small lattices by its fixed cost: 7 vectors a site where
+// separate r and x/p updates read and wrote 8 in two launches (32^3 x 8, 16
+// FP32 vectors: 53 us against 31 + 38; 64^3 x 16 FP16 storage 46 against
+// 22 + 32; 32^3 x 8 FP64 9.3 against 6.4 + 6.1).
+
+template <int PA, int PI, bool EARLY>
+__global__ void __launch_bounds__(BLAS_BLOCK) step_kernel(int vh, char *x, char *r, char *p, const char *q, int64_t sa,
+                                                          int64_t si, const CgState *st, double *rr_partials,
+                                                          int max_blocks)
 {
     typedef typename RealOf<PA>::type T;
+    typedef typename RealOf<PI>::type TI;
     const int rhs = blockIdx.y;
-    CgState &S = st[rhs];
+    x += rhs * sa;
     r += rhs * sa;
+    p += rhs * si;
     q += rhs * si;
-    const int stride = gridDim.x * blockDim.x;
     const int c0 = blockIdx.x * blockDim.x + threadIdx.x;
-    const int cf = c0 < vh ? c0 : vh - 1;  // a valid site for every thread (vh >= 1)
-    const typename SpinorIO<PI>::Raw qraw = SpinorIO<PI>::load_raw(q, vh, cf);
-    const typename SpinorIO<PA>::Raw rraw = SpinorIO<PA>::load_raw(r, vh, cf);
-    const int phase = S.phase;
-    issue_here(qraw);
-    issue_here(rraw);
-    if (phase != CG_RUNNING) return;
-    double alpha_d = S.alpha;  // nd_blocks == 0: set by the FIN_DOT finalize
-    if (nd_blocks > 0) {
-        double acc = 0.0;
-        for (int i = threadIdx.x; i < nd_blocks; i += blockDim.x) acc += pq_partials[(int64_t)rhs * max_blocks + i];
-        const double pq = block_sum(acc);
-        const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-        if (!isfinite(pq) || !(pq > 0.0)) {
-            if (lead) S.phase = isfinite(pq) ? CG_BREAKDOWN : CG_NONFINITE;
-            return;
-        }
-        alpha_d = S.rho / pq;
-        if (lead) S.alpha = alpha_d;
+    typename SpinorIO<PI>::Raw qraw{}, praw{};
+    typename SpinorIO<PA>::Raw rraw{}, xraw{};
+    if (EARLY) {
+        const int cf = c0 < vh ? c0 : vh - 1;  // a valid site for every thread (vh >= 1)
+        qraw = SpinorIO<PI>::load_raw(q, vh, cf);
+        praw = SpinorIO<PI>::load_raw(p, vh, cf);
+        rraw = SpinorIO<PA>::load_raw(r, vh, cf);
+        xraw = SpinorIO<PA>::load_raw(x, vh, cf);
     }
-    const T alpha = (T)alpha_d;
+    const int live = st[rhs].live;
+    const bool pdir = !st[rhs].p_due;
+    const T alpha = (T)st[rhs].alpha, beta = (T)st[rhs].beta;
+    if (EARLY) {
+        issue_here(qraw);
+        issue_here(praw);
+        issue_here(rraw);
+        issue_here(xraw);
+    }
+    if (!live) return;
     double local = 0.0;
-    auto site = [&](int cb, const V3<T> &qv, V3<T> rv) {
+    auto site = [&](int cb, const V3<T> &qv, const V3<T> &pv, V3<T> rv, V3<T> xv) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
+            xv.c[a].re = fused(alpha, pv.c[a].re, xv.c[a].re);
+            xv.c[a].im = fused(alpha, pv.c[a].im, xv.c[a].im);
             rv.c[a].re = fused(-alpha, qv.c[a].re, rv.c[a].re);
             rv.c[a].im = fused(-alpha, qv.c[a].im, rv.c[a].im);
             local += (double)rv.c[a].re * (double)rv.c[a].re + (double)rv.c[a].im * (double)rv.c[a].im;
         }
+        SpinorIO<PA>::store(x, vh, cb, xv);
         SpinorIO<PA>::store(r, vh, cb, rv);
+        if (pdir) SpinorIO<PI>::store(p, vh, cb, vcast<TI>(direction_of<PA>(rv, pv, beta)));
     };
-    if (c0 < vh) site(c0, vcast<T>(SpinorIO<PI>::decode(qraw)), SpinorIO<PA>::decode(rraw));
-    for (int cb = c0 + stride; cb < vh; cb += stride)
-        site(cb, vcast<T>(SpinorIO<PI>::load(q, vh, cb)), SpinorIO<PA>::load(r, vh, cb));
-    const double s = block_sum(local);
-    if (threadIdx.x == 0) partials[(int64_t)rhs * max_blocks + blockIdx.x] = s;
-}
-
-// ---------------------------------------------------------------------------
-// 4. x += alpha p (x_lo in mixed precision), p = r + beta p
-//
-// The x update belongs to this iteration's alpha and the p before this
-// kernel; it is skipped when the FP64 group ran after the update kernel
-// (since_rel == 0: its flush already applied it).  No block writes the state.
-// (As in the update kernel, the first site's operands are requested before
-// the gate.)
-template <int PA, int PI>
-__device__ __forceinline__ void x_step(V3<typename RealOf<PA>::type> &xv, const V3<typename RealOf<PA>::type> &pv,
-                                       typename RealOf<PA>::type alpha)
-{
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        xv.c[a].re = fused(alpha, pv.c[a].re, xv.c[a].re);
-        xv.c[a].im = fused(alpha, pv.c[a].im, xv.c[a].im);
+    if (EARLY) {
+        if (c0 < vh)
+            site(c0, vcast<T>(SpinorIO<PI>::decode(qraw)), vcast<T>(SpinorIO<PI>::decode(praw)),
+                 SpinorIO<PA>::decode(rraw), SpinorIO<PA>::decode(xraw));
+    } else {
+        for (int cb = c0; cb < vh; cb += gridDim.x * blockDim.x)
+            site(cb, vcast<T>(SpinorIO<PI>::load(q, vh, cb)), vcast<T>(SpinorIO<PI>::load(p, vh, cb)),
+                 SpinorIO<PA>::load(r, vh, cb), SpinorIO<PA>::load(x, vh, cb));
     }
+    const double s = block_sum(local);
+    if (threadIdx.x == 0) rr_partials[(int64_t)rhs * max_blocks + blockIdx.x] = s;
 }
 
+// FP64 group, last: the direction update the step kernel left out, with the
+// residual and beta the group has set.
 template <int PA, int PI>
-__global__ void __launch_bounds__(BLAS_BLOCK) pupdate_kernel(int vh, char *x, const char *r, char *p, int64_t sa,
-                                                             int64_t si, const CgState *st)
+__global__ void __launch_bounds__(BLAS_BLOCK) pdir_kernel(int vh, const char *r, char *p, int64_t sa, int64_t si,
+                                                          const CgState *st)
 {
     typedef typename RealOf<PA>::type T;
     typedef typename RealOf<PI>::type TI;
     const int rhs = blockIdx.y;
     const CgState &S = st[rhs];
-    x += rhs * sa;
+    if (!S.p_due || S.phase != CG_RUNNING) return;
+    const T beta = (T)S.beta;
     r += rhs * sa;
     p += rhs * si;
-    const int stride = gridDim.x * blockDim.x;
-    const int c0 = blockIdx.x * blockDim.x + threadIdx.x;
-    const int cf = c0 < vh ? c0 : vh - 1;
-    const typename SpinorIO<PA>::Raw rraw = SpinorIO<PA>::load_raw(r, vh, cf);
-    const typename SpinorIO<PI>::Raw praw = SpinorIO<PI>::load_raw(p, vh, cf);
-    const typename SpinorIO<PA>::Raw xraw = SpinorIO<PA>::load_raw(x, vh, cf);
-    const int phase = S.phase;
-    const bool xstep = S.since_rel != 0;
-    const T beta = (T)S.beta, alpha = (T)S.alpha;
-    issue_here(rraw);
-    issue_here(praw);
-    issue_here(xraw);
-    if (phase != CG_RUNNING) return;
-    auto site = [&](int cb, const V3<T> &rv, const V3<T> &pv, V3<T> xv) {
-        if (xstep) {
-            x_step<PA, PI>(xv, pv, alpha);
-            SpinorIO<PA>::store(x, vh, cb, xv);
-        }
-        SpinorIO<PI>::store(p, vh, cb, vcast<TI>(direction_of<PA>(rv, pv, beta)));
-    };
-    if (c0 < vh)
-        site(c0, SpinorIO<PA>::decode(rraw), vcast<T>(SpinorIO<PI>::decode(praw)), SpinorIO<PA>::decode(xraw));
-    for (int cb = c0 + stride; cb < vh; cb += stride)
-        site(cb, SpinorIO<PA>::load(r, vh, cb), vcast<T>(SpinorIO<PI>::load(p, vh, cb)),
-             xstep ? SpinorIO<PA>::load(x, vh, cb) : vzero<T>());
-}
-
-// FP64 group, first: x += alpha p for the iteration whose p-update has not
-// run yet (gate: reliable pending), with the p-update's arithmetic.
-template <int PA, int PI>
-__global__ void __launch_bounds__(BLAS_BLOCK) xflush_kernel(int vh, char *x, const char *p, int64_t sa, int64_t si,
-                                                            const CgState *st)
-{
-    typedef typename RealOf<PA>::type T;
-    const int rhs = blockIdx.y;
-    const CgState &S = st[rhs];
-    if (!S.reliable_pending) return;
-    const T alpha = (T)S.alpha;
-    x += rhs * sa;
-    p += rhs * si;
-    for (int cb = blockIdx.x * blockDim.x + threadIdx.x; cb < vh; cb += gridDim.x * blockDim.x) {
-        V3<T> xv = SpinorIO<PA>::load(x, vh, cb);
-        x_step<PA, PI>(xv, vcast<T>(SpinorIO<PI>::load(p, vh, cb)), alpha);
-        SpinorIO<PA>::store(x, vh, cb, xv);
-    }
+    for (int cb = blockIdx.x * blockDim.x + threadIdx.x; cb < vh; cb += gridDim.x * blockDim.x)
+        SpinorIO<PI>::store(p, vh, cb,
+                            vcast<TI>(direction_of<PA>(SpinorIO<PA>::load(r, vh, cb),
+                                                       vcast<T>(SpinorIO<PI>::load(p, vh, cb)), beta)));
 }
 
 // ---------------------------------------------------------------------------
@@ -447,7 +446,7 @@ __global__ void __launch_bounds__(BLAS_BLOCK) init_kernel(int vh, const char *b,
 // producer) needs no device-scope fence: the kernel boundary orders the
 // partials' stores before these loads.
 
-enum FinMode { FIN_DOT = 0, FIN_UPDATE = 1, FIN_RESID = 2, FIN_INIT = 3 };
+enum FinMode { FIN_RESID = 0, FIN_INIT = 1 };
 
 __global__ void __launch_bounds__(1024) finalize_kernel(CgState *st, const double *partials, int max_blocks,
                                                        int nblocks, int mode, int gate_mode, int sub)
@@ -465,21 +464,17 @@ __global__ void __launch_bounds__(1024) finalize_kernel(CgState *st, const doubl
     acc += i0 < nblocks ? first : 0.0;
     for (int i = i0 + blockDim.x; i < nblocks; i += blockDim.x) acc += p[i];
     bool active = true;
-    if (mode == FIN_DOT || mode == FIN_UPDATE) active = S.phase == CG_RUNNING;
-    else if (mode == FIN_RESID) active = gate_state(S, gate_mode);
+    if (mode == FIN_RESID) active = gate_state(S, gate_mode);
     if (!active) return;
     const double v = block_sum(acc);
     if (threadIdx.x != 0) return;
-    if (mode == FIN_DOT) {
-        fin_alpha(S, v);
-    } else if (mode == FIN_UPDATE) {
-        fin_update(S, v);
-    } else if (mode == FIN_RESID) {
+    if (mode == FIN_RESID) {
         fin_residual(S, v, sub);
     } else {  // FIN_INIT, sub = cold start
         S.b2 = v;
         S.stop2 = S.stop2 * v;  // the host stored tol^2 here
         if (sub) {
+            S.rho_known = 1;
             S.rho = v;
             S.max_rho = v;
             S.true_r2 = v;
@@ -524,11 +519,12 @@ void cg_fill_rates(lqs_cg_stats &o, const Gauge &gauge, int prec, int recon, int
     o.gbytes_per_s = bytes * n / t * 1e-9;
 }
 
-int cg_partials_needed(const Gauge &gauge, int nrhs)
+// Doubles of partials per right-hand side: one per block of the init (at most
+// 1024) and residual kernels (256 threads), two per block of the normal kernel.
+int cg_partials_needed(const Gauge &gauge, int normal_block)
 {
-    (void)nrhs;
-    int64_t hop_blocks = (gauge.vh + MIN_HOP_BLOCK - 1) / MIN_HOP_BLOCK;
-    return (int)(hop_blocks > 1024 ? hop_blocks : 1024);
+    const int64_t dots = 2 * ((gauge.vh + normal_block - 1) / normal_block), one = (gauge.vh + 255) / 256;
+    return (int)std::max<int64_t>(1024, std::max(dots, one));
 }
 
 template <int P, int R>
@@ -543,8 +539,8 @@ static void launch_normal_dot(const Gauge &gauge, const CgVectors &v, LaunchShap
     const size_t lds = hop_lds_bytes(g, P, sh.rhs_per_thread, sh);
 #define LQS_ND(K, LF)                                                                                             \
     hipLaunchKernelGGL((normal_dot_kernel<P, R, K, LF>), grid, dim3(sh.block), lds, s, g, L, (const char *)v.t,   \
-                       (const char *)v.p, (char *)v.q, stride, v.state, v.partials,          \
-                       v.max_blocks, v.nrhs, G, tmap)
+                       (const char *)v.p, (char *)v.q, stride, (const CgState *)v.state, v.partials, v.max_blocks, \
+                       v.nrhs, G, tmap)
 #define LQS_ND_LF(LF)                                                                                            \
     if (sh.rhs_per_thread == 1) LQS_ND(1, LF);                                                                   \
     else if (sh.rhs_per_thread == 2) LQS_ND(2, LF);                                                              \
@@ -585,27 +581,36 @@ void launch_normal_dot_shape(const Gauge &gauge, const CgVectors &v, LaunchShape
     else launch_normal_dot<F16, 12>(gauge, v, shd, s);
 }
 
-// which 0: update (alpha from the nd_blocks <p,q> partials in v.partials, or
-// from the state when nd_blocks is 0; |r|^2 partials into v.partials2) and
-// its finalize; 1: x += alpha p (unless flushed), p = r + beta p; 2: the FP64
-// group's flush of x += alpha p
+// The scalars of a step from the nd_blocks partials of the normal kernel, and
+// the step.
 template <int PA, int PI>
-static void launch_blas(const Gauge &gauge, const CgVectors &v, int which, int nd_blocks, hipStream_t s)
+static void launch_step(const Gauge &gauge, const CgVectors &v, int nd_blocks, int last, hipStream_t s)
 {
     const int vh = (int)gauge.vh;
     const int64_t sa = field_bytes(gauge.g, PA, 1), si = field_bytes(gauge.g, PI, 1);
-    dim3 grid(blas_blocks(vh), v.nrhs);
-    if (which == 0)
-        hipLaunchKernelGGL((update_kernel<PA, PI>), grid, dim3(BLAS_BLOCK), 0, s, vh, (char *)v.r, (const char *)v.q,
-                           sa, si, v.state, (const double *)v.partials, nd_blocks, v.partials2, v.max_blocks);
-    else if (which == 1)
-        hipLaunchKernelGGL((pupdate_kernel<PA, PI>), grid, dim3(BLAS_BLOCK), 0, s, vh, (char *)v.xlo,
-                           (const char *)v.r, (char *)v.p, sa, si, (const CgState *)v.state);
-    else
-        hipLaunchKernelGGL((xflush_kernel<PA, PI>), grid, dim3(BLAS_BLOCK), 0, s, vh, (char *)v.xlo,
-                           (const char *)v.p, sa, si, (const CgState *)v.state);
+    const dim3 grid(blas_blocks(vh), v.nrhs);
+    hipLaunchKernelGGL(step_finalize_kernel, dim3(v.nrhs), dim3(1024), 0, s, v.state, (const double *)v.partials,
+                       (const double *)v.partials2, v.max_blocks, nd_blocks, (int)grid.x, last);
+    const bool early = v.nrhs == 1 && vh <= (int)grid.x * BLAS_BLOCK;
+#define LQS_STEP(EARLY)                                                                                           \
+    hipLaunchKernelGGL((step_kernel<PA, PI, EARLY>), grid, dim3(BLAS_BLOCK), 0, s, vh, (char *)v.xlo,             \
+                       (char *)v.r, (char *)v.p, (const char *)v.q, sa, si, (const CgState *)v.state,             \
+                       v.partials2, v.max_blocks)
+    if (early) LQS_STEP(true);
+    else LQS_STEP(false);
+#undef LQS_STEP
     LQS_HIP(hipGetLastError());
-    if (which == 0) launch_finalize(v, v.partials2, grid.x, FIN_UPDATE, 0, 0, s);
+}
+
+// The FP64 group's direction update.
+template <int PA, int PI>
+static void launch_pdir(const Gauge &gauge, const CgVectors &v, hipStream_t s)
+{
+    const int vh = (int)gauge.vh;
+    const int64_t sa = field_bytes(gauge.g, PA, 1), si = field_bytes(gauge.g, PI, 1);
+    hipLaunchKernelGGL((pdir_kernel<PA, PI>), dim3(blas_blocks(vh), v.nrhs), dim3(BLAS_BLOCK), 0, s, vh,
+                       (const char *)v.r, (char *)v.p, sa, si, (const CgState *)v.state);
+    LQS_HIP(hipGetLastError());
 }
 
 template <int PA, int R, int K>
@@ -711,48 +716,38 @@ void cg_init(Ctx &ctx, const Gauge &gauge, CgVectors &v, bool use_x0, hipStream_
     }
 }
 
-// Launch shape of the CG hop (tuned, else the default)
-static LaunchShape cg_hop_shape(Ctx &ctx, const Gauge &gauge, int prec, int recon, int nrhs)
+// Launch shapes of the CG kernels (tuned, else the default)
+static void cg_shapes(Ctx &ctx, const Gauge &gauge, CgVectors &v)
 {
-    LaunchShape sh = default_hop_shape(gauge.ref(prec, recon), nrhs);
-    if (ctx.tuner) ctx.tuner->lookup(tune_key(ctx, gauge.temporal ? "hop_tg" : "hop", gauge.g, prec, recon, nrhs), sh);
-    return sh;
+    v.hop_shape = v.normal_shape = default_hop_shape(gauge.ref(v.prec, v.recon), v.nrhs);
+    if (!ctx.tuner) return;
+    const bool tg = gauge.temporal;
+    ctx.tuner->lookup(tune_key(ctx, tg ? "hop_tg" : "hop", gauge.g, v.prec, v.recon, v.nrhs), v.hop_shape);
+    ctx.tuner->lookup(tune_key(ctx, tg ? "normal_dot_tg" : "normal_dot", gauge.g, v.prec, v.recon, v.nrhs),
+                      v.normal_shape);
 }
 
-void cg_iteration(Ctx &ctx, const Gauge &gauge, CgVectors &v, hipStream_t s, bool with_reliable)
+static void cg_iteration(Ctx &ctx, const Gauge &gauge, CgVectors &v, hipStream_t s, bool with_reliable)
 {
-    const LaunchShape sh = cg_hop_shape(ctx, gauge, v.prec, v.recon, v.nrhs);
-    LaunchShape shd = default_hop_shape(gauge.ref(v.prec, v.recon), v.nrhs);
-    if (ctx.tuner) {
-        const bool tg = gauge.temporal;
-        ctx.tuner->lookup(tune_key(ctx, tg ? "normal_dot_tg" : "normal_dot", gauge.g, v.prec, v.recon, v.nrhs), shd);
-    }
     // 1. t = D_oe p
     prof_begin(ctx, s);
-    launch_hop_gated(gauge.g, gauge.ref(v.prec, v.recon), v.prec, v.recon, 0, 1, v.nrhs, v.p, v.t, v.state, 1, sh, s);
+    launch_hop_gated(gauge.g, gauge.ref(v.prec, v.recon), v.prec, v.recon, 0, 1, v.nrhs, v.p, v.t, v.state, 1,
+                     v.hop_shape, s);
     prof_end(ctx, v.prec, v.recon, gauge.vh * v.nrhs, s);
-    // 2. q = m^2 p - D_eo t, <p,q>
-    launch_normal_dot_shape(gauge, v, shd, s);
-    // 3. update
-    int nd_blocks = (int)((gauge.vh + shd.block - 1) / shd.block);
-    if (nd_blocks > FOLD_ALPHA_MAX) {
-        launch_finalize(v, v.partials, nd_blocks, FIN_DOT, 0, 0, s);
-        nd_blocks = 0;
-    }
-    if (v.acc_prec == F64) launch_blas<F64, F64>(gauge, v, 0, nd_blocks, s);
-    else if (v.prec == F32) launch_blas<F32, F32>(gauge, v, 0, nd_blocks, s);
-    else launch_blas<F32, F16>(gauge, v, 0, nd_blocks, s);
-    // FP64 residual group (gated), after the x step it needs
-    if (with_reliable) {
-        if (v.acc_prec == F64) launch_blas<F64, F64>(gauge, v, 2, 0, s);
-        else if (v.prec == F32) launch_blas<F32, F32>(gauge, v, 2, 0, s);
-        else launch_blas<F32, F16>(gauge, v, 2, 0, s);
-        cg_residual_group(ctx, gauge, v, 2, 0, s);
-    }
-    // 4. p = r + beta p
-    if (v.acc_prec == F64) launch_blas<F64, F64>(gauge, v, 1, 0, s);
-    else if (v.prec == F32) launch_blas<F32, F32>(gauge, v, 1, 0, s);
-    else launch_blas<F32, F16>(gauge, v, 1, 0, s);
+    // 2. q = m^2 p - D_eo t and the dots
+    launch_normal_dot_shape(gauge, v, v.normal_shape, s);
+    // 3. and 4. the scalars; x, r and p
+    const int nd_blocks = (int)((gauge.vh + v.normal_shape.block - 1) / v.normal_shape.block);
+    const int last = with_reliable ? 1 : 0;
+    if (v.acc_prec == F64) launch_step<F64, F64>(gauge, v, nd_blocks, last, s);
+    else if (v.prec == F32) launch_step<F32, F32>(gauge, v, nd_blocks, last, s);
+    else launch_step<F32, F16>(gauge, v, nd_blocks, last, s);
+    if (!with_reliable) return;
+    // FP64 residual group (gated), then the direction it owes
+    cg_residual_group(ctx, gauge, v, 2, 0, s);
+    if (v.acc_prec == F64) launch_pdir<F64, F64>(gauge, v, s);
+    else if (v.prec == F32) launch_pdir<F32, F32>(gauge, v, s);
+    else launch_pdir<F32, F16>(gauge, v, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -782,14 +777,19 @@ static void cg_initial_states(const lqs_cg_params &prm, int nrhs, const double *
     }
 }
 
-// Device workspace of one problem, every buffer starting on a 256-byte boundary.
+// Device workspace that a problem is charged with against the preallocated
+// region of the allocation-free solve (two reduction buffers of one double per
+// 64 sites).  The buffers of a solve whose normal kernel runs in blocks of 64 or
+// 128 threads (two sums a block) may need more, at most NOALLOC_SLACK_BYTES,
+// which the region holds in addition (a problem is charged at least 144 bytes a
+// site and side, so its sides have fewer than 2^19 sites together).
 size_t cg_workspace_bytes(const Gauge &gauge, const lqs_cg_params &prm, int nrhs)
 {
     auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
     const bool mixed = prm.inner_prec != F64;
     const size_t fp = field_bytes(gauge.g, prm.inner_prec, nrhs), fa = field_bytes(gauge.g, mixed ? F32 : F64, nrhs),
                  f64 = field_bytes(gauge.g, F64, nrhs);
-    const size_t part = sizeof(double) * (size_t)cg_partials_needed(gauge, nrhs) * nrhs;
+    const size_t part = sizeof(double) * std::max<size_t>(1024, (size_t)(gauge.vh + 63) / 64) * nrhs;
     size_t n = up(sizeof(CgState) * nrhs) + 2 * up(part) + 3 * up(fp) + up(fa);
     if (mixed) n += up(fa) + up(f64);
     return n;
@@ -874,13 +874,14 @@ struct CgRun {
         v.nrhs = nrhs;
         v.mass = pb.mass;
         (void)gauge().ref(v.prec, v.recon);  // format must exist
-        v.max_blocks = cg_partials_needed(gauge(), nrhs);
+        cg_shapes(ctx, gauge(), v);
+        v.max_blocks = cg_partials_needed(gauge(), v.normal_shape.block);
         sbytes = sizeof(CgState) * nrhs;
         // every size is checked before the first launch
         const size_t need = cg_workspace_bytes(gauge(), prm, nrhs);
-        LQS_REQUIRE(!arena || need <= arena_bytes, LQS_EINVAL,
+        LQS_REQUIRE(!arena || need <= NOALLOC_SCRATCH_BYTES, LQS_EINVAL,
                     "solve needs " + std::to_string(need) + " bytes of workspace, the preallocated region holds " +
-                        std::to_string(arena_bytes));
+                        std::to_string(NOALLOC_SCRATCH_BYTES));
         const int64_t fp = field_bytes(g, v.prec, nrhs), fa = field_bytes(g, v.acc_prec, nrhs),
                       f64 = field_bytes(g, F64, nrhs);
         v.state = (CgState *)buf("cg.state", sbytes);
@@ -929,12 +930,14 @@ struct CgRun {
     }
 
     // queue one round of iterations and an asynchronous poll of the state.
-    // With graphs the round is captured once (the kernels read their scalars
+    // With graphs the first round runs eagerly, so that the GPU works while
+    // the host captures and instantiates (150-200 us of an idle GPU otherwise,
+    // at the start of every solve); the round is then captured once (the kernels read their scalars
     // and gates from the device state, so every replay is the same work) and
     // replayed; the round holds no memset or host synchronisation.
     void enqueue()
     {
-        if (use_graph) {
+        if (use_graph && enqueued > 0) {
             if (!exec) {
                 LQS_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
                 try {
@@ -970,6 +973,14 @@ struct CgRun {
         bool all = true;
         for (int r = 0; r < nrhs; ++r) all &= final_phase(h[r].phase);
         if (all || enqueued > cap) done = true;
+    }
+
+    // wait for the state the initial residuals left
+    void check_initial()
+    {
+        LQS_HIP(hipMemcpyAsync(hs[0], v.state, sbytes, hipMemcpyDeviceToHost, s));
+        LQS_HIP(hipStreamSynchronize(s));
+        decide(hs[0]);
     }
 
     // with two polls in flight, wait for the older one and decide
@@ -1051,6 +1062,10 @@ void cg_solve_one(Ctx &ctx, const lqs_problem &pb, const lqs_cg_params &prm, lqs
         if (masses) run.masses = *masses;
         run.setup();
         try {
+            // one mass per column: the multi-shift solver's check of solutions
+            // that mostly meet the target already; two rounds of gated launches
+            // cost more than waiting for the initial residuals
+            if (masses && prm.use_x0) run.check_initial();
             while (!run.done) {
                 run.enqueue();
                 run.check();
@@ -1138,7 +1153,7 @@ void cg_solve_concurrent(Ctx &ctx, int nprob, const lqs_problem *probs, const lq
 // stream (no graphs, no events, no pinned host buffers), with the kernels of
 // cg_solve and the same launch shapes.
 
-static __device__ __align__(256) char scratch[NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) char scratch[NOALLOC_SCRATCH_BYTES + NOALLOC_SLACK_BYTES];
 
 static std::mutex scratch_mu;
 static void *scratch_ptr[NOALLOC_MAX_DEVICES];
@@ -1174,7 +1189,7 @@ void cg_solve_noalloc_impl(Ctx &ctx, const lqs_problem &pb, const lqs_cg_params 
     CgState host[2 * 16];
     CgRun run(ctx, pb, prm, stats, s, "", std::chrono::steady_clock::now());
     run.arena = (char *)ctx.noalloc_scratch;
-    run.arena_bytes = NOALLOC_SCRATCH_BYTES;
+    run.arena_bytes = NOALLOC_SCRATCH_BYTES + NOALLOC_SLACK_BYTES;
     run.arena_host = host;
     try {
         run.setup();

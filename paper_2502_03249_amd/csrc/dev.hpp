@@ -734,6 +734,62 @@ __device__ __forceinline__ double block_sum(double v)
     return s;
 }
 
+// Sums of N values (a power of two, at most 16) over the wave.  Each of the
+// first log2 N exchange steps halves the values a lane carries, so N sums
+// take N - 1 + 6 - log2 N exchanges instead of 6 N; the additions are those of
+// wave_sum, in the same pairs (same bits).  Returns the sum of value `idx`.
+template <int N> __device__ __forceinline__ double wave_sums(double (&v)[N], int &idx)
+{
+    const int lane = threadIdx.x & 63;
+    idx = 0;
+    int off = 32;
+#pragma unroll
+    for (int n = N; n > 1; n >>= 1, off >>= 1) {
+        const bool up = lane & off;
+        idx = 2 * idx + (up ? 1 : 0);
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            if (i >= n / 2) break;
+            const double keep = up ? v[i + n / 2] : v[i], send = up ? v[i] : v[i + n / 2];
+            v[i] = keep + __shfl_xor(send, off, 64);
+        }
+    }
+    double s = v[0];
+    for (; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    return s;
+}
+
+// Sums of N values over the block (blockDim.x a multiple of 64; red: one row
+// per wave).  block_sums: thread k < N gets sum k in v[0].  block_sums_all:
+// every thread gets all N.
+template <int N> __device__ __forceinline__ void block_sums(double (&v)[N], double (*red)[N])
+{
+    int idx;
+    const double s = wave_sums<N>(v, idx);
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    if ((lane & (64 / N - 1)) == 0) red[threadIdx.x >> 6][idx] = s;
+    __syncthreads();
+    if (threadIdx.x < N) {
+        double t = 0.0;
+        for (int w = 0; w < nw; ++w) t += red[w][threadIdx.x];
+        v[0] = t;
+    }
+}
+template <int N> __device__ __forceinline__ void block_sums_all(double (&v)[N], double (*red)[N])
+{
+    int idx;
+    const double s = wave_sums<N>(v, idx);
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    if ((lane & (64 / N - 1)) == 0) red[threadIdx.x >> 6][idx] = s;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        double t = 0.0;
+        for (int w = 0; w < nw; ++w) t += red[w][k];
+        v[k] = t;
+    }
+}
+
 // Fixed-order sum of n partials by one block (valid in every thread); the
 // loads are device-coherent, for partials written by other blocks of the
 // same kernel behind a grid barrier.

@@ -71,6 +71,9 @@ struct CgState {
     int32_t nreliable;
     int32_t restarts;
     int32_t max_iter;
+    int32_t rho_known;  // rho was measured (init, FP64 residual), not predicted by the last step
+    int32_t live;       // the last step's scalars are valid: its vector update is due
+    int32_t p_due;      // that update leaves p = r + beta p to the FP64 group
 };
 
 // Default reliable-update threshold delta of a mixed solve (an update when
@@ -215,12 +218,12 @@ struct CgVectors {
     void *t64;              // FP64 odd scratch (residual hop)
     CgState *state;         // nrhs records
     double *partials;       // nrhs * max_blocks (normal kernel, residual, init)
-    double *partials2;      // nrhs * max_blocks (update kernel)
-    int max_blocks;
+    double *partials2;      // nrhs * max_blocks (|r|^2 of the step kernel)
+    int max_blocks;         // doubles of partials per right-hand side
+    LaunchShape hop_shape, normal_shape;
 };
 void cg_init(Ctx &ctx, const Gauge &gauge, CgVectors &v, bool use_x0, hipStream_t s);
-void cg_iteration(Ctx &ctx, const Gauge &gauge, CgVectors &v, hipStream_t s, bool with_reliable);
-int cg_partials_needed(const Gauge &gauge, int nrhs);
+int cg_partials_needed(const Gauge &gauge, int normal_block);
 // gflops and gbytes_per_s of one right-hand side's stats from its iterations
 // and times (inner precision and link format of the iteration; nrhs
 // right-hand sides share the link reads)
@@ -244,6 +247,7 @@ void persistent_solve(Ctx &ctx, const std::vector<PersistentProblem> &probs, con
 size_t cg_workspace_bytes(const Gauge &gauge, const lqs_cg_params &prm, int nrhs);
 // cg.hip: the allocation-free solve and its per-device scratch array
 constexpr size_t NOALLOC_SCRATCH_BYTES = LQS_NOALLOC_SCRATCH_BYTES;
+constexpr size_t NOALLOC_SLACK_BYTES = (size_t)512 << 10;  // see cg_workspace_bytes
 constexpr int NOALLOC_MAX_DEVICES = 64;
 void *noalloc_scratch(int device);
 void cg_solve_noalloc_impl(Ctx &ctx, const lqs_problem &pb, const lqs_cg_params &prm, lqs_cg_stats *stats,

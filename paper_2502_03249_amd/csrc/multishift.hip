@@ -14,11 +14,11 @@
 // stops updating once |zeta| |r| meets the target.  This is the multi-mass
 // solve a rational-approximation HMC needs for staggered fermions.
 //
-// One iteration: the base hop and fused normal operator (shared with the
-// plain solver), a finalize for alpha and every zeta, the base update
-// (x_0, r, |r|^2), a finalize for beta, and one kernel that advances every
-// shifted solution x_i += alpha_i p_i with the p_i it reads anyway and then
-// every search direction (one read of each p_i per iteration, not two).  The recurrence runs in FP64, or with the search
+// One iteration: the base hop and fused normal operator with its two dots
+// (shared with the plain solver), one one-block kernel for every scalar of the
+// step (alpha, beta, each zeta, alpha_i, beta_i; |r - alpha q|^2 is predicted
+// from the dots, see cg.hip), and one kernel that advances x_0, r, p_0 and every
+// x_i, p_i with one read of each.  The recurrence runs in FP64, or with the search
 // directions and the operator in FP32 or FP16 storage and the residual and
 // the solutions in FP32.  In the mixed recurrence the base system takes the
 // reliable updates of the mixed-precision CG: every K iterations, or when
@@ -46,7 +46,7 @@ static constexpr int MS_BLOCK = 256;
 
 struct ShiftState {
     double sigma;                    // m_i^2 - m_0^2
-    double zeta, zeta_prev, zeta_next;
+    double zeta, zeta_prev;
     double alpha, beta;
     int32_t active;                  // still above the target
     int32_t iters;
@@ -60,109 +60,82 @@ struct ShiftPtrs {
                                      // (entry nshift: the base, for the final flush)
 };
 
-__global__ void __launch_bounds__(1024) ms_finalize_dot(CgState *base, ShiftState *sh, int nshift,
-                                                        const double *partials, int nblocks)
+// Every scalar of one iteration from the base's <p,q>, <q,q> (partials) and
+// |r|^2 as the last step summed it (rr_partials, at most 1024; unused while
+// rho holds a measured one).  `last`: the FP64 group follows this iteration.
+__global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh, int nshift, const double *partials,
+                                                   const double *rr_partials, int nblocks, int nr_blocks, int last)
 {
     CgState &S = *base;
-    if (S.phase != CG_RUNNING) return;
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < nblocks; i += blockDim.x) acc += partials[i];
-    const double pq = block_sum(acc);
-    if (threadIdx.x != 0) return;
-    for (int i = 0; i < nshift; ++i) sh[i].xupd = 0;
-    if (!isfinite(pq)) {
-        S.phase = CG_NONFINITE;
-        return;
+    const int phase = S.phase;
+    double v[4] = {0.0, 0.0, (int)threadIdx.x < nr_blocks ? rr_partials[threadIdx.x] : 0.0, 0.0};
+    const double2 *p2 = (const double2 *)partials;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nblocks; i += blockDim.x) {
+        const double2 a = p2[i];
+        v[0] += a.x;
+        v[1] += a.y;
     }
-    if (!(pq > 0.0)) {
-        S.phase = CG_BREAKDOWN;
-        return;
-    }
-    const double a_prev = S.alpha, b_prev = S.beta, a = S.rho / pq;
-    for (int i = 0; i < nshift; ++i) {
-        ShiftState &T = sh[i];
-        if (!T.active) continue;
+    __shared__ double red[16][4];
+    block_sums_all<4>(v, red);
+    if (threadIdx.x >= 64) return;
+    const double pq = v[0], qq = v[1], rr = S.rho_known ? S.rho : v[2];
+    // lane i < nshift advances shift i; lane 0 the base
+    const int i = threadIdx.x;
+    const bool mine = i < nshift;
+    ShiftState T{};
+    if (mine) T = sh[i];
+    const bool ok = phase == CG_RUNNING && isfinite(pq) && pq > 0.0;
+    const double a_prev = S.alpha, b_prev = S.beta, a = ok ? rr / pq : 0.0;
+    double r2 = fma(a * a, qq, -rr);
+    if (r2 < 0.0) r2 = 0.0;
+    const double b = rr > 0.0 ? r2 / rr : 0.0;
+    const bool finite = isfinite(r2);
+    T.xupd = 0;
+    if (mine && ok && finite && T.active) {
         const double z = T.zeta, zp = T.zeta_prev;
         const double den = zp * a_prev * (1.0 + a * T.sigma) + a * b_prev * (zp - z);
-        const double zn = z * zp * a_prev / den;
-        T.zeta_next = zn;
-        T.alpha = a * zn / z;
-        T.xupd = 1;
-    }
-    S.alpha = a;
-}
-
-// x_0 += alpha p_0, r -= alpha q, |r|^2 of the base.  p_0 and q are stored
-// as PI, r and x_0 as PR; the arithmetic is FP64.
-template <int PI, int PR>
-__global__ void __launch_bounds__(MS_BLOCK) ms_update(int vh, char *x0, char *r, const char *p0, const char *q,
-                                                      const CgState *base, double *partials)
-{
-    typedef typename RealOf<PR>::type TR;
-    if (base->phase != CG_RUNNING) return;
-    const double a = base->alpha;
-    double local = 0.0;
-    for (int cb = blockIdx.x * blockDim.x + threadIdx.x; cb < vh; cb += gridDim.x * blockDim.x) {
-        const V3<double> pv = vcast<double>(SpinorIO<PI>::load(p0, vh, cb));
-        const V3<double> qv = vcast<double>(SpinorIO<PI>::load(q, vh, cb));
-        V3<double> xv = vcast<double>(SpinorIO<PR>::load(x0, vh, cb));
-        V3<double> rv = vcast<double>(SpinorIO<PR>::load(r, vh, cb));
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            xv.c[c].re += a * pv.c[c].re;
-            xv.c[c].im += a * pv.c[c].im;
-            rv.c[c].re -= a * qv.c[c].re;
-            rv.c[c].im -= a * qv.c[c].im;
-        }
-        const V3<TR> rs = vcast<TR>(rv);
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            local += (double)rs.c[c].re * (double)rs.c[c].re + (double)rs.c[c].im * (double)rs.c[c].im;
-        SpinorIO<PR>::store(x0, vh, cb, vcast<TR>(xv));
-        SpinorIO<PR>::store(r, vh, cb, rs);
-    }
-    const double s = block_sum(local);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s;
-}
-
-__global__ void __launch_bounds__(1024) ms_finalize_update(CgState *base, ShiftState *sh, int nshift,
-                                                           const double *partials, int nblocks)
-{
-    CgState &S = *base;
-    if (S.phase != CG_RUNNING) return;
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < nblocks; i += blockDim.x) acc += partials[i];
-    const double r2 = block_sum(acc);
-    if (threadIdx.x != 0) return;
-    S.rho_old = S.rho;
-    S.rho = r2;
-    S.beta = r2 / S.rho_old;
-    S.iters += 1;
-    int any = 0;
-    for (int i = 0; i < nshift; ++i) {
-        ShiftState &T = sh[i];
-        if (!T.active) continue;
-        const double ratio = T.zeta_next / T.zeta;
-        T.beta = S.beta * ratio * ratio;
-        T.zeta_prev = T.zeta;
-        T.zeta = T.zeta_next;
+        const double zn = z * zp * a_prev / den, ratio = zn / z;
+        T.alpha = a * ratio;
+        T.beta = b * ratio * ratio;
+        T.zeta_prev = z;
+        T.zeta = zn;
         T.iters += 1;
-        if (T.zeta * T.zeta * r2 <= S.stop2) T.active = 0;
-        any |= T.active;
+        T.xupd = 1;
+        if (zn * zn * r2 <= S.stop2) T.active = 0;
     }
+    if (mine) sh[i] = T;
+    const bool any = __any(mine && T.active);
+    if (i != 0) return;
+    S.live = 0;
+    S.p_due = 0;
+    if (phase != CG_RUNNING) return;
+    if (!ok) {
+        S.phase = isfinite(pq) ? CG_BREAKDOWN : CG_NONFINITE;
+        return;
+    }
+    S.rho_known = 0;
+    S.iters += 1;
     S.since_rel += 1;
-    if (!isfinite(r2)) {
+    if (!finite) {
         S.phase = CG_NONFINITE;
         return;
     }
+    S.alpha = a;
+    S.beta = b;
+    S.rho_old = rr;
+    S.rho = r2;
+    S.live = 1;
     if (r2 > S.max_rho) S.max_rho = r2;
     if ((r2 <= S.stop2 && !any) || S.iters >= S.max_iter) {
         S.phase = CG_INNER_DONE;
+        S.p_due = 1;
         // mixed: the FP64 residual of the base decides (and resumes when it is above the target)
         if (S.rel_interval > 0) S.reliable_pending = 1;
         return;
     }
     if (S.rel_interval > 0 && (S.since_rel >= S.rel_interval || r2 < S.delta2 * S.max_rho)) S.reliable_pending = 1;
+    if (last && S.reliable_pending) S.p_due = 1;
 }
 
 // Mixed recurrence, reliable update: add every FP32 solution into its FP64
@@ -189,7 +162,7 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_accumulate(int vh, const ShiftPtr
 }
 
 // after a reliable update of the base: beta_i = beta (zeta_{k+1} / zeta_k)^2
-// with the base's new beta (the same value ms_finalize_update set otherwise)
+// with the base's new beta (the same value ms_scalars set otherwise)
 __global__ void ms_rebeta(const CgState *base, ShiftState *sh, int nshift)
 {
     if (threadIdx.x != 0 || base->phase != CG_RUNNING) return;
@@ -201,45 +174,66 @@ __global__ void ms_rebeta(const CgState *base, ShiftState *sh, int nshift)
     }
 }
 
-// x_i += alpha_i p_i at site cb, p_i already loaded
-template <int PI, int PR>
-__device__ __forceinline__ void ms_shift_x(const ShiftPtrs *ptr, int i, int vh, int cb, double ai, const V3<double> &pi)
-{
-    typedef typename RealOf<PR>::type TR;
-    V3<double> xi = vcast<double>(SpinorIO<PR>::load(ptr->x[i], vh, cb));
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        xi.c[c].re += ai * pi.c[c].re;
-        xi.c[c].im += ai * pi.c[c].im;
-    }
-    SpinorIO<PR>::store(ptr->x[i], vh, cb, vcast<TR>(xi));
-}
-
-// x_i += alpha_i p_i where alpha_i was formed this iteration; p_0 = r + beta p_0;
-// p_i = zeta_i r + beta_i p_i for active shifts.  (One block grid per system
-// instead of the loop over the shifts measured slower: 0.41 vs 0.37 s for 8
-// masses on 64^3 x 16 in FP64, as every system re-read the residual.)
-template <int PI, int PR>
-__global__ void __launch_bounds__(MS_BLOCK) ms_pupdate(int vh, const char *r, char *p0, const ShiftPtrs *ptr,
-                                                       int nshift, const CgState *base, const ShiftState *sh)
+// x_0 += alpha p_0, r -= alpha q, p_0 = r + beta p_0 and the block partials of
+// |r|^2; for every shift, x_i += alpha_i p_i and p_i = zeta_i r + beta_i p_i.  Vectors are stored as PI
+// (p, q) and PR (x, r); the arithmetic is FP64.  DIRS: the directions alone
+// (the FP64 group's end, for the updates it was left).  Bound by HBM: 4 vectors
+// a site and shift and 7 for the base.  (One block grid per system instead of
+// the loop over the shifts measured slower: 0.41 vs 0.37 s for 8 masses on
+// 64^3 x 16 in FP64, as every system re-read the residual.)
+template <int PI, int PR, bool DIRS>
+__global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, char *p0, const char *q,
+                                                    const ShiftPtrs *ptr, int nshift, const CgState *base,
+                                                    const ShiftState *sh, double *rr_partials)
 {
     typedef typename RealOf<PI>::type TI;
-    if (base->phase != CG_RUNNING) return;
-    const double b = base->beta;
+    typedef typename RealOf<PR>::type TR;
+    if (DIRS ? (!base->p_due || base->phase != CG_RUNNING) : !base->live) return;
+    const double a = base->alpha, b = base->beta;
+    const bool pdir = DIRS || !base->p_due;
+    double local = 0.0;
     for (int cb = blockIdx.x * blockDim.x + threadIdx.x; cb < vh; cb += gridDim.x * blockDim.x) {
-        const V3<double> rv = vcast<double>(SpinorIO<PR>::load(r, vh, cb));
         V3<double> pv = vcast<double>(SpinorIO<PI>::load(p0, vh, cb));
+        V3<double> rv = vcast<double>(SpinorIO<PR>::load(r, vh, cb));
+        if (!DIRS) {
+            const V3<double> qv = vcast<double>(SpinorIO<PI>::load(q, vh, cb));
+            V3<double> xv = vcast<double>(SpinorIO<PR>::load(x0, vh, cb));
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            pv.c[c].re = rv.c[c].re + b * pv.c[c].re;
-            pv.c[c].im = rv.c[c].im + b * pv.c[c].im;
+            for (int c = 0; c < 3; ++c) {
+                xv.c[c].re += a * pv.c[c].re;
+                xv.c[c].im += a * pv.c[c].im;
+                rv.c[c].re -= a * qv.c[c].re;
+                rv.c[c].im -= a * qv.c[c].im;
+            }
+            SpinorIO<PR>::store(x0, vh, cb, vcast<TR>(xv));
+            const V3<TR> rs = vcast<TR>(rv);
+            SpinorIO<PR>::store(r, vh, cb, rs);
+            rv = vcast<double>(rs);  // the norm and the directions follow the stored residual
+#pragma unroll
+            for (int c = 0; c < 3; ++c) local += rv.c[c].re * rv.c[c].re + rv.c[c].im * rv.c[c].im;
         }
-        SpinorIO<PI>::store(p0, vh, cb, vcast<TI>(pv));
+        if (pdir) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                pv.c[c].re = rv.c[c].re + b * pv.c[c].re;
+                pv.c[c].im = rv.c[c].im + b * pv.c[c].im;
+            }
+            SpinorIO<PI>::store(p0, vh, cb, vcast<TI>(pv));
+        }
         for (int i = 0; i < nshift; ++i) {
-            const bool xu = sh[i].xupd != 0, act = sh[i].active != 0;
+            const bool xu = !DIRS && sh[i].xupd != 0, act = pdir && sh[i].active != 0;
             if (!xu && !act) continue;
             V3<double> pi = vcast<double>(SpinorIO<PI>::load(ptr->p[i], vh, cb));
-            if (xu) ms_shift_x<PI, PR>(ptr, i, vh, cb, sh[i].alpha, pi);
+            if (xu) {
+                const double ai = sh[i].alpha;
+                V3<double> xi = vcast<double>(SpinorIO<PR>::load(ptr->x[i], vh, cb));
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    xi.c[c].re += ai * pi.c[c].re;
+                    xi.c[c].im += ai * pi.c[c].im;
+                }
+                SpinorIO<PR>::store(ptr->x[i], vh, cb, vcast<TR>(xi));
+            }
             if (!act) continue;
             const double z = sh[i].zeta, bi = sh[i].beta;
 #pragma unroll
@@ -250,23 +244,9 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_pupdate(int vh, const char *r, ch
             SpinorIO<PI>::store(ptr->p[i], vh, cb, vcast<TI>(pi));
         }
     }
-}
-
-// After the recurrence: the x_i updates of the last iteration, whose p-update
-// was skipped because that iteration ended the recurrence (alpha_i formed,
-// base no longer running).  Nothing to do while the base still runs (the
-// iteration cap of the host loop): its p-update has applied them.
-template <int PI, int PR>
-__global__ void __launch_bounds__(MS_BLOCK) ms_xflush(int vh, const ShiftPtrs *ptr, int nshift, const CgState *base,
-                                                      const ShiftState *sh)
-{
-    if (base->phase == CG_RUNNING) return;
-    for (int cb = blockIdx.x * blockDim.x + threadIdx.x; cb < vh; cb += gridDim.x * blockDim.x)
-        for (int i = 0; i < nshift; ++i) {
-            if (!sh[i].xupd) continue;
-            const V3<double> pi = vcast<double>(SpinorIO<PI>::load(ptr->p[i], vh, cb));
-            ms_shift_x<PI, PR>(ptr, i, vh, cb, sh[i].alpha, pi);
-        }
+    if (DIRS) return;
+    const double s = block_sum(local);
+    if (threadIdx.x == 0) rr_partials[blockIdx.x] = s;
 }
 
 // x_0 = x_i = 0, r = p_0 = p_i = b, |b|^2 (of b in FP64)
@@ -303,6 +283,7 @@ __global__ void __launch_bounds__(1024) ms_finalize_init(CgState *base, const do
     S.b2 = b2;
     S.stop2 *= b2;
     S.rho = b2;
+    S.rho_known = 1;
     S.max_rho = b2;
     S.true_r2 = b2;
     S.alpha = 1.0;  // alpha_{-1}
@@ -349,8 +330,11 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
     v.xlo = xr[base];
     v.b = (double *)b;
     v.t64 = mixed ? ctx.workspace("ms.t64", field_bytes(g, F64, 1)) : nullptr;
-    v.max_blocks = cg_partials_needed(gauge, 1);
+    const LinkRef L = gauge.ref(PI, v.recon);
+    const LaunchShape sh = default_hop_shape(L, 1);
+    v.max_blocks = cg_partials_needed(gauge, sh.block);
     v.partials = (double *)ctx.workspace("ms.partials", sizeof(double) * (size_t)v.max_blocks);
+    v.partials2 = (double *)ctx.workspace("ms.partials2", sizeof(double) * 1024);
     v.state = (CgState *)ctx.workspace("ms.state", sizeof(CgState));
     ShiftPtrs hp{};
     std::vector<ShiftState> hsh(nshift);
@@ -406,48 +390,57 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
     hipLaunchKernelGGL(ms_finalize_init, dim3(1), dim3(1024), 0, s, v.state, (const double *)v.partials, blocks);
     LQS_HIP(hipGetLastError());
 
-    const LinkRef L = gauge.ref(PI, v.recon);
-    const LaunchShape sh = default_hop_shape(L, 1);
+    // Rounds of eight iterations with two polls of the state in flight: the
+    // next round is queued before the host waits for this one's poll, so the
+    // GPU does not idle between rounds; the kernels of a round queued after the
+    // recurrence has ended return at once.
     const int nd_blocks = (vh + sh.block - 1) / sh.block;
-    CgState hs{};
+    CgState *hs2 = (CgState *)ctx.pinned("ms.host", 2 * sizeof(CgState));
+    struct Events {
+        hipEvent_t e[2] = {nullptr, nullptr};
+        ~Events()
+        {
+            for (hipEvent_t x : e)
+                if (x) (void)hipEventDestroy(x);
+        }
+    } ev;
+    for (hipEvent_t &e : ev.e) LQS_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     int64_t enqueued = 0;
     const int64_t cap = (int64_t)prm.max_iter + 64;
-    while (true) {
+    for (int round = 0;; ++round) {
         for (int i = 0; i < 8; ++i) {
+            const int group = mixed && (i & 3) == 3;
             launch_hop_gated(g, L, PI, v.recon, 0, 1, 1, v.p, v.t, v.state, 1, sh, s);
             launch_normal_dot_shape(gauge, v, sh, s);
-            hipLaunchKernelGGL(ms_finalize_dot, dim3(1), dim3(1024), 0, s, v.state, dsh, nshift,
-                               (const double *)v.partials, nd_blocks);
-            LQS_MS_PREC(hipLaunchKernelGGL((ms_update<P_I, P_R>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh, xr[base],
-                                           (char *)v.r, (const char *)v.p, (const char *)v.q,
-                                           (const CgState *)v.state, v.partials));
-            hipLaunchKernelGGL(ms_finalize_update, dim3(1), dim3(1024), 0, s, v.state, dsh, nshift,
-                               (const double *)v.partials, blocks);
-            if (mixed && (i & 3) == 3) {
+            hipLaunchKernelGGL(ms_scalars, dim3(1), dim3(1024), 0, s, v.state, dsh, nshift, (const double *)v.partials,
+                               (const double *)v.partials2, nd_blocks, blocks, group);
+            LQS_MS_PREC(hipLaunchKernelGGL((ms_step<P_I, P_R, false>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh, xr[base],
+                                           (char *)v.r, (char *)v.p, (const char *)v.q, (const ShiftPtrs *)dp, nshift,
+                                           (const CgState *)v.state, (const ShiftState *)dsh, v.partials2));
+            if (group) {
                 // reliable update (gated on the base's pending flag)
                 hipLaunchKernelGGL((ms_accumulate<F32>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh, (const ShiftPtrs *)dp,
                                    nshift, (const CgState *)v.state, 1);
                 cg_residual_group(ctx, gauge, v, 2, 0, s);
                 hipLaunchKernelGGL(ms_rebeta, dim3(1), dim3(64), 0, s, (const CgState *)v.state, dsh, nshift);
+                LQS_MS_PREC(hipLaunchKernelGGL((ms_step<P_I, P_R, true>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh,
+                                               xr[base], (char *)v.r, (char *)v.p, (const char *)v.q,
+                                               (const ShiftPtrs *)dp, nshift, (const CgState *)v.state,
+                                               (const ShiftState *)dsh, v.partials2));
             }
-            LQS_MS_PREC(hipLaunchKernelGGL((ms_pupdate<P_I, P_R>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh,
-                                           (const char *)v.r, (char *)v.p, (const ShiftPtrs *)dp, nshift,
-                                           (const CgState *)v.state, (const ShiftState *)dsh));
             LQS_HIP(hipGetLastError());
         }
         enqueued += 8;
-        LQS_HIP(hipMemcpyAsync(&hs, v.state, sizeof(CgState), hipMemcpyDeviceToHost, s));
-        LQS_HIP(hipStreamSynchronize(s));
-        if (hs.phase != CG_RUNNING || enqueued > cap) break;
+        LQS_HIP(hipMemcpyAsync(hs2 + (round & 1), v.state, sizeof(CgState), hipMemcpyDeviceToHost, s));
+        LQS_HIP(hipEventRecord(ev.e[round & 1], s));
+        if (round == 0) continue;
+        LQS_HIP(hipEventSynchronize(ev.e[(round - 1) & 1]));
+        if (hs2[(round - 1) & 1].phase != CG_RUNNING || enqueued > cap) break;
     }
-    if (nshift) {
-        LQS_MS_PREC(hipLaunchKernelGGL((ms_xflush<P_I, P_R>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh,
-                                       (const ShiftPtrs *)dp, nshift, (const CgState *)v.state,
-                                       (const ShiftState *)dsh));
-    }
-    LQS_HIP(hipGetLastError());
     if (nshift) LQS_HIP(hipMemcpyAsync(hsh.data(), dsh, sizeof(ShiftState) * nshift, hipMemcpyDeviceToHost, s));
+    LQS_HIP(hipMemcpyAsync(hs2, v.state, sizeof(CgState), hipMemcpyDeviceToHost, s));
     LQS_HIP(hipStreamSynchronize(s));
+    const CgState hs = hs2[0];
 
 #undef LQS_MS_PREC
     if (mixed) {
