@@ -2,7 +2,7 @@
 // M = m^2 - D_eo D_oe (the inversion of Sec. 4.2), in FP64 or with a
 // low-precision inner iteration and FP64 residual updates.
 //
-// Per iteration three or four kernels run back to back on one stream:
+// Per iteration four kernels run back to back on one stream:
 //   1. t = D_oe p                                      (hop)
 //   2. q = m^2 p - D_eo t, <p,q> and <q,q>              (hop + fused dots)
 //   3. the scalars of the step                          (one block per side)
@@ -31,98 +31,12 @@
 #include <cmath>
 #include <mutex>
 
+#include "cg_step.hpp"
 #include "hop.hpp"
 
 namespace lqs {
 
 static constexpr int BLAS_BLOCK = 256;
-// ---------------------------------------------------------------------------
-// Scalars of one iteration from its dots (rr: |r|^2 as the last step summed it,
-// unused while S.rho holds a measured one).  `live`: this iteration's update is
-// due; `p_due`: the direction update is left to the FP64 group that closes the
-// round (`last`: the group follows this iteration).
-
-__device__ void cg_step_scalars(CgState &S, double pq, double qq, double rr, int last)
-{
-    if (S.rho_known) rr = S.rho;
-    S.live = 0;
-    S.p_due = 0;
-    if (!isfinite(pq)) {
-        S.phase = CG_NONFINITE;
-        return;
-    }
-    if (!(pq > 0.0)) {
-        S.phase = CG_BREAKDOWN;
-        return;
-    }
-    S.alpha = rr / pq;
-    double r2 = fma(S.alpha * S.alpha, qq, -rr);
-    if (r2 < 0.0) r2 = 0.0;  // rounding, when the step removes the residual altogether
-    S.rho_known = 0;
-    S.iters += 1;
-    S.since_rel += 1;
-    if (!isfinite(r2)) {
-        S.phase = CG_NONFINITE;
-        return;
-    }
-    S.rho_old = rr;
-    S.rho = r2;
-    S.beta = rr > 0.0 ? r2 / rr : 0.0;
-    S.live = 1;
-    if (r2 > S.max_rho) S.max_rho = r2;
-    if (r2 <= S.stop2 || S.iters >= S.max_iter) {
-        S.phase = CG_INNER_DONE;
-        S.reliable_pending = 1;
-        S.p_due = 1;
-        return;
-    }
-    if (S.rel_interval > 0 && (S.since_rel >= S.rel_interval || r2 < S.delta2 * S.max_rho)) S.reliable_pending = 1;
-    if (last && S.reliable_pending) S.p_due = 1;
-}
-
-// mode: 0 reliable update inside the iteration, 1 initial residual, 2 measure
-// only, 3 periodic update with the reconstructed FP64 links (a residual that
-// meets the target is handed on, still pending, to the mode-0 check with the
-// stored links instead of ending the solve)
-__device__ void fin_residual(CgState &S, double r2, int mode)
-{
-    S.true_r2 = r2;
-    if (mode == 2) return;
-    if (mode == 3 && isfinite(r2) && r2 <= S.stop2) {
-        S.phase = CG_INNER_DONE;
-        return;
-    }
-    S.rho_known = 1;  // wherever the iteration goes on, S.rho is set below
-    if (mode == 1) {
-        S.rho = r2;
-        S.max_rho = r2;
-        S.phase = isfinite(r2) ? (r2 <= S.stop2 ? CG_CONVERGED : CG_RUNNING) : CG_NONFINITE;
-        return;
-    }
-    S.nreliable += 1;
-    S.reliable_pending = 0;
-    S.since_rel = 0;
-    if (!isfinite(r2)) {
-        S.phase = CG_NONFINITE;
-    } else if (r2 <= S.stop2) {
-        S.phase = CG_CONVERGED;
-    } else if (S.iters >= S.max_iter) {
-        S.phase = CG_MAXITER;
-    } else if (S.rel_interval == 0) {
-        // FP64 solver whose iterated residual drifted: restart from r = b - M x
-        S.rho = r2;
-        S.max_rho = r2;
-        S.beta = 0.0;
-        S.restarts += 1;
-        S.phase = CG_RUNNING;
-    } else {
-        // mixed precision: continue with the FP64 residual, keep p
-        S.beta = S.rho_old > 0.0 ? r2 / S.rho_old : 0.0;
-        S.rho = r2;
-        S.max_rho = r2;
-        S.phase = CG_RUNNING;
-    }
-}
 
 // ---------------------------------------------------------------------------
 // The new search direction r + beta p, in the accumulation precision (one

@@ -243,6 +243,11 @@ struct PersistentProblem {
 void persistent_solve(Ctx &ctx, const std::vector<PersistentProblem> &probs, const lqs_cg_params &prm,
                       lqs_cg_stats *stats, hipStream_t s);
 
+// small.hip: lattices that fit one compute unit each, one block per lattice
+bool small_fits(const std::vector<PersistentProblem> &probs, int prec);
+void small_solve(Ctx &ctx, const std::vector<PersistentProblem> &probs, const lqs_cg_params &prm, const CgState *init,
+                 CgState *out, unsigned long long *clk, hipStream_t s);
+
 // cg.hip: device workspace of one problem's solve
 size_t cg_workspace_bytes(const Gauge &gauge, const lqs_cg_params &prm, int nrhs);
 // cg.hip: the allocation-free solve and its per-device scratch array

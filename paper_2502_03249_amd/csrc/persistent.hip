@@ -429,6 +429,50 @@ void persistent_solve(Ctx &ctx, const std::vector<PersistentProblem> &probs, con
     const int pa = prec == F64 ? F64 : F32;
     const bool mixed = prec != F64;
 
+    std::vector<unsigned long long> hclk(2 * nlat);
+    int clk_khz = 0;
+    LQS_HIP(hipDeviceGetAttribute(&clk_khz, hipDeviceAttributeWallClockRate, ctx.device));
+    std::vector<CgState> init(nlat), hs(nlat);
+    const int rel_interval = mixed ? (prm.reliable_interval > 0 ? prm.reliable_interval : 100) : 0;
+    const double delta =
+        mixed ? (prm.reliable_delta > 0 ? prm.reliable_delta : default_reliable_delta(prm.inner_prec)) : 0.0;
+    for (auto &S : init) {
+        S = CgState{};
+        S.stop2 = prm.tol * prm.tol;
+        S.delta2 = delta * delta;
+        S.rel_interval = rel_interval;
+        S.max_iter = prm.max_iter;
+        S.phase = CG_RUNNING;
+    }
+    auto fill_stats = [&] {
+        const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+        for (int l = 0; l < nlat; ++l) {
+            const CgState &S = hs[l];
+            lqs_cg_stats &o = stats[l];
+            o.iters = S.iters;
+            o.reliable_updates = S.nreliable;
+            o.restarts = S.restarts;
+            o.true_rel_residual = S.b2 > 0 ? std::sqrt(S.true_r2 / S.b2) : 0.0;
+            o.seconds = secs;
+            o.device_seconds = clk_khz > 0 ? (double)(hclk[2 * l + 1] - hclk[2 * l]) / (1e3 * clk_khz) : 0.0;
+            cg_fill_rates(o, *probs[l].gauge, prec, recon, 1);
+            switch (S.phase) {
+            case CG_CONVERGED: o.status = LQS_OK; break;
+            case CG_BREAKDOWN: o.status = LQS_EBREAKDOWN; break;
+            case CG_NONFINITE: o.status = LQS_ENONFINITE; break;
+            default: o.status = LQS_ENOTCONV; break;
+            }
+        }
+    };
+
+    // A batch of lattices that all fit the registers of one compute unit each:
+    // the one-block solver, 1.3 to 4 times as fast there (small.hip)
+    if (small_fits(probs, prec)) {
+        small_solve(ctx, probs, prm, init.data(), hs.data(), hclk.data(), s);
+        fill_stats();
+        return;
+    }
+
     // fields and descriptors (partials sized for the smallest tile)
     std::vector<PLat> L(nlat);
     size_t part_total = 0;
@@ -459,21 +503,6 @@ void persistent_solve(Ctx &ctx, const std::vector<PersistentProblem> &probs, con
     GroupBar *bars = (GroupBar *)ctx.workspace("pcg.bar", bar_bytes);
     uint32_t *abort_flag = (uint32_t *)(bars + PMAX_LAT);
     unsigned long long *clk = (unsigned long long *)ctx.workspace("pcg.clk", 2 * sizeof(unsigned long long) * nlat);
-    std::vector<unsigned long long> hclk(2 * nlat);
-    int clk_khz = 0;
-    LQS_HIP(hipDeviceGetAttribute(&clk_khz, hipDeviceAttributeWallClockRate, ctx.device));
-    std::vector<CgState> init(nlat), hs(nlat);
-    const int rel_interval = mixed ? (prm.reliable_interval > 0 ? prm.reliable_interval : 100) : 0;
-    const double delta =
-        mixed ? (prm.reliable_delta > 0 ? prm.reliable_delta : default_reliable_delta(prm.inner_prec)) : 0.0;
-    for (auto &S : init) {
-        S = CgState{};
-        S.stop2 = prm.tol * prm.tol;
-        S.delta2 = delta * delta;
-        S.rel_interval = rel_interval;
-        S.max_iter = prm.max_iter;
-        S.phase = CG_RUNNING;
-    }
     const int max_trips = prm.max_iter + 8;
     uint32_t habort = 0;
 
@@ -554,24 +583,7 @@ void persistent_solve(Ctx &ctx, const std::vector<PersistentProblem> &probs, con
         ctx.tuner->save();
     }
     solve_once(best.block, best.rhs_per_thread);
-    const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-    for (int l = 0; l < nlat; ++l) {
-        const CgState &S = hs[l];
-        lqs_cg_stats &o = stats[l];
-        o.iters = S.iters;
-        o.reliable_updates = S.nreliable;
-        o.restarts = S.restarts;
-        o.true_rel_residual = S.b2 > 0 ? std::sqrt(S.true_r2 / S.b2) : 0.0;
-        o.seconds = secs;
-        o.device_seconds = clk_khz > 0 ? (double)(hclk[2 * l + 1] - hclk[2 * l]) / (1e3 * clk_khz) : 0.0;
-        cg_fill_rates(o, *probs[l].gauge, prec, recon, 1);
-        switch (S.phase) {
-        case CG_CONVERGED: o.status = LQS_OK; break;
-        case CG_BREAKDOWN: o.status = LQS_EBREAKDOWN; break;
-        case CG_NONFINITE: o.status = LQS_ENONFINITE; break;
-        default: o.status = LQS_ENOTCONV; break;
-        }
-    }
+    fill_stats();
 }
 
 }  // namespace lqs
