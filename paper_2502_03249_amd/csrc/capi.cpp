@@ -36,9 +36,81 @@ void *Ctx::workspace(const std::string &slot, size_t bytes)
         ws.erase(it);
     }
     void *p = nullptr;
-    LQS_HIP(hipMalloc(&p, bytes < 256 ? 256 : bytes));
+    hipError_t e = hipMalloc(&p, bytes < 256 ? 256 : bytes);
+    if (e == hipErrorOutOfMemory && links) {
+        (void)hipGetLastError();
+        links->drain();
+        e = hipMalloc(&p, bytes < 256 ? 256 : bytes);
+    }
+    LQS_HIP(e);
     ws[slot] = {p, bytes};
     return p;
+}
+
+void *LinkPool::take(size_t bytes, size_t &got)
+{
+    bytes = (bytes + 65535) & ~size_t(65535);
+    std::lock_guard<std::mutex> lock(mu);
+    auto best = blocks.end();
+    for (auto it = blocks.begin(); it != blocks.end(); ++it)
+        if (it->second >= bytes && it->second <= bytes + bytes / 8 && (best == blocks.end() || it->second < best->second))
+            best = it;
+    if (best != blocks.end()) {
+        void *p = best->first;
+        got = best->second;
+        cached -= got;
+        blocks.erase(best);
+        return p;
+    }
+    void *p = nullptr;
+    hipError_t e = hipMalloc(&p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        drain_locked();
+        e = hipMalloc(&p, bytes);
+    }
+    LQS_HIP(e);
+    got = bytes;
+    return p;
+}
+
+void LinkPool::give(void *p, size_t size)
+{
+    std::lock_guard<std::mutex> lock(mu);
+    try {
+        if (open && size <= LINK_POOL_BYTES) {
+            blocks.emplace_back(p, size);
+            cached += size;
+            p = nullptr;
+        }
+    } catch (const std::bad_alloc &) {
+    }
+    if (p) (void)hipFree(p);
+    while (cached > LINK_POOL_BYTES) {
+        (void)hipFree(blocks.front().first);
+        cached -= blocks.front().second;
+        blocks.pop_front();
+    }
+}
+
+void LinkPool::drain_locked()
+{
+    for (auto &b : blocks) (void)hipFree(b.first);
+    blocks.clear();
+    cached = 0;
+}
+
+void LinkPool::drain()
+{
+    std::lock_guard<std::mutex> lock(mu);
+    drain_locked();
+}
+
+void LinkPool::close()
+{
+    std::lock_guard<std::mutex> lock(mu);
+    open = false;
+    drain_locked();
 }
 
 void *Ctx::pinned(const std::string &slot, size_t bytes)
@@ -77,14 +149,21 @@ Ctx::~Ctx()
         (void)hipEventDestroy(e.first);
         (void)hipEventDestroy(e.second);
     }
+    if (links) links->close();
     if (tuner) tuner->save();
 }
 
+// Waits for the gauge's device, whichever is current, before its block may be
+// used again.
 Gauge::~Gauge()
 {
-    for (auto &row : fmt)
-        for (auto &p : row)
-            if (p) (void)hipFree(p);
+    if (!block) return;
+    int cur = -1;
+    if (hipGetDevice(&cur) != hipSuccess) cur = -1;
+    (void)hipSetDevice(pool->device);
+    (void)hipDeviceSynchronize();
+    pool->give(block, block_bytes);
+    if (cur >= 0) (void)hipSetDevice(cur);
 }
 
 }  // namespace lqs
@@ -182,6 +261,7 @@ lqs_status lqs_ctx_create(int32_t device, const char *tune_cache_path, lqs_ctx *
         try {
             c->noalloc_scratch = noalloc_scratch(device);
             c->tuner.reset(new Tuner(tune_cache_path));
+            c->links = std::make_shared<LinkPool>(device);
         } catch (...) {
             delete c;
             throw;
@@ -242,12 +322,22 @@ lqs_status lqs_gauge_create(lqs_ctx *ctx, const int32_t dims[4], const double *l
             g->temporal = temporal;
             g->pitch = temporal ? g->vh + TEMPORAL_PAD : g->vh;
             LinkOut packed;
+            // every format in one block, each from a 256-byte boundary
+            auto format_bytes = [&](int prec, int rc) -> size_t {
+                if (!(formats & LQS_FMT(prec, rc ? 12 : 18))) return 0;
+                return ((size_t)link_block_bytes_per_site(prec, rc ? 12 : 18) * g->pitch * 8 + 255) & ~size_t(255);
+            };
+            size_t total = 0, at = 0;
+            for (int prec = 0; prec < 3; ++prec)
+                for (int rc = 0; rc < 2; ++rc) total += format_bytes(prec, rc);
+            g->pool = ctx->links;
+            g->block = g->pool->take(total, g->block_bytes);
             for (int prec = 0; prec < 3; ++prec)
                 for (int rc = 0; rc < 2; ++rc) {
                     const int recon = rc ? 12 : 18;
                     if (!(formats & LQS_FMT(prec, recon))) continue;
-                    const size_t bytes = (size_t)link_block_bytes_per_site(prec, recon) * g->pitch * 8;
-                    LQS_HIP(hipMalloc(&g->fmt[prec][rc], bytes));
+                    g->fmt[prec][rc] = (char *)g->block + at;
+                    at += format_bytes(prec, rc);
                     packed.fmt[prec][rc] = (char *)g->fmt[prec][rc];
                     if (temporal) launch_unit_link(g->g, prec, recon, g->pitch, g->fmt[prec][rc], as_stream(stream));
                 }
@@ -262,8 +352,6 @@ lqs_status lqs_gauge_create(lqs_ctx *ctx, const int32_t dims[4], const double *l
 
 void lqs_gauge_destroy(lqs_gauge *g)
 {
-    if (!g) return;
-    (void)hipDeviceSynchronize();
     delete g;
 }
 
