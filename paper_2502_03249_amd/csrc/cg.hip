@@ -17,19 +17,21 @@
 // The x, r and p updates then share one kernel and one read of each vector.
 // The dot products are reduced in two fixed-order stages and alpha, beta stay
 // on the device; the host only polls the state record.
-// Every few iterations a gated FP64 group runs after kernel 4:
+// The FP64 group
 //   x += x_lo, x_lo = 0                                 (mixed precision)
 //   t64 = D_oe x, r_hi = b - (m^2 x - D_eo t64), |r_hi|^2, r = r_hi
 //   p = r + beta p                                      (kernel 4 left it out)
-// It does nothing unless the state asks for it: after the iterated residual
-// met the target (then it decides convergence on the FP64 residual), at the
-// iteration cap, or in mixed precision every K iterations or when |r| fell
-// below delta * max|r| (the reliable update of the mixed-precision solvers the
-// paper cites, Clark et al. 2010).
+// is gated on the state.  It decides convergence on the FP64 residual after the
+// iterated residual met the target, or the iteration cap; the host queues it
+// when it has seen such a state.  In mixed precision it also closes every round
+// of eight iterations, for the reliable update (of the mixed-precision solvers
+// the paper cites, Clark et al. 2010) that a right-hand side asks for every K
+// iterations or when |r| fell below delta * max|r|.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "cg_step.hpp"
 #include "hop.hpp"
@@ -136,7 +138,7 @@ normal_dot_kernel(Geom g, LinkRef L, const char *t, const char *p, char *q, int6
 
 __global__ void __launch_bounds__(1024) step_finalize_kernel(CgState *st, const double *partials,
                                                             const double *rr_partials, int max_blocks, int nblocks,
-                                                            int nr_blocks, int last)
+                                                            int nr_blocks, int last, int32_t *host_phase)
 {
     const int r = blockIdx.x;
     const double2 *pp = (const double2 *)(partials + (int64_t)r * max_blocks);
@@ -156,6 +158,7 @@ __global__ void __launch_bounds__(1024) step_finalize_kernel(CgState *st, const 
     if (S.phase == CG_RUNNING) cg_step_scalars(S, v[0], v[1], v[2], last);
     else S.live = 0;
     st[r] = S;
+    publish(host_phase, r, S.phase);
 }
 
 // ---------------------------------------------------------------------------
@@ -233,12 +236,13 @@ __global__ void __launch_bounds__(BLAS_BLOCK) step_kernel(int vh, char *x, char 
 // residual and beta the group has set.
 template <int PA, int PI>
 __global__ void __launch_bounds__(BLAS_BLOCK) pdir_kernel(int vh, const char *r, char *p, int64_t sa, int64_t si,
-                                                          const CgState *st)
+                                                          const CgState *st, int32_t *host_phase)
 {
     typedef typename RealOf<PA>::type T;
     typedef typename RealOf<PI>::type TI;
     const int rhs = blockIdx.y;
     const CgState &S = st[rhs];
+    if (blockIdx.x == 0 && threadIdx.x == 0) publish(host_phase, rhs, S.phase);
     if (!S.p_due || S.phase != CG_RUNNING) return;
     const T beta = (T)S.beta;
     r += rhs * sa;
@@ -250,14 +254,14 @@ __global__ void __launch_bounds__(BLAS_BLOCK) pdir_kernel(int vh, const char *r,
 }
 
 // ---------------------------------------------------------------------------
-// FP64 group: x += x_lo, x_lo = 0   (gate: 1 = reliable pending, 0 = always)
+// FP64 group: x += x_lo, x_lo = 0   (gate as in gate_state)
 
 template <int PA>
 __global__ void __launch_bounds__(BLAS_BLOCK) accumulate_kernel(int vh, double *x, char *xlo, int64_t sa,
-                                                                const CgState *st, int gated)
+                                                                const CgState *st, int gate_mode)
 {
     const int rhs = blockIdx.y;
-    if (gated && !st[rhs].reliable_pending) return;
+    if (!gate_state(st[rhs], gate_mode)) return;
     char *xd = (char *)x + rhs * spinor_bytes_per_site(F64) * (int64_t)vh;
     xlo += rhs * sa;
     for (int cb = blockIdx.x * blockDim.x + threadIdx.x; cb < vh; cb += gridDim.x * blockDim.x) {
@@ -498,13 +502,14 @@ void launch_normal_dot_shape(const Gauge &gauge, const CgVectors &v, LaunchShape
 // The scalars of a step from the nd_blocks partials of the normal kernel, and
 // the step.
 template <int PA, int PI>
-static void launch_step(const Gauge &gauge, const CgVectors &v, int nd_blocks, int last, hipStream_t s)
+static void launch_step(const Gauge &gauge, const CgVectors &v, int nd_blocks, int last, int32_t *host_phase,
+                        hipStream_t s)
 {
     const int vh = (int)gauge.vh;
     const int64_t sa = field_bytes(gauge.g, PA, 1), si = field_bytes(gauge.g, PI, 1);
     const dim3 grid(blas_blocks(vh), v.nrhs);
     hipLaunchKernelGGL(step_finalize_kernel, dim3(v.nrhs), dim3(1024), 0, s, v.state, (const double *)v.partials,
-                       (const double *)v.partials2, v.max_blocks, nd_blocks, (int)grid.x, last);
+                       (const double *)v.partials2, v.max_blocks, nd_blocks, (int)grid.x, last, host_phase);
     const bool early = v.nrhs == 1 && vh <= (int)grid.x * BLAS_BLOCK;
 #define LQS_STEP(EARLY)                                                                                           \
     hipLaunchKernelGGL((step_kernel<PA, PI, EARLY>), grid, dim3(BLAS_BLOCK), 0, s, vh, (char *)v.xlo,             \
@@ -518,12 +523,12 @@ static void launch_step(const Gauge &gauge, const CgVectors &v, int nd_blocks, i
 
 // The FP64 group's direction update.
 template <int PA, int PI>
-static void launch_pdir(const Gauge &gauge, const CgVectors &v, hipStream_t s)
+static void launch_pdir(const Gauge &gauge, const CgVectors &v, int32_t *host_phase, hipStream_t s)
 {
     const int vh = (int)gauge.vh;
     const int64_t sa = field_bytes(gauge.g, PA, 1), si = field_bytes(gauge.g, PI, 1);
     hipLaunchKernelGGL((pdir_kernel<PA, PI>), dim3(blas_blocks(vh), v.nrhs), dim3(BLAS_BLOCK), 0, s, vh,
-                       (const char *)v.r, (char *)v.p, sa, si, (const CgState *)v.state);
+                       (const char *)v.r, (char *)v.p, sa, si, (const CgState *)v.state, host_phase);
     LQS_HIP(hipGetLastError());
 }
 
@@ -570,14 +575,14 @@ static void launch_residual(const Gauge &gauge, const CgVectors &v, int R, int g
 #undef LQS_RES_PA
 }
 
-static void launch_accumulate(const Gauge &gauge, const CgVectors &v, int gated, hipStream_t s)
+static void launch_accumulate(const Gauge &gauge, const CgVectors &v, int gate_mode, hipStream_t s)
 {
     const int vh = (int)gauge.vh;
     dim3 grid(blas_blocks(vh), v.nrhs);
     const int64_t sa = field_bytes(gauge.g, v.acc_prec, 1);
     LQS_REQUIRE(v.acc_prec == F32, LQS_EUNSUPPORTED, "accumulate needs an FP32 inner solution");
     hipLaunchKernelGGL((accumulate_kernel<F32>), grid, dim3(BLAS_BLOCK), 0, s, vh, v.x, (char *)v.xlo, sa,
-                       (const CgState *)v.state, gated);
+                       (const CgState *)v.state, gate_mode);
     LQS_HIP(hipGetLastError());
 }
 
@@ -590,22 +595,33 @@ static void residual_pass(const Gauge &gauge, const CgVectors &v, int R, int gat
     launch_residual(gauge, v, R, gate_mode, mode, s);
 }
 
-// The FP64 residual group: x += x_lo (mixed), t64 = D_oe x, residual kernel.
-// In a mixed solve on 12-real links the periodic reliable updates use the
-// FP64 12-real links (two thirds of the bytes); the update that decides
-// convergence always uses the stored 18-real links, so the reported residual
-// is that of the operator the caller passed.
+// Stored reals of the FP64 links that a mixed solve's reliable updates use.
+static int periodic_links(const Gauge &gauge, const CgVectors &v)
+{
+    return v.recon == 12 && gauge.fmt[F64][1] ? 12 : 18;
+}
+
+// Both at once, for a recurrence that waits for no host: the reliable update,
+// and the final check where the iterated residual met the target.
+void cg_reliable_group(const Gauge &gauge, const CgVectors &v, hipStream_t s)
+{
+    launch_accumulate(gauge, v, 2, s);
+    if (periodic_links(gauge, v) == 12) {
+        residual_pass(gauge, v, 12, 3, 3, s);
+        residual_pass(gauge, v, 18, 4, 0, s);
+    } else {
+        residual_pass(gauge, v, 18, 2, 0, s);
+    }
+}
+
+// The FP64 residual group: x += x_lo (mixed), t64 = D_oe x, residual kernel,
+// with the stored 18-real links.
 void cg_residual_group(Ctx &ctx, const Gauge &gauge, const CgVectors &v, int gate_mode, int mode, hipStream_t s)
 {
     (void)ctx;
     const bool mixed = v.acc_prec != F64;
-    if (mixed && mode == 0) launch_accumulate(gauge, v, gate_mode == 2 ? 1 : 0, s);
-    if (mixed && mode == 0 && gate_mode == 2 && v.recon == 12 && gauge.fmt[F64][1]) {
-        residual_pass(gauge, v, 12, 3, 3, s);
-        residual_pass(gauge, v, 18, 4, 0, s);
-    } else {
-        residual_pass(gauge, v, 18, gate_mode, mode, s);
-    }
+    if (mixed && mode == 0) launch_accumulate(gauge, v, gate_mode, s);
+    residual_pass(gauge, v, 18, gate_mode, mode, s);
 }
 
 void cg_init(Ctx &ctx, const Gauge &gauge, CgVectors &v, bool use_x0, hipStream_t s)
@@ -641,8 +657,21 @@ static void cg_shapes(Ctx &ctx, const Gauge &gauge, CgVectors &v)
                       v.normal_shape);
 }
 
-static void cg_iteration(Ctx &ctx, const Gauge &gauge, CgVectors &v, hipStream_t s, bool with_reliable)
+template <typename F> static void with_precs(const CgVectors &v, F &&f)
 {
+    if (v.acc_prec == F64) f(std::integral_constant<int, F64>(), std::integral_constant<int, F64>());
+    else if (v.prec == F32) f(std::integral_constant<int, F32>(), std::integral_constant<int, F32>());
+    else f(std::integral_constant<int, F32>(), std::integral_constant<int, F16>());
+}
+
+// One iteration; `last` of its round: the phases go to the host, in mixed
+// precision after the group of the reliable updates.  In a solve on 12-real
+// links the updates use the FP64 12-real links (two thirds of the bytes), and
+// one that meets the target is handed to the final check; on 18-real links
+// the group decides convergence as well.
+static void cg_iteration(Ctx &ctx, const Gauge &gauge, CgVectors &v, hipStream_t s, bool last, int32_t *host_phase)
+{
+    const bool mixed = v.acc_prec != F64;
     // 1. t = D_oe p
     prof_begin(ctx, s);
     launch_hop_gated(gauge.g, gauge.ref(v.prec, v.recon), v.prec, v.recon, 0, 1, v.nrhs, v.p, v.t, v.state, 1,
@@ -652,16 +681,27 @@ static void cg_iteration(Ctx &ctx, const Gauge &gauge, CgVectors &v, hipStream_t
     launch_normal_dot_shape(gauge, v, v.normal_shape, s);
     // 3. and 4. the scalars; x, r and p
     const int nd_blocks = (int)((gauge.vh + v.normal_shape.block - 1) / v.normal_shape.block);
-    const int last = with_reliable ? 1 : 0;
-    if (v.acc_prec == F64) launch_step<F64, F64>(gauge, v, nd_blocks, last, s);
-    else if (v.prec == F32) launch_step<F32, F32>(gauge, v, nd_blocks, last, s);
-    else launch_step<F32, F16>(gauge, v, nd_blocks, last, s);
-    if (!with_reliable) return;
-    // FP64 residual group (gated), then the direction it owes
-    cg_residual_group(ctx, gauge, v, 2, 0, s);
-    if (v.acc_prec == F64) launch_pdir<F64, F64>(gauge, v, s);
-    else if (v.prec == F32) launch_pdir<F32, F32>(gauge, v, s);
-    else launch_pdir<F32, F16>(gauge, v, s);
+    with_precs(v, [&](auto pa, auto pi) {
+        launch_step<pa.value, pi.value>(gauge, v, nd_blocks, last && mixed, last && !mixed ? host_phase : nullptr, s);
+    });
+    if (!last || !mixed) return;
+    if (periodic_links(gauge, v) == 12) {
+        launch_accumulate(gauge, v, 3, s);
+        residual_pass(gauge, v, 12, 3, 3, s);
+    } else {
+        cg_residual_group(ctx, gauge, v, 2, 0, s);
+    }
+    with_precs(v, [&](auto pa, auto pi) { launch_pdir<pa.value, pi.value>(gauge, v, host_phase, s); });
+}
+
+// The FP64 check of the right-hand sides whose iterated residual met the target
+// or that reached the iteration cap, always with the stored 18-real links, so
+// the reported residual is that of the operator the caller passed; a side that
+// is above the target goes on.
+static void cg_final_check(Ctx &ctx, const Gauge &gauge, CgVectors &v, hipStream_t s, int32_t *host_phase)
+{
+    cg_residual_group(ctx, gauge, v, 4, 0, s);
+    with_precs(v, [&](auto pa, auto pi) { launch_pdir<pa.value, pi.value>(gauge, v, host_phase, s); });
 }
 
 // ---------------------------------------------------------------------------
@@ -725,19 +765,23 @@ struct CgRun {
     bool mixed = false;
     int nrhs = 1;
     size_t sbytes = 0;
-    CgState *hs[2] = {nullptr, nullptr};
+    CgState *hs = nullptr;         // host mirror of the records
+    int32_t *host_phase = nullptr; // phases as the rounds publish them (null with an arena)
     hipEvent_t ev[2] = {nullptr, nullptr};
     hipEvent_t tev[2] = {nullptr, nullptr};  // timing: first and last kernel of the solve
-    int inflight = 0, slot = 0;
-    int64_t enqueued = 0, cap = 0;
+    int64_t queued = 0, waited = 0;  // rounds and final checks queued, and known to have run
+    int64_t check_at = 0;            // `queued` after the last final check (0: none yet)
+    int64_t enqueued = 0, cap = 0;   // iterations
     bool done = false;
+    bool want_check = false;  // a right-hand side waits for its final check
+    bool idle = false;        // none is iterating
     bool use_graph = false;  // s is a side stream and graphs are on
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    // iterations between FP64 groups (gated launches that return at once unless a
-    // reliable update or the final check is pending) and chunks between state polls
+    // iterations of a round, between polls of the state and in mixed precision
+    // between FP64 groups (gated launches that return at once unless a reliable
+    // update is pending)
     static constexpr int chunk = 8;
-    static constexpr int poll_every = 1;
 
     CgRun(Ctx &c, const lqs_problem &p, const lqs_cg_params &pr, lqs_cg_stats *st, hipStream_t str, std::string tg,
           std::chrono::steady_clock::time_point start)
@@ -754,11 +798,9 @@ struct CgRun {
         if (graph) (void)hipGraphDestroy(graph);
     }
 
-    // one round: poll_every chunks of iterations, each closed by the gated FP64 group
     void round()
     {
-        for (int c = 0; c < poll_every; ++c)
-            for (int i = 0; i < chunk; ++i) cg_iteration(ctx, gauge(), v, s, i == chunk - 1);
+        for (int i = 0; i < chunk; ++i) cg_iteration(ctx, gauge(), v, s, i == chunk - 1, host_phase);
     }
     const Gauge &gauge() const { return *pb.gauge; }
 
@@ -767,7 +809,7 @@ struct CgRun {
     std::vector<double> masses;  // per right-hand side (empty: pb.mass for all)
     char *arena = nullptr;
     size_t arena_bytes = 0, arena_used = 0;
-    CgState *arena_host = nullptr;  // host mirror (two records per rhs) with an arena
+    CgState *arena_host = nullptr;  // host mirror with an arena
     void *buf(const std::string &slot, size_t bytes)
     {
         if (!arena) return ctx.workspace(slot + tag, bytes);
@@ -818,23 +860,22 @@ struct CgRun {
             v.rhi = (double *)v.r;
         }
         if (arena) {
-            hs[0] = arena_host;
-            hs[1] = arena_host + nrhs;
+            hs = arena_host;
         } else {
-            char *host = (char *)ctx.pinned("cg.host" + tag, 2 * sbytes);
-            hs[0] = (CgState *)host;
-            hs[1] = (CgState *)(host + sbytes);
+            hs = (CgState *)ctx.pinned("cg.host" + tag, sbytes + sizeof(int32_t) * nrhs);
+            host_phase = (int32_t *)(hs + nrhs);
+            for (int r = 0; r < nrhs; ++r) host_phase[r] = CG_RUNNING;
         }
         std::vector<double> mass(nrhs, pb.mass);
         if (!masses.empty()) mass = masses;
         LQS_REQUIRE((int)mass.size() == nrhs, LQS_EINVAL, "one mass per right-hand side");
-        cg_initial_states(prm, nrhs, mass.data(), hs[0]);
+        cg_initial_states(prm, nrhs, mass.data(), hs);
         if (!arena) {
             LQS_HIP(hipEventCreate(&tev[0]));
             LQS_HIP(hipEventCreate(&tev[1]));
             LQS_HIP(hipEventRecord(tev[0], s));
         }
-        LQS_HIP(hipMemcpyAsync(v.state, hs[0], sbytes, hipMemcpyHostToDevice, s));
+        LQS_HIP(hipMemcpyAsync(v.state, hs, sbytes, hipMemcpyHostToDevice, s));
         cg_init(ctx, gauge(), v, prm.use_x0 != 0, s);
         if (!arena) {
             LQS_HIP(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
@@ -843,83 +884,108 @@ struct CgRun {
         cap = (int64_t)prm.max_iter + 16 * chunk + 64;
     }
 
-    // queue one round of iterations and an asynchronous poll of the state.
-    // With graphs the first round runs eagerly, so that the GPU works while
-    // the host captures and instantiates (150-200 us of an idle GPU otherwise,
-    // at the start of every solve); the round is then captured once (the kernels read their scalars
-    // and gates from the device state, so every replay is the same work) and
-    // replayed; the round holds no memset or host synchronisation.
+    // queue the final check that a right-hand side waits for, or one round of
+    // iterations.  With graphs the first round runs eagerly, so that the GPU
+    // works while the host captures and instantiates (150-200 us of an idle GPU
+    // otherwise, at the start of every solve); the round is then captured once
+    // (the kernels read their scalars and gates from the device state, so every
+    // replay is the same work) and replayed; the round holds no memset, copy or
+    // host synchronisation.
     void enqueue()
     {
-        if (use_graph && enqueued > 0) {
-            if (!exec) {
-                LQS_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-                try {
-                    round();
-                } catch (...) {
-                    hipGraph_t g = nullptr;
-                    (void)hipStreamEndCapture(s, &g);
-                    if (g) (void)hipGraphDestroy(g);
-                    throw;
-                }
-                LQS_HIP(hipStreamEndCapture(s, &graph));
-                LQS_HIP(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
-            }
-            LQS_HIP(hipGraphLaunch(exec, s));
+        if (want_check) {
+            cg_final_check(ctx, gauge(), v, s, host_phase);
+            want_check = false;
+            check_at = queued + 1;
         } else {
-            round();
+            if (use_graph && enqueued > 0) {
+                if (!exec) {
+                    LQS_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+                    try {
+                        round();
+                    } catch (...) {
+                        hipGraph_t g = nullptr;
+                        (void)hipStreamEndCapture(s, &g);
+                        if (g) (void)hipGraphDestroy(g);
+                        throw;
+                    }
+                    LQS_HIP(hipStreamEndCapture(s, &graph));
+                    LQS_HIP(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
+                }
+                LQS_HIP(hipGraphLaunch(exec, s));
+            } else {
+                round();
+            }
+            enqueued += chunk;
         }
-        enqueued += chunk * poll_every;
-        LQS_HIP(hipMemcpyAsync(hs[slot], v.state, sbytes, hipMemcpyDeviceToHost, s));
         if (arena) {
-            // no events: wait for this poll at once
-            LQS_HIP(hipStreamSynchronize(s));
-            decide(hs[slot]);
+            // no events: wait for the records at once
+            fetch();
+            waited = ++queued;
+            decide();
             return;
         }
-        LQS_HIP(hipEventRecord(ev[slot], s));
-        ++inflight;
-        slot ^= 1;
+        LQS_HIP(hipEventRecord(ev[queued & 1], s));
+        ++queued;
     }
 
-    void decide(const CgState *h)
+    void fetch()
     {
-        bool all = true;
-        for (int r = 0; r < nrhs; ++r) all &= final_phase(h[r].phase);
+        LQS_HIP(hipMemcpyAsync(hs, v.state, sbytes, hipMemcpyDeviceToHost, s));
+        LQS_HIP(hipStreamSynchronize(s));
+    }
+
+    int32_t phase_of(int r) const
+    {
+        return host_phase ? __atomic_load_n(host_phase + r, __ATOMIC_RELAXED) : hs[r].phase;
+    }
+
+    // What to queue next, from phases at least as new as entry `waited`.
+    void decide()
+    {
+        bool all = true, waits = false, runs = false;
+        for (int r = 0; r < nrhs; ++r) {
+            const int32_t ph = phase_of(r);
+            all &= final_phase(ph);
+            waits |= ph == CG_INNER_DONE;
+            runs |= ph == CG_RUNNING;
+        }
+        // (a check that is still in flight may be about to settle what waits)
+        want_check = waits && waited >= check_at;
+        idle = waits && !runs;
         if (all || enqueued > cap) done = true;
     }
 
     // wait for the state the initial residuals left
     void check_initial()
     {
-        LQS_HIP(hipMemcpyAsync(hs[0], v.state, sbytes, hipMemcpyDeviceToHost, s));
-        LQS_HIP(hipStreamSynchronize(s));
-        decide(hs[0]);
+        fetch();
+        for (int r = 0; r < nrhs; ++r) host_phase[r] = hs[r].phase;
+        decide();
     }
 
-    // with two polls in flight, wait for the older one and decide
+    // Wait for all but the newest entry (so that the GPU has work meanwhile), or
+    // for that one too when no side is iterating, and decide.
     void check()
     {
-        if (inflight < 2) return;
-        LQS_HIP(hipEventSynchronize(ev[slot]));
-        --inflight;
-        decide(hs[slot]);
+        const int64_t upto = idle ? queued : queued - 1;
+        if (upto <= waited) return;
+        LQS_HIP(hipEventSynchronize(ev[(upto - 1) & 1]));
+        waited = upto;
+        decide();
     }
 
     void finish()
     {
-        LQS_HIP(hipStreamSynchronize(s));
         // right-hand sides that stopped without an FP64 check (breakdown,
         // non-finite, host cap) get x += x_lo and a measured residual
-        LQS_HIP(hipMemcpyAsync(hs[0], v.state, sbytes, hipMemcpyDeviceToHost, s));
-        LQS_HIP(hipStreamSynchronize(s));
+        fetch();
         bool need = false;
-        for (int r = 0; r < nrhs; ++r) need |= !(hs[0][r].phase == CG_CONVERGED || hs[0][r].phase == CG_MAXITER);
+        for (int r = 0; r < nrhs; ++r) need |= !(hs[r].phase == CG_CONVERGED || hs[r].phase == CG_MAXITER);
         if (need) {
             if (mixed) launch_accumulate(gauge(), v, 0, s);
             cg_residual_group(ctx, gauge(), v, 0, 2, s);
-            LQS_HIP(hipMemcpyAsync(hs[0], v.state, sbytes, hipMemcpyDeviceToHost, s));
-            LQS_HIP(hipStreamSynchronize(s));
+            fetch();
         }
         float dev_ms = 0.f;
         if (tev[0]) {
@@ -929,7 +995,7 @@ struct CgRun {
         }
         const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         for (int r = 0; r < nrhs; ++r) {
-            const CgState &S = hs[0][r];
+            const CgState &S = hs[r];
             lqs_cg_stats &o = stats[r];
             o.iters = S.iters;
             o.reliable_updates = S.nreliable;
@@ -1100,7 +1166,7 @@ void cg_solve_noalloc_impl(Ctx &ctx, const lqs_problem &pb, const lqs_cg_params 
         ~ProfOff() { c.profiling = was; }
     } prof{ctx, ctx.profiling};
     ctx.profiling = false;
-    CgState host[2 * 16];
+    CgState host[16];
     CgRun run(ctx, pb, prm, stats, s, "", std::chrono::steady_clock::now());
     run.arena = (char *)ctx.noalloc_scratch;
     run.arena_bytes = NOALLOC_SCRATCH_BYTES + NOALLOC_SLACK_BYTES;

@@ -93,4 +93,13 @@ __device__ inline void fin_residual(CgState &S, double r2, int mode)
     }
 }
 
+// The phase of a right-hand side for the host, in pinned memory (null: not now).
+// Phases only move towards a final one while the host waits, so a word that a
+// later kernel overwrites meanwhile misleads nobody.  (A copy of the records on
+// the stream instead held the next round back by 12 us.)
+__device__ __forceinline__ void publish(int32_t *host_phase, int rhs, int32_t phase)
+{
+    if (host_phase) __hip_atomic_store(host_phase + rhs, phase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 }  // namespace lqs

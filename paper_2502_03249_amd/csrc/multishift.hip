@@ -34,12 +34,13 @@
 #include <chrono>
 #include <cmath>
 
+#include "cg_step.hpp"
 #include "hop.hpp"
 
 namespace lqs {
 
 void launch_normal_dot_shape(const Gauge &gauge, const CgVectors &v, LaunchShape sh, hipStream_t s);
-void cg_residual_group(Ctx &ctx, const Gauge &gauge, const CgVectors &v, int gate_mode, int mode, hipStream_t s);
+void cg_reliable_group(const Gauge &gauge, const CgVectors &v, hipStream_t s);
 
 static constexpr int MS_MAX = 16;
 static constexpr int MS_BLOCK = 256;
@@ -64,7 +65,8 @@ struct ShiftPtrs {
 // |r|^2 as the last step summed it (rr_partials, at most 1024; unused while
 // rho holds a measured one).  `last`: the FP64 group follows this iteration.
 __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh, int nshift, const double *partials,
-                                                   const double *rr_partials, int nblocks, int nr_blocks, int last)
+                                                   const double *rr_partials, int nblocks, int nr_blocks, int last,
+                                                   int32_t *host_phase)
 {
     CgState &S = *base;
     const int phase = S.phase;
@@ -107,6 +109,11 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
     if (mine) sh[i] = T;
     const bool any = __any(mine && T.active);
     if (i != 0) return;
+    struct Publish {
+        CgState &S;
+        int32_t *host;
+        __device__ ~Publish() { publish(host, 0, S.phase); }
+    } published{S, host_phase};
     S.live = 0;
     S.p_due = 0;
     if (phase != CG_RUNNING) return;
@@ -184,10 +191,11 @@ __global__ void ms_rebeta(const CgState *base, ShiftState *sh, int nshift)
 template <int PI, int PR, bool DIRS>
 __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, char *p0, const char *q,
                                                     const ShiftPtrs *ptr, int nshift, const CgState *base,
-                                                    const ShiftState *sh, double *rr_partials)
+                                                    const ShiftState *sh, double *rr_partials, int32_t *host_phase)
 {
     typedef typename RealOf<PI>::type TI;
     typedef typename RealOf<PR>::type TR;
+    if (DIRS && blockIdx.x == 0 && threadIdx.x == 0) publish(host_phase, 0, base->phase);
     if (DIRS ? (!base->p_due || base->phase != CG_RUNNING) : !base->live) return;
     const double a = base->alpha, b = base->beta;
     const bool pdir = DIRS || !base->p_due;
@@ -395,7 +403,9 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
     // GPU does not idle between rounds; the kernels of a round queued after the
     // recurrence has ended return at once.
     const int nd_blocks = (vh + sh.block - 1) / sh.block;
-    CgState *hs2 = (CgState *)ctx.pinned("ms.host", 2 * sizeof(CgState));
+    CgState *hs1 = (CgState *)ctx.pinned("ms.host", sizeof(CgState) + sizeof(int32_t));
+    int32_t *host_phase = (int32_t *)(hs1 + 1);
+    *host_phase = CG_RUNNING;
     struct Events {
         hipEvent_t e[2] = {nullptr, nullptr};
         ~Events()
@@ -410,37 +420,38 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
     for (int round = 0;; ++round) {
         for (int i = 0; i < 8; ++i) {
             const int group = mixed && (i & 3) == 3;
+            int32_t *tell = i == 7 ? host_phase : nullptr;  // by the round's last kernel that settles the phase
             launch_hop_gated(g, L, PI, v.recon, 0, 1, 1, v.p, v.t, v.state, 1, sh, s);
             launch_normal_dot_shape(gauge, v, sh, s);
             hipLaunchKernelGGL(ms_scalars, dim3(1), dim3(1024), 0, s, v.state, dsh, nshift, (const double *)v.partials,
-                               (const double *)v.partials2, nd_blocks, blocks, group);
+                               (const double *)v.partials2, nd_blocks, blocks, group, mixed ? nullptr : tell);
             LQS_MS_PREC(hipLaunchKernelGGL((ms_step<P_I, P_R, false>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh, xr[base],
                                            (char *)v.r, (char *)v.p, (const char *)v.q, (const ShiftPtrs *)dp, nshift,
-                                           (const CgState *)v.state, (const ShiftState *)dsh, v.partials2));
+                                           (const CgState *)v.state, (const ShiftState *)dsh, v.partials2,
+                                           (int32_t *)nullptr));
             if (group) {
                 // reliable update (gated on the base's pending flag)
                 hipLaunchKernelGGL((ms_accumulate<F32>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh, (const ShiftPtrs *)dp,
                                    nshift, (const CgState *)v.state, 1);
-                cg_residual_group(ctx, gauge, v, 2, 0, s);
+                cg_reliable_group(gauge, v, s);
                 hipLaunchKernelGGL(ms_rebeta, dim3(1), dim3(64), 0, s, (const CgState *)v.state, dsh, nshift);
                 LQS_MS_PREC(hipLaunchKernelGGL((ms_step<P_I, P_R, true>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh,
                                                xr[base], (char *)v.r, (char *)v.p, (const char *)v.q,
                                                (const ShiftPtrs *)dp, nshift, (const CgState *)v.state,
-                                               (const ShiftState *)dsh, v.partials2));
+                                               (const ShiftState *)dsh, v.partials2, tell));
             }
             LQS_HIP(hipGetLastError());
         }
         enqueued += 8;
-        LQS_HIP(hipMemcpyAsync(hs2 + (round & 1), v.state, sizeof(CgState), hipMemcpyDeviceToHost, s));
         LQS_HIP(hipEventRecord(ev.e[round & 1], s));
         if (round == 0) continue;
         LQS_HIP(hipEventSynchronize(ev.e[(round - 1) & 1]));
-        if (hs2[(round - 1) & 1].phase != CG_RUNNING || enqueued > cap) break;
+        if (__atomic_load_n(host_phase, __ATOMIC_RELAXED) != CG_RUNNING || enqueued > cap) break;
     }
     if (nshift) LQS_HIP(hipMemcpyAsync(hsh.data(), dsh, sizeof(ShiftState) * nshift, hipMemcpyDeviceToHost, s));
-    LQS_HIP(hipMemcpyAsync(hs2, v.state, sizeof(CgState), hipMemcpyDeviceToHost, s));
+    LQS_HIP(hipMemcpyAsync(hs1, v.state, sizeof(CgState), hipMemcpyDeviceToHost, s));
     LQS_HIP(hipStreamSynchronize(s));
-    const CgState hs = hs2[0];
+    const CgState hs = *hs1;
 
 #undef LQS_MS_PREC
     if (mixed) {
