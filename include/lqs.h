@@ -117,11 +117,11 @@ void lqs_ctx_destroy(lqs_ctx *ctx);
  * context) are used, the built-in defaults otherwise. */
 lqs_status lqs_set_tuning(lqs_ctx *ctx, int32_t enable);
 
-/* HIP graphs for the multi-kernel CG: 1 (default) = each solve captures one
- * round of iterations (8 iterations and their gated FP64 groups) into a
- * graph on a side stream and replays it, which removes most of the launch
- * cost on small lattices; 0 = launch every kernel.  Results are identical.
- * Graphs are not used while hop profiling is on. */
+/* HIP graphs for the multi-kernel CG: 1 (default) = solves of several problems
+ * at once, and of one small problem, capture a round of 8 iterations (in mixed
+ * precision with its gated FP64 group) into a graph on a side stream and
+ * replay it, which removes most of the launch cost; 0 = launch every kernel.
+ * Results are identical.  Graphs are not used while hop profiling is on. */
 lqs_status lqs_set_graphs(lqs_ctx *ctx, int32_t enable);
 
 /* Pack a canonical link field into the formats of the `formats` bitmask

@@ -1016,12 +1016,21 @@ struct CgRun {
 
 }  // namespace
 
+// One problem replays graphs only below this many sites per parity, all sides
+// together: between two graph launches the GPU idles for 13 us, and from here
+// on a kernel runs longer than the host takes to launch the next.  16^4 FP16
+// storage 5.21 ms with graphs, 5.09 launched kernel by kernel; 24^4 trajectory
+// with fermions 28.5 and 27.3; 32^3 x 8 FP64 8.65 and 8.52; 8^4 FP64 3.45 and
+// 3.51.  (Several problems at once share the host, and graphs win there:
+// 16^4, 24^3 x 8 and 32^3 x 8 in FP32 8.6 against 9.1 ms.)
+static constexpr int64_t GRAPH_SITES = 1 << 15;
+
 void cg_solve_one(Ctx &ctx, const lqs_problem &pb, const lqs_cg_params &prm, lqs_cg_stats *stats, hipStream_t s,
                   const std::vector<double> *masses)
 {
     // graphs are captured on a side stream (the caller's stream may be the
     // null stream, which cannot be captured), forked from and joined into s
-    const bool graphs = ctx.graphs && !ctx.profiling;
+    const bool graphs = ctx.graphs && !ctx.profiling && pb.gauge->vh * pb.nrhs < GRAPH_SITES;
     hipStream_t rs = graphs ? ctx.side_stream(0) : s;
     hipEvent_t fork = nullptr, join = nullptr;
     if (graphs) {
