@@ -333,9 +333,108 @@ __device__ __forceinline__ void pin(Mat &m)
     for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(m.e[k / 3][k % 3].re), "+v"(m.e[k / 3][k % 3].im));
 }
 
-template <bool WM, bool FERM>
+__device__ __forceinline__ Cd cfma(Cd a, Cd b, Cd c)
+{
+    return {fused(-a.im, b.im, fused(a.re, b.re, c.re)), fused(a.im, b.re, fused(a.re, b.im, c.im))};
+}
+
+// exp(A) for a 3x3 complex A: A is scaled by 2^-s so that its max-row-sum
+// norm is at most 1/4, the Taylor polynomial of degree 16 is evaluated in
+// Horner form (truncation below 1e-24), and the result squared s times.
+// Every polynomial in A is held as c0 + c1 A + c2 A^2 (Cayley-Hamilton:
+// A^3 = t A^2 - w A + d, with t = tr A, w = (t^2 - tr A^2) / 2, d = det A), so
+// a Horner step takes three complex products instead of the 27 of a matrix
+// product, and the matrix products left are A^2 and the caller's.
+__device__ __forceinline__ Mat mat_exp(const Mat &a0)
+{
+    double nrm = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        double r = 0.0;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) r += sqrt(a0.e[i][j].re * a0.e[i][j].re + a0.e[i][j].im * a0.e[i][j].im);
+        nrm = r > nrm ? r : nrm;
+    }
+    int s = 0;
+    while (nrm > 0.25 && s < 60) {
+        nrm *= 0.5;
+        ++s;
+    }
+    const double sc = ldexp(1.0, -s);
+    Mat a;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) a.e[i][j] = {a0.e[i][j].re * sc, a0.e[i][j].im * sc};
+    const Mat a2 = mat_mul<false, false>(a, a);
+    const Cd t = {a.e[0][0].re + a.e[1][1].re + a.e[2][2].re, a.e[0][0].im + a.e[1][1].im + a.e[2][2].im};
+    const Cd t2 = {a2.e[0][0].re + a2.e[1][1].re + a2.e[2][2].re, a2.e[0][0].im + a2.e[1][1].im + a2.e[2][2].im};
+    const Cd tt = cmul(t, t);
+    const Cd nw = {0.5 * (t2.re - tt.re), 0.5 * (t2.im - tt.im)};  // -w
+    Cd d = {0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int j = (i + 1) % 3, k = (i + 2) % 3;
+        d = cfma(a.e[0][i], csub(cmul(a.e[1][j], a.e[2][k]), cmul(a.e[1][k], a.e[2][j])), d);
+    }
+    // Horner: E = I + a/1 (I + a/2 (I + ... (I + a/16)))
+    Cd c0 = {1.0, 0.0}, c1 = {0.0, 0.0}, c2 = {0.0, 0.0};
+#pragma unroll 4
+    for (int k = 16; k >= 1; --k) {
+        const double inv = 1.0 / k;
+        const Cd n0 = cmul(d, c2), n1 = cfma(nw, c2, c0), n2 = cfma(t, c2, c1);
+        c0 = {fused(n0.re, inv, 1.0), n0.im * inv};
+        c1 = {n1.re * inv, n1.im * inv};
+        c2 = {n2.re * inv, n2.im * inv};
+    }
+    for (int k = 0; k < s; ++k) {
+        // (c0 + c1 A + c2 A^2)^2 = c0^2 + 2 c0 c1 A + (c1^2 + 2 c0 c2) A^2 + 2 c1 c2 A^3 + c2^2 A^4,
+        // reduced by A^4 = t A^3 - w A^2 + d A and then A^3
+        const Cd q4 = cmul(c2, c2), h = cmul(c1, c2);
+        const Cd q3 = cfma(t, q4, Cd{2.0 * h.re, 2.0 * h.im});
+        const Cd c02 = cmul(c0, c2), c01 = cmul(c0, c1);
+        const Cd q2 = cfma(nw, q4, cfma(c1, c1, Cd{2.0 * c02.re, 2.0 * c02.im}));
+        const Cd q1 = cfma(d, q4, Cd{2.0 * c01.re, 2.0 * c01.im});
+        c0 = cfma(d, q3, cmul(c0, c0));
+        c1 = cfma(nw, q3, q1);
+        c2 = cfma(t, q3, q2);
+    }
+    Mat e;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const Cd diag = i == j ? c0 : Cd{0.0, 0.0};
+            e.e[i][j] = cfma(c2, a2.e[i][j], cfma(c1, a.e[i][j], diag));
+        }
+    return e;
+}
+
+template <int P, int R> __device__ __forceinline__ void lu_store(const Mat &u, char *out, int blk, int64_t pitch, int cb)
+{
+    typedef typename RealOf<P>::type T;
+    if (!out) return;
+    M3<T> v;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) v.e[k / 3][k % 3] = {(T)u.e[k / 3][k % 3].re, (T)u.e[k / 3][k % 3].im};
+    LinkIO<P, R>::store(out + blk * (int64_t)link_block_bytes_per_site(P, R) * pitch, pitch, cb, v);
+}
+
+// the link of site cb and block blk in every format a trajectory holds
+__device__ __forceinline__ void lu_store_all(const Mat &w, const LinkOut &out, int blk, int64_t vh, int cb)
+{
+    lu_store<F64, 18>(w, out.fmt[F64][0], blk, vh, cb);
+    lu_store<F64, 12>(w, out.fmt[F64][1], blk, vh, cb);
+    lu_store<F32, 18>(w, out.fmt[F32][0], blk, vh, cb);
+    lu_store<F32, 12>(w, out.fmt[F32][1], blk, vh, cb);
+    lu_store<F16, 18>(w, out.fmt[F16][0], blk, vh, cb);
+    lu_store<F16, 12>(w, out.fmt[F16][1], blk, vh, cb);
+}
+
+template <bool WM, bool FERM, bool UPD>
 __global__ void __launch_bounds__(256) link_force_kernel(Geom g, SweepMap sm, const double2 *U, const char *chi,
-                                                         const char *psi, double gb, double c, int mode, double2 *Q)
+                                                         const char *psi, double gb, double c, int mode, double2 *Q,
+                                                         double eps, LinkOut out)
 {
     const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
     const int par = q & 1, o = xcd * sm.per + (q >> 1);
@@ -433,85 +532,20 @@ __global__ void __launch_bounds__(256) link_force_kernel(Geom g, SweepMap sm, co
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
         const double2 f = rec[64 * k + lane];
-        if (at[k]) *at[k] = make_double2(fused(c, f.x, prev[k].x), fused(c, f.y, prev[k].y));
+        const double2 n = make_double2(fused(c, f.x, prev[k].x), fused(c, f.y, prev[k].y));
+        if (at[k]) *at[k] = n;
+        if (UPD) rec[64 * k + lane] = n;
     }
-}
-
-__device__ __forceinline__ Cd cfma(Cd a, Cd b, Cd c)
-{
-    return {fused(-a.im, b.im, fused(a.re, b.re, c.re)), fused(a.im, b.re, fused(a.re, b.im, c.im))};
-}
-
-// exp(A) for a 3x3 complex A: A is scaled by 2^-s so that its max-row-sum
-// norm is at most 1/4, the Taylor polynomial of degree 16 is evaluated in
-// Horner form (truncation below 1e-24), and the result squared s times.
-// Every polynomial in A is held as c0 + c1 A + c2 A^2 (Cayley-Hamilton:
-// A^3 = t A^2 - w A + d, with t = tr A, w = (t^2 - tr A^2) / 2, d = det A), so
-// a Horner step takes three complex products instead of the 27 of a matrix
-// product, and the matrix products left are A^2 and the caller's.
-__device__ __forceinline__ Mat mat_exp(const Mat &a0)
-{
-    double nrm = 0.0;
+    if constexpr (UPD) {
+        __syncthreads();
+        Mat qn = mat_load(rec + 9 * lane);
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        double r = 0.0;
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int j = 0; j < 3; ++j) r += sqrt(a0.e[i][j].re * a0.e[i][j].re + a0.e[i][j].im * a0.e[i][j].im);
-        nrm = r > nrm ? r : nrm;
+            for (int j = 0; j < 3; ++j) qn.e[i][j] = {eps * qn.e[i][j].re, eps * qn.e[i][j].im};
+        const Mat w = mat_mul<false, false>(mat_exp(qn), a);
+        if (lane < count) lu_store_all(w, out, 2 * mu + par, vh, cb);
     }
-    int s = 0;
-    while (nrm > 0.25 && s < 60) {
-        nrm *= 0.5;
-        ++s;
-    }
-    const double sc = ldexp(1.0, -s);
-    Mat a;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) a.e[i][j] = {a0.e[i][j].re * sc, a0.e[i][j].im * sc};
-    const Mat a2 = mat_mul<false, false>(a, a);
-    const Cd t = {a.e[0][0].re + a.e[1][1].re + a.e[2][2].re, a.e[0][0].im + a.e[1][1].im + a.e[2][2].im};
-    const Cd t2 = {a2.e[0][0].re + a2.e[1][1].re + a2.e[2][2].re, a2.e[0][0].im + a2.e[1][1].im + a2.e[2][2].im};
-    const Cd tt = cmul(t, t);
-    const Cd nw = {0.5 * (t2.re - tt.re), 0.5 * (t2.im - tt.im)};  // -w
-    Cd d = {0.0, 0.0};
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const int j = (i + 1) % 3, k = (i + 2) % 3;
-        d = cfma(a.e[0][i], csub(cmul(a.e[1][j], a.e[2][k]), cmul(a.e[1][k], a.e[2][j])), d);
-    }
-    // Horner: E = I + a/1 (I + a/2 (I + ... (I + a/16)))
-    Cd c0 = {1.0, 0.0}, c1 = {0.0, 0.0}, c2 = {0.0, 0.0};
-#pragma unroll 4
-    for (int k = 16; k >= 1; --k) {
-        const double inv = 1.0 / k;
-        const Cd n0 = cmul(d, c2), n1 = cfma(nw, c2, c0), n2 = cfma(t, c2, c1);
-        c0 = {fused(n0.re, inv, 1.0), n0.im * inv};
-        c1 = {n1.re * inv, n1.im * inv};
-        c2 = {n2.re * inv, n2.im * inv};
-    }
-    for (int k = 0; k < s; ++k) {
-        // (c0 + c1 A + c2 A^2)^2 = c0^2 + 2 c0 c1 A + (c1^2 + 2 c0 c2) A^2 + 2 c1 c2 A^3 + c2^2 A^4,
-        // reduced by A^4 = t A^3 - w A^2 + d A and then A^3
-        const Cd q4 = cmul(c2, c2), h = cmul(c1, c2);
-        const Cd q3 = cfma(t, q4, Cd{2.0 * h.re, 2.0 * h.im});
-        const Cd c02 = cmul(c0, c2), c01 = cmul(c0, c1);
-        const Cd q2 = cfma(nw, q4, cfma(c1, c1, Cd{2.0 * c02.re, 2.0 * c02.im}));
-        const Cd q1 = cfma(d, q4, Cd{2.0 * c01.re, 2.0 * c01.im});
-        c0 = cfma(d, q3, cmul(c0, c0));
-        c1 = cfma(nw, q3, q1);
-        c2 = cfma(t, q3, q2);
-    }
-    Mat e;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const Cd diag = i == j ? c0 : Cd{0.0, 0.0};
-            e.e[i][j] = cfma(c2, a2.e[i][j], cfma(c1, a.e[i][j], diag));
-        }
-    return e;
 }
 
 // U = exp(eps Q) U on every link.  A block takes 128 consecutive sites of one
@@ -530,16 +564,6 @@ __device__ __forceinline__ void lu_stage(double2 *sh, const double2 *src, int n)
         if (i < n) sh[i] = src[i];
     }
     __syncthreads();
-}
-
-template <int P, int R> __device__ __forceinline__ void lu_store(const Mat &u, char *out, int blk, int64_t pitch, int cb)
-{
-    typedef typename RealOf<P>::type T;
-    if (!out) return;
-    M3<T> v;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) v.e[k / 3][k % 3] = {(T)u.e[k / 3][k % 3].re, (T)u.e[k / 3][k % 3].im};
-    LinkIO<P, R>::store(out + blk * (int64_t)link_block_bytes_per_site(P, R) * pitch, pitch, cb, v);
 }
 
 template <bool WM>
@@ -570,12 +594,7 @@ __global__ void __launch_bounds__(LU_SITES) link_update_kernel(Geom g, double2 *
     if constexpr (WM) {
         if (!valid) return;
         const int blk = 2 * mu + parity;
-        lu_store<F64, 18>(w, (char *)U, blk, g.vh, cb);
-        lu_store<F64, 12>(w, out.fmt[F64][1], blk, g.vh, cb);
-        lu_store<F32, 18>(w, out.fmt[F32][0], blk, g.vh, cb);
-        lu_store<F32, 12>(w, out.fmt[F32][1], blk, g.vh, cb);
-        lu_store<F16, 18>(w, out.fmt[F16][0], blk, g.vh, cb);
-        lu_store<F16, 12>(w, out.fmt[F16][1], blk, g.vh, cb);
+        lu_store_all(w, out, blk, g.vh, cb);
     } else {
         if (valid) mat_store(own, w);  // own record only: read by this thread alone
         __syncthreads();
@@ -649,13 +668,13 @@ void launch_gauge_action(Ctx &ctx, const Geom &g, const double *U, double beta, 
     launch_action<false>(ctx, g, U, beta, out, slot, s);
 }
 
-template <bool WM, bool FERM>
+template <bool WM, bool FERM, bool UPD = false>
 static void launch_link_force(const Geom &g, const double *U, const double *chi, const double *psi, double gb, double c,
-                              int mode, double *Q, hipStream_t s)
+                              int mode, double *Q, hipStream_t s, double eps = 0.0, const LinkOut &out = LinkOut())
 {
     const SweepMap sm = sweep_map(g, SWEEP_RUN);
-    hipLaunchKernelGGL((link_force_kernel<WM, FERM>), dim3(8u * sm.per * 2), dim3(256), 0, s, g, sm, (const double2 *)U,
-                       (const char *)chi, (const char *)psi, gb, c, mode, (double2 *)Q);
+    hipLaunchKernelGGL((link_force_kernel<WM, FERM, UPD>), dim3(8u * sm.per * 2), dim3(256), 0, s, g, sm,
+                       (const double2 *)U, (const char *)chi, (const char *)psi, gb, c, mode, (double2 *)Q, eps, out);
     LQS_HIP(hipGetLastError());
 }
 
@@ -728,8 +747,17 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
     // read; the inner format is written along with each link update
     WsGauge wg(ctx, g, prm.cg.inner_prec, prm.cg.inner_recon);
     Gauge &gauge = wg.g;
-    const LinkRef L64 = gauge.ref(F64, 18);
+    LinkRef L64 = gauge.ref(F64, 18);
     double *U1 = (double *)gauge.fmt[F64][0];
+    // where a momentum step that goes on to the link step writes the new links;
+    // without room for it the two steps are separate kernels
+    double *U2 = nullptr;
+    try {
+        U2 = (double *)ctx.workspace("hmc.links.next", (size_t)link_block_bytes_per_site(F64, 18) * gauge.pitch * 8);
+    } catch (const Error &e) {
+        if (e.status != LQS_ENOMEM) throw;
+        (void)hipGetLastError();
+    }
     LinkOut fmts;
     for (int prec = 0; prec < 3; ++prec)
         for (int rc = 0; rc < 2; ++rc) fmts.fmt[prec][rc] = (char *)gauge.fmt[prec][rc];
@@ -791,22 +819,34 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
     };
     // mom -= eps F / 2 with F_g = (beta/3) TA(U V) and F_f = -TA(U Pi), the
     // fermion part from chi on the current links; the solve on the final links
-    // (last) also gives S_f at the end
-    auto momentum = [&](double eps, bool have_chi, bool last) {
-        if (!ferm) {
-            launch_link_force<true, false>(g, U1, nullptr, nullptr, prm.beta / 3.0, -0.5 * eps, 1, mom, s);
+    // (last) also gives S_f at the end.  drift > 0: then the links move,
+    // U = exp(drift mom) U.
+    auto momentum = [&](double eps, bool have_chi, bool last, double drift) {
+        if (ferm) {
+            if (!have_chi) solve(last);
+            launch_hop_gated(g, L64, F64, 18, 0, 1, 1, chi, psx, nullptr, 0, sh, s);
+        }
+        const double gb = prm.beta / 3.0, c = -0.5 * eps;
+        if (drift > 0 && U2) {
+            LinkOut next = fmts;
+            next.fmt[F64][0] = (char *)U2;
+            if (ferm) launch_link_force<true, true, true>(g, U1, chi, psx, gb, c, 1, mom, s, drift, next);
+            else launch_link_force<true, false, true>(g, U1, nullptr, nullptr, gb, c, 1, mom, s, drift, next);
+            std::swap(U1, U2);
+            fmts = next;
+            gauge.fmt[F64][0] = U1;
+            L64 = gauge.ref(F64, 18);
             return;
         }
-        if (!have_chi) solve(last);
-        launch_hop_gated(g, L64, F64, 18, 0, 1, 1, chi, psx, nullptr, 0, sh, s);
-        launch_link_force<true, true>(g, U1, chi, psx, prm.beta / 3.0, -0.5 * eps, 1, mom, s);
-    };
-    auto links_step = [&](double eps) {
-        dim3 grid;
-        link_update_grid(g, grid);
-        hipLaunchKernelGGL(link_update_kernel<true>, grid, dim3(LU_SITES), 0, s, g, (double2 *)U1, (const double2 *)mom,
-                           eps, fmts);
-        LQS_HIP(hipGetLastError());
+        if (ferm) launch_link_force<true, true>(g, U1, chi, psx, gb, c, 1, mom, s);
+        else launch_link_force<true, false>(g, U1, nullptr, nullptr, gb, c, 1, mom, s);
+        if (drift > 0) {
+            dim3 grid;
+            link_update_grid(g, grid);
+            hipLaunchKernelGGL(link_update_kernel<true>, grid, dim3(LU_SITES), 0, s, g, (double2 *)U1,
+                               (const double2 *)mom, drift, fmts);
+            LQS_HIP(hipGetLastError());
+        }
     };
 
     // H at the start: scal[0..1] = K0, Sg0 / beta, scal[8] = Sf0
@@ -821,23 +861,20 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
     const double lam = prm.lambda > 0 ? prm.lambda : 0.1931833275037836;
     bool have_chi = ferm;  // chi belongs to the current links
     if (prm.integrator == LQS_LEAPFROG) {
-        momentum(0.5 * h, have_chi, false);
+        momentum(0.5 * h, have_chi, false, h);
         for (int k = 0; k < prm.nsteps; ++k) {
-            links_step(h);
             const bool last = k == prm.nsteps - 1;
-            momentum(last ? 0.5 * h : h, false, last);
+            momentum(last ? 0.5 * h : h, false, last, last ? 0.0 : h);
         }
     } else {
         // consecutive lam*h updates at a step boundary act on the same links: merged
         double pending = lam * h;
         for (int k = 0; k < prm.nsteps; ++k) {
-            momentum(pending, k == 0 && have_chi, false);
-            links_step(0.5 * h);
-            momentum((1.0 - 2.0 * lam) * h, false, false);
-            links_step(0.5 * h);
+            momentum(pending, k == 0 && have_chi, false, 0.5 * h);
+            momentum((1.0 - 2.0 * lam) * h, false, false, 0.5 * h);
             pending = 2.0 * lam * h;
         }
-        momentum(lam * h, false, true);
+        momentum(lam * h, false, true, 0.0);
     }
     // H at the end: chi is the solve on the final links (last momentum step)
     launch_kinetic(ctx, g, mom, scal, 3, s);
