@@ -283,12 +283,15 @@ template <int R, int PA, int K, int LF>
 __global__ void __launch_bounds__(512) residual_kernel(Geom g, LinkRef L, const char *t64, const char *x,
                                                        const char *b, char *r, int64_t sa, CgState *st,
                                                        double *partials, int max_blocks, int nrhs, int gate_mode,
-                                                       int mode)
+                                                       int mode, int ngroups, TileMap tmap)
 {
     const int64_t s64 = spinor_bytes_per_site(F64) * (int64_t)g.vh;
-    const int cb = blockIdx.x * blockDim.x + threadIdx.x;
+    int grp;
+    const int tile = tile_group(ngroups, tmap, g.n[3], grp);
+    if (tile < 0 || tile * (int)blockDim.x >= g.vh) return;  // padding tile (whole block)
+    const int cb = tile * blockDim.x + threadIdx.x;
     const bool valid = cb < g.vh;
-    const int r0 = blockIdx.y * K;
+    const int r0 = grp * K;
     bool blk[K], act[K];
     bool any = false;
 #pragma unroll
@@ -325,7 +328,7 @@ __global__ void __launch_bounds__(512) residual_kernel(Geom g, LinkRef L, const 
         if (!blk[j]) continue;
         const int rr = r0 + j;
         const double s = block_sum(nrm[j]);
-        if (threadIdx.x == 0) partials[(int64_t)rr * max_blocks + blockIdx.x] = s;
+        if (threadIdx.x == 0) partials[(int64_t)rr * max_blocks + tile] = s;
     }
 }
 
@@ -532,47 +535,59 @@ static void launch_pdir(const Gauge &gauge, const CgVectors &v, int32_t *host_ph
     LQS_HIP(hipGetLastError());
 }
 
-template <int PA, int R, int K>
+// The hop's default launch for this many right-hand sides, in blocks of 256 (the
+// partials are indexed by tile: the sums do not depend on the map or on K).  16
+// sides on 32^3 x 8 with 12-real links: 137 us, and 251 with two sides per
+// thread in lexicographic order; 8 sides with 18-real links 80 and 175.
+template <int PA, int R>
 static void launch_residual_k(const Gauge &gauge, const CgVectors &v, int gate_mode, int mode, hipStream_t s)
 {
     const Geom &g = gauge.g;
-    const int block = 256;
-    const dim3 grid((g.vh + block - 1) / block, (v.nrhs + K - 1) / K);
     const LinkRef L = gauge.ref(F64, R);
-    const int lf = (L.temporal ? LF_TEMPORAL : 0) | (default_hop_shape(L, v.nrhs).stream_links ? LF_STREAM : 0);
+    const LaunchShape sh = default_hop_shape(L, v.nrhs);
+    const int block = 256, tiles = (g.vh + block - 1) / block;
+    const int G = (v.nrhs + sh.rhs_per_thread - 1) / sh.rhs_per_thread;
+    const TileMap tmap = tile_map(g, block, sh.xcd_slab, time_run(g, block, v.nrhs, F64, sh.trun));
+    const dim3 grid(tile_map_blocks(g, block, tmap, G));
+    const int lf =
+        (L.temporal ? LF_TEMPORAL : 0) | (sh.stream_links ? LF_STREAM : 0) | (sh.prefetch ? LF_PREFETCH : 0);
     const int64_t sa = field_bytes(g, PA, 1);
     char *r = (char *)(mode == 2 ? nullptr : v.r);
-#define LQS_RES(LF)                                                                                               \
+#define LQS_RES(K, LF)                                                                                            \
     hipLaunchKernelGGL((residual_kernel<R, PA, K, LF>), grid, dim3(block), 0, s, g, L, (const char *)v.t64,       \
-                       (const char *)v.x, (const char *)v.b, r, sa, v.state, v.partials, v.max_blocks, v.nrhs,  \
-                       gate_mode, mode)
+                       (const char *)v.x, (const char *)v.b, r, sa, v.state, v.partials, v.max_blocks, v.nrhs,    \
+                       gate_mode, mode, G, tmap)
+#define LQS_RES_K(LF)                                                                                             \
+    if (sh.rhs_per_thread == 1) LQS_RES(1, LF);                                                                   \
+    else if (sh.rhs_per_thread == 2) LQS_RES(2, LF);                                                              \
+    else LQS_RES(4, LF)
     switch (lf) {
-    case 0: LQS_RES(0); break;
-    case LF_TEMPORAL: LQS_RES(LF_TEMPORAL); break;
-    case LF_STREAM: LQS_RES(LF_STREAM); break;
-    default: LQS_RES(LF_TEMPORAL | LF_STREAM); break;
+    // without prefetch: one side on a large lattice
+    case 0: LQS_RES(1, 0); break;
+    case LF_TEMPORAL: LQS_RES(1, LF_TEMPORAL); break;
+    case LF_STREAM: LQS_RES(1, LF_STREAM); break;
+    case LF_TEMPORAL | LF_STREAM: LQS_RES(1, LF_TEMPORAL | LF_STREAM); break;
+    case LF_PREFETCH: LQS_RES_K(LF_PREFETCH); break;
+    case LF_PREFETCH | LF_TEMPORAL: LQS_RES_K(LF_PREFETCH | LF_TEMPORAL); break;
+    case LF_PREFETCH | LF_STREAM: LQS_RES_K(LF_PREFETCH | LF_STREAM); break;
+    default: LQS_RES_K(LF_PREFETCH | LF_TEMPORAL | LF_STREAM); break;
     }
+#undef LQS_RES_K
 #undef LQS_RES
     LQS_HIP(hipGetLastError());
-    launch_finalize(v, v.partials, grid.x, FIN_RESID, gate_mode, mode, s);
+    launch_finalize(v, v.partials, tiles, FIN_RESID, gate_mode, mode, s);
 }
 
-// FP64 residual with the R-real FP64 links (two right-hand sides per thread
-// from two on)
+// FP64 residual with the R-real FP64 links
 static void launch_residual(const Gauge &gauge, const CgVectors &v, int R, int gate_mode, int mode, hipStream_t s)
 {
-    const bool two = v.nrhs >= 2;
-#define LQS_RES_PA(PA)                                                                                            \
-    if (R == 12 && two) launch_residual_k<PA, 12, 2>(gauge, v, gate_mode, mode, s);                               \
-    else if (R == 12) launch_residual_k<PA, 12, 1>(gauge, v, gate_mode, mode, s);                                 \
-    else if (two) launch_residual_k<PA, 18, 2>(gauge, v, gate_mode, mode, s);                                     \
-    else launch_residual_k<PA, 18, 1>(gauge, v, gate_mode, mode, s)
     if (v.acc_prec == F64) {
-        LQS_RES_PA(F64);
+        if (R == 12) launch_residual_k<F64, 12>(gauge, v, gate_mode, mode, s);
+        else launch_residual_k<F64, 18>(gauge, v, gate_mode, mode, s);
     } else {
-        LQS_RES_PA(F32);
+        if (R == 12) launch_residual_k<F32, 12>(gauge, v, gate_mode, mode, s);
+        else launch_residual_k<F32, 18>(gauge, v, gate_mode, mode, s);
     }
-#undef LQS_RES_PA
 }
 
 static void launch_accumulate(const Gauge &gauge, const CgVectors &v, int gate_mode, hipStream_t s)
