@@ -193,7 +193,9 @@ void launch_hop(Ctx &ctx, const Gauge &gauge, int prec, int recon, int dagger, i
 {
     const LinkRef L = gauge.ref(prec, recon);
     LaunchShape sh = default_hop_shape(L, nrhs);
-    if (ctx.tuner) ctx.tuner->lookup(tune_key(ctx, gauge.temporal ? "hop_tg" : "hop", gauge.g, prec, recon, nrhs), sh);
+    // (the key is a string: 1.5 us to form, not for an empty cache)
+    if (ctx.tuner && !ctx.tuner->cache.empty())
+        ctx.tuner->lookup(tune_key(ctx, gauge.temporal ? "hop_tg" : "hop", gauge.g, prec, recon, nrhs), sh);
     prof_begin(ctx, s);
     launch_hop_gated(gauge.g, L, prec, recon, dagger, out_parity, nrhs, in, out, gate, gate ? 1 : 0, sh, s);
     prof_end(ctx, prec, recon, (int64_t)gauge.vh * nrhs, s);
