@@ -582,7 +582,7 @@ lqs_status fermion_force(lqs_ctx *ctx, const lqs_gauge *g, const double *X, cons
         double *psx = (double *)ctx->workspace("force.psx", fb);
         double *psy = psx;
         const LinkRef L = g->ref(F64, 18);
-        const LaunchShape sh = default_hop_shape(L, 1);
+        const LaunchShape sh = default_hop_shape(g->g, F64, L, 1);
         launch_hop_gated(g->g, L, F64, 18, 0, 1, 1, X, psx, nullptr, 0, sh, s);
         if (Y && Y != X) {
             psy = (double *)ctx->workspace("force.psy", fb);

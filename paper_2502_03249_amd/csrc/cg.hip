@@ -416,9 +416,13 @@ static void launch_finalize(const CgVectors &v, const double *partials, int nblo
 // ---------------------------------------------------------------------------
 // host side
 
-static int blas_blocks(int64_t vh)
+// Threads per block of the vector kernels: 64 while all sides together leave
+// CUs idle (at most 2^16 sites, and so at most 1024 blocks a side).
+static int blas_block(int64_t vh, int nrhs) { return vh * nrhs <= (1 << 16) ? 64 : BLAS_BLOCK; }
+static int blas_blocks(int64_t vh, int nrhs)
 {
-    int64_t b = (vh + BLAS_BLOCK - 1) / BLAS_BLOCK;
+    const int block = blas_block(vh, nrhs);
+    int64_t b = (vh + block - 1) / block;
     return (int)(b < 1024 ? b : 1024);
 }
 
@@ -441,10 +445,11 @@ void cg_fill_rates(lqs_cg_stats &o, const Gauge &gauge, int prec, int recon, int
 }
 
 // Doubles of partials per right-hand side: one per block of the init (at most
-// 1024) and residual kernels (256 threads), two per block of the normal kernel.
+// 1024) and residual kernels (64 threads or more), two per block of the normal
+// kernel.
 int cg_partials_needed(const Gauge &gauge, int normal_block)
 {
-    const int64_t dots = 2 * ((gauge.vh + normal_block - 1) / normal_block), one = (gauge.vh + 255) / 256;
+    const int64_t dots = 2 * ((gauge.vh + normal_block - 1) / normal_block), one = (gauge.vh + 63) / 64;
     return (int)std::max<int64_t>(1024, std::max(dots, one));
 }
 
@@ -510,12 +515,12 @@ static void launch_step(const Gauge &gauge, const CgVectors &v, int nd_blocks, i
 {
     const int vh = (int)gauge.vh;
     const int64_t sa = field_bytes(gauge.g, PA, 1), si = field_bytes(gauge.g, PI, 1);
-    const dim3 grid(blas_blocks(vh), v.nrhs);
+    const dim3 grid(blas_blocks(vh, v.nrhs), v.nrhs);
     hipLaunchKernelGGL(step_finalize_kernel, dim3(v.nrhs), dim3(1024), 0, s, v.state, (const double *)v.partials,
                        (const double *)v.partials2, v.max_blocks, nd_blocks, (int)grid.x, last, host_phase);
-    const bool early = v.nrhs == 1 && vh <= (int)grid.x * BLAS_BLOCK;
+    const bool early = v.nrhs == 1 && vh <= (int)grid.x * blas_block(vh, v.nrhs);
 #define LQS_STEP(EARLY)                                                                                           \
-    hipLaunchKernelGGL((step_kernel<PA, PI, EARLY>), grid, dim3(BLAS_BLOCK), 0, s, vh, (char *)v.xlo,             \
+    hipLaunchKernelGGL((step_kernel<PA, PI, EARLY>), grid, dim3(blas_block(vh, v.nrhs)), 0, s, vh, (char *)v.xlo,             \
                        (char *)v.r, (char *)v.p, (const char *)v.q, sa, si, (const CgState *)v.state,             \
                        v.partials2, v.max_blocks)
     if (early) LQS_STEP(true);
@@ -530,13 +535,13 @@ static void launch_pdir(const Gauge &gauge, const CgVectors &v, int32_t *host_ph
 {
     const int vh = (int)gauge.vh;
     const int64_t sa = field_bytes(gauge.g, PA, 1), si = field_bytes(gauge.g, PI, 1);
-    hipLaunchKernelGGL((pdir_kernel<PA, PI>), dim3(blas_blocks(vh), v.nrhs), dim3(BLAS_BLOCK), 0, s, vh,
+    hipLaunchKernelGGL((pdir_kernel<PA, PI>), dim3(blas_blocks(vh, v.nrhs), v.nrhs), dim3(blas_block(vh, v.nrhs)), 0, s, vh,
                        (const char *)v.r, (char *)v.p, sa, si, (const CgState *)v.state, host_phase);
     LQS_HIP(hipGetLastError());
 }
 
-// The hop's default launch for this many right-hand sides, in blocks of 256 (the
-// partials are indexed by tile: the sums do not depend on the map or on K).  16
+// The hop's default launch for this many right-hand sides (the partials are
+// indexed by tile: the sums do not depend on the map or on K).  16
 // sides on 32^3 x 8 with 12-real links: 137 us, and 251 with two sides per
 // thread in lexicographic order; 8 sides with 18-real links 80 and 175.
 template <int PA, int R>
@@ -544,8 +549,8 @@ static void launch_residual_k(const Gauge &gauge, const CgVectors &v, int gate_m
 {
     const Geom &g = gauge.g;
     const LinkRef L = gauge.ref(F64, R);
-    const LaunchShape sh = default_hop_shape(L, v.nrhs);
-    const int block = 256, tiles = (g.vh + block - 1) / block;
+    const LaunchShape sh = default_hop_shape(g, F64, L, v.nrhs);
+    const int block = sh.block, tiles = (g.vh + block - 1) / block;
     const int G = (v.nrhs + sh.rhs_per_thread - 1) / sh.rhs_per_thread;
     const TileMap tmap = tile_map(g, block, sh.xcd_slab, time_run(g, block, v.nrhs, F64, sh.trun));
     const dim3 grid(tile_map_blocks(g, block, tmap, G));
@@ -593,10 +598,10 @@ static void launch_residual(const Gauge &gauge, const CgVectors &v, int R, int g
 static void launch_accumulate(const Gauge &gauge, const CgVectors &v, int gate_mode, hipStream_t s)
 {
     const int vh = (int)gauge.vh;
-    dim3 grid(blas_blocks(vh), v.nrhs);
+    dim3 grid(blas_blocks(vh, v.nrhs), v.nrhs);
     const int64_t sa = field_bytes(gauge.g, v.acc_prec, 1);
     LQS_REQUIRE(v.acc_prec == F32, LQS_EUNSUPPORTED, "accumulate needs an FP32 inner solution");
-    hipLaunchKernelGGL((accumulate_kernel<F32>), grid, dim3(BLAS_BLOCK), 0, s, vh, v.x, (char *)v.xlo, sa,
+    hipLaunchKernelGGL((accumulate_kernel<F32>), grid, dim3(blas_block(vh, v.nrhs)), 0, s, vh, v.x, (char *)v.xlo, sa,
                        (const CgState *)v.state, gate_mode);
     LQS_HIP(hipGetLastError());
 }
@@ -605,7 +610,7 @@ static void launch_accumulate(const Gauge &gauge, const CgVectors &v, int gate_m
 static void residual_pass(const Gauge &gauge, const CgVectors &v, int R, int gate_mode, int mode, hipStream_t s)
 {
     const LinkRef L64 = gauge.ref(F64, R);
-    const LaunchShape sh = default_hop_shape(L64, v.nrhs);
+    const LaunchShape sh = default_hop_shape(gauge.g, F64, L64, v.nrhs);
     launch_hop_gated(gauge.g, L64, F64, R, 0, 1, v.nrhs, v.x, v.t64, v.state, gate_mode, sh, s);
     launch_residual(gauge, v, R, gate_mode, mode, s);
 }
@@ -642,12 +647,12 @@ void cg_residual_group(Ctx &ctx, const Gauge &gauge, const CgVectors &v, int gat
 void cg_init(Ctx &ctx, const Gauge &gauge, CgVectors &v, bool use_x0, hipStream_t s)
 {
     const int vh = (int)gauge.vh;
-    dim3 grid(blas_blocks(vh), v.nrhs);
+    dim3 grid(blas_blocks(vh, v.nrhs), v.nrhs);
     const int64_t sa = field_bytes(gauge.g, v.acc_prec, 1), si = field_bytes(gauge.g, v.prec, 1);
     char *xlo = v.acc_prec == F64 ? nullptr : (char *)v.xlo;
     const int cold = use_x0 ? 0 : 1;
 #define LQS_INIT(PA, PI)                                                                                          \
-    hipLaunchKernelGGL((init_kernel<PA, PI>), grid, dim3(BLAS_BLOCK), 0, s, vh, (const char *)v.b, v.x,           \
+    hipLaunchKernelGGL((init_kernel<PA, PI>), grid, dim3(blas_block(vh, v.nrhs)), 0, s, vh, (const char *)v.b, v.x,           \
                        (char *)v.r, (char *)v.p, xlo, sa, si, v.state, v.partials, v.max_blocks, cold)
     if (v.acc_prec == F64) LQS_INIT(F64, F64);
     else if (v.prec == F32) LQS_INIT(F32, F32);
@@ -664,7 +669,7 @@ void cg_init(Ctx &ctx, const Gauge &gauge, CgVectors &v, bool use_x0, hipStream_
 // Launch shapes of the CG kernels (tuned, else the default)
 static void cg_shapes(Ctx &ctx, const Gauge &gauge, CgVectors &v)
 {
-    v.hop_shape = v.normal_shape = default_hop_shape(gauge.ref(v.prec, v.recon), v.nrhs);
+    v.hop_shape = v.normal_shape = default_hop_shape(gauge.g, v.prec, gauge.ref(v.prec, v.recon), v.nrhs);
     if (!ctx.tuner) return;
     const bool tg = gauge.temporal;
     ctx.tuner->lookup(tune_key(ctx, tg ? "hop_tg" : "hop", gauge.g, v.prec, v.recon, v.nrhs), v.hop_shape);

@@ -116,43 +116,61 @@ void launch_hop_gated(const Geom &g, LinkRef L, int prec, int recon, int dagger,
     else launch_pr<F16, 12>(g, L, dagger, parity, nrhs, in, out, gate, gate_mode, sh, s);
 }
 
-// Default shapes from measured sweeps on 32^4, 32^3x8 and 64^3x16: from 4
-// vectors on, 4 right-hand sides per thread in 256-thread blocks with the
-// pencil block -> tile map in runs of time slices (time_run) and prefetched
-// words (steady state, 64^3x16, 4 vectors: FP16 12-real 154 against 197 us
-// without prefetch, FP32 250 against 331, FP64 12-real 501 against 623; 16
-// vectors 10-20 % faster on 32^4 and 64^3x16; the pencil map against
-// time-inner over all slices: 32^4 FP16 12-real 4 vectors 33.7 against
-// 41.9 us, FP64 18-real 16 vectors 458 against 499, 64^3x16 FP64 18-real
-// 16 vectors 1739 against 1946, 32^3x8 FP32 12-real 16 vectors 38 against
-// 49, elsewhere within 3 %); 2 per thread in 128-thread blocks for 2-3 vectors, also
-// prefetched (3 vectors at 64^3x16: FP32 12-real 252 against 336 us, FP64
-// 18-real 688 against 903 us; 2 vectors 0-8 % faster).  Links are streamed
-// when their footprint exceeds STREAM_LINK_BYTES and one group of right-hand
-// sides covers all of them; with several groups the blocks of one site tile
-// reuse the links from L2 (see tile_group) and cached loads win.  One vector
-// on a lattice of at most PREFETCH_MAX_SITES sites per parity (a few waves per
-// SIMD) is prefetched too; on larger ones prefetch is within -7 .. +5 % and
-// left to the tuner.
+// Default shapes, from measured sweeps (us; steady state).
+//
+// One vector: 256-thread blocks, 64 up to 2^15 sites per parity, where a few
+// hundred waves have 256 CUs to spread over (8^4 FP64 5.3 -> 3.4, 16^4 FP64
+// 7.5 -> 6.9, FP32 4.2 -> 3.6; 16^3 x 32, 2^16 sites: 13.5 either way).
+// Prefetched up to PREFETCH_MAX_SITES (a few waves per SIMD); beyond, prefetch
+// is within -7 .. +5 % and left to the tuner.
+//
+// Several vectors, all prefetched.  W = sites per parity times vectors; a
+// thread carries fewer vectors while W leaves CUs idle, at the cost of reading
+// the links once per group of them, from L2:
+//   W <= 2^16: one per thread, blocks of 64 (8^4 with 16 vectors: FP64 18-real
+//     12.6 -> 4.4, FP16 7.6 -> 3.8; 12^4 with 2: 5.6 -> 4.2);
+//   2 or 3 vectors: two per thread, blocks of 64 up to 2^18 sites (24^4: FP64
+//     40.1 -> 38.7, FP16 11.4 -> 10.4) and of 128 beyond;
+//   W <= 2^17, or where whole tiles of 128 sites do not make up a z plane: two
+//     per thread, blocks of 64 (16^4 with 4 vectors: FP32 8.5 -> 6.1; 24^4 with
+//     4: FP64 63.7 -> 51.2, FP32 26.6 -> 19.4, with 16: FP32 70 -> 57; 24^3 x 8
+//     with 16: FP64 53.8 -> 44.6), except FP16 storage with more than 8 vectors,
+//     bound by the vector ALU: four (24^4 with 16: 50.5 -> 46.0);
+//   else four per thread and the pencil block -> tile map in runs of time slices
+//     (time_run), in blocks of 256 where they tile a z plane (against 64 and two
+//     per thread: 32^3 x 8 with 16, FP64 152 -> 112, FP32 45 -> 40; 64^3 x 16 and
+//     32^4 alike), else of 128 (48^3 x 16 with 16: FP64 813 -> 735).
+//
+// Links are streamed when their footprint exceeds STREAM_LINK_BYTES and one
+// group of right-hand sides covers all of them; with several groups the blocks
+// of one site tile reuse the links from L2 (see tile_group) and cached loads win.
 static constexpr int64_t PREFETCH_MAX_SITES = (int64_t)1 << 18;
-LaunchShape default_hop_shape(const LinkRef &L, int nrhs)
+LaunchShape default_hop_shape(const Geom &g, int prec, const LinkRef &L, int nrhs)
 {
     LaunchShape sh;
-    if (nrhs >= 4) {
-        sh.block = 256;
+    const int64_t vh = g.vh, w = vh * nrhs, plane = (int64_t)g.n[0] * g.n[1] / 2;
+    sh.prefetch = 1;
+    if (nrhs == 1) {
+        sh.block = vh <= (1 << 15) ? 64 : 256;
+        sh.prefetch = vh <= PREFETCH_MAX_SITES ? 1 : 0;
+    } else if (w <= (1 << 16)) {
+        sh.block = 64;
+    } else if (nrhs < 4) {
+        sh.block = vh <= (1 << 18) ? 64 : 128;
+        sh.rhs_per_thread = 2;
+    } else if (w > (1 << 17) && plane % 128 == 0) {
+        sh.block = plane % 256 == 0 ? 256 : 128;
         sh.rhs_per_thread = 4;
         sh.xcd_slab = 3;
-        sh.prefetch = 1;
-    } else if (nrhs >= 2) {
-        sh.block = 128;
-        sh.rhs_per_thread = 2;
-        sh.prefetch = 1;
+    } else if (w > (1 << 17) && prec == F16 && nrhs > 8) {
+        sh.block = 64;
+        sh.rhs_per_thread = 4;
+        sh.xcd_slab = 3;
     } else {
-        sh.block = 256;
-        sh.rhs_per_thread = 1;
+        sh.block = 64;
+        sh.rhs_per_thread = 2;
     }
     sh.stream_links = (8 * L.block_bytes >= STREAM_LINK_BYTES && nrhs <= sh.rhs_per_thread) ? 1 : 0;
-    if (sh.rhs_per_thread == 1) sh.prefetch = L.pitch <= PREFETCH_MAX_SITES ? 1 : 0;
     return sh;
 }
 
@@ -192,7 +210,7 @@ void launch_hop(Ctx &ctx, const Gauge &gauge, int prec, int recon, int dagger, i
                 const void *in, void *out, hipStream_t s, const CgState *gate)
 {
     const LinkRef L = gauge.ref(prec, recon);
-    LaunchShape sh = default_hop_shape(L, nrhs);
+    LaunchShape sh = default_hop_shape(gauge.g, prec, L, nrhs);
     // (the key is a string: 1.5 us to form, not for an empty cache)
     if (ctx.tuner && !ctx.tuner->cache.empty())
         ctx.tuner->lookup(tune_key(ctx, gauge.temporal ? "hop_tg" : "hop", gauge.g, prec, recon, nrhs), sh);

@@ -762,7 +762,7 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
     for (int prec = 0; prec < 3; ++prec)
         for (int rc = 0; rc < 2; ++rc) fmts.fmt[prec][rc] = (char *)gauge.fmt[prec][rc];
     launch_pack_links(g, links, fmts, g.vh, s);
-    const LaunchShape sh = default_hop_shape(L64, 1);
+    const LaunchShape sh = default_hop_shape(g, F64, L64, 1);
 
     double *phi = nullptr, *chi = nullptr, *psx = nullptr, *chi_prev = nullptr;
     int cg_solves = 0, cg_iters = 0, worst = LQS_OK;

@@ -232,7 +232,7 @@ struct LaunchShape {
 constexpr int64_t STREAM_LINK_BYTES = 192ll << 20;
 void launch_hop(Ctx &ctx, const Gauge &gauge, int prec, int recon, int dagger, int out_parity, int nrhs,
                 const void *in, void *out, hipStream_t s, const CgState *gate);
-LaunchShape default_hop_shape(const LinkRef &L, int nrhs);
+LaunchShape default_hop_shape(const Geom &g, int prec, const LinkRef &L, int nrhs);
 void launch_hop_gated(const Geom &g, LinkRef L, int prec, int recon, int dagger, int parity, int nrhs,
                       const void *in, void *out, const CgState *gate, int gate_mode, LaunchShape sh, hipStream_t s);
 void launch_hop_shape(const Geom &g, LinkRef links, int prec, int recon, int dagger, int out_parity, int nrhs,

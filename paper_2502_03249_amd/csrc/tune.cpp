@@ -195,7 +195,7 @@ void autotune(Ctx &ctx, const Gauge &gauge, const char *kernel, int prec, int re
     // otherwise be picked by noise (measured: a 64-thread FP16 hop chosen
     // this way made the 64^3 x 16 solve 1 % slower than the default).
     constexpr float MARGIN = 0.98f;
-    LaunchShape best_shape = default_hop_shape(L, nrhs);
+    LaunchShape best_shape = default_hop_shape(g, prec, L, nrhs);
     // After an idle spell the first launches run slower for several
     // milliseconds; the default shape, timed first, would be measured cold
     // against candidates timed warm.  Run it back to back for about 20 ms
@@ -245,7 +245,7 @@ void autotune(Ctx &ctx, const Gauge &gauge, const char *kernel, int prec, int re
     // Confirm a winner against the default with fresh timings, the two
     // alternating: on lattices whose launches take 10-20 us one noisy median
     // had picked shapes up to 34 % slower than the default.
-    const LaunchShape def = default_hop_shape(L, nrhs);
+    const LaunchShape def = default_hop_shape(g, prec, L, nrhs);
     auto same = [](const LaunchShape &a, const LaunchShape &b) {
         return a.block == b.block && a.rhs_per_thread == b.rhs_per_thread && a.stream_links == b.stream_links &&
                a.xcd_slab == b.xcd_slab && a.lds == b.lds && a.prefetch == b.prefetch && a.trun == b.trun;
