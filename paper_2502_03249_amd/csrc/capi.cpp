@@ -160,9 +160,11 @@ Gauge::~Gauge()
     if (!block) return;
     int cur = -1;
     if (hipGetDevice(&cur) != hipSuccess) cur = -1;
-    (void)hipSetDevice(pool->device);
-    (void)hipDeviceSynchronize();
-    pool->give(block, block_bytes);
+    // without the wait (a stream capture forbids it, say) the block is not known
+    // to be idle: freed, not kept
+    if (hipSetDevice(pool->device) == hipSuccess && hipDeviceSynchronize() == hipSuccess)
+        pool->give(block, block_bytes);
+    else (void)hipFree(block);
     if (cur >= 0) (void)hipSetDevice(cur);
 }
 
