@@ -68,13 +68,17 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
                                                    const double *rr_partials, int nblocks, int nr_blocks, int last,
                                                    int32_t *host_phase)
 {
-    CgState &S = *base;
-    const int phase = S.phase;
+    // the records and the partials are requested together
+    CgState S = *base;
+    const int phase = S.phase, i = threadIdx.x;
+    const bool mine = i < nshift;
+    ShiftState T{};
+    if (mine) T = sh[i];
     double v[4] = {0.0, 0.0, (int)threadIdx.x < nr_blocks ? rr_partials[threadIdx.x] : 0.0, 0.0};
     const double2 *p2 = (const double2 *)partials;
 #pragma unroll 4
-    for (int i = threadIdx.x; i < nblocks; i += blockDim.x) {
-        const double2 a = p2[i];
+    for (int k = threadIdx.x; k < nblocks; k += blockDim.x) {
+        const double2 a = p2[k];
         v[0] += a.x;
         v[1] += a.y;
     }
@@ -83,10 +87,6 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
     if (threadIdx.x >= 64) return;
     const double pq = v[0], qq = v[1], rr = S.rho_known ? S.rho : v[2];
     // lane i < nshift advances shift i; lane 0 the base
-    const int i = threadIdx.x;
-    const bool mine = i < nshift;
-    ShiftState T{};
-    if (mine) T = sh[i];
     const bool ok = phase == CG_RUNNING && isfinite(pq) && pq > 0.0;
     const double a_prev = S.alpha, b_prev = S.beta, a = ok ? rr / pq : 0.0;
     double r2 = fma(a * a, qq, -rr);
@@ -110,10 +110,15 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
     const bool any = __any(mine && T.active);
     if (i != 0) return;
     struct Publish {
-        CgState &S;
+        const CgState &S;
+        CgState *base;
         int32_t *host;
-        __device__ ~Publish() { publish(host, 0, S.phase); }
-    } published{S, host_phase};
+        __device__ ~Publish()
+        {
+            *base = S;
+            publish(host, 0, S.phase);
+        }
+    } published{S, base, host_phase};
     S.live = 0;
     S.p_due = 0;
     if (phase != CG_RUNNING) return;
@@ -188,6 +193,12 @@ __global__ void ms_rebeta(const CgState *base, ShiftState *sh, int nshift)
 // a site and shift and 7 for the base.  (One block grid per system instead of
 // the loop over the shifts measured slower: 0.41 vs 0.37 s for 8 masses on
 // 64^3 x 16 in FP64, as every system re-read the residual.)
+//
+// A lattice of 32^3 x 8 gives each SIMD two waves, so a wave has its own next
+// loads in flight: the block keeps the scalars and addresses of the shifts that
+// are due in LDS, and x_i, p_i of the next one are requested before the present
+// one is advanced (8 masses in FP64: 42.0 -> 34.6 us; 64^3 x 16: solve 357 -> 349 ms;
+// 16^3 x 8 with 12 masses, in blocks of 64: 6.4 -> 3.3 ms with the earlier steps).
 template <int PI, int PR, bool DIRS>
 __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, char *p0, const char *q,
                                                     const ShiftPtrs *ptr, int nshift, const CgState *base,
@@ -195,17 +206,70 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, c
 {
     typedef typename RealOf<PI>::type TI;
     typedef typename RealOf<PR>::type TR;
-    if (DIRS && blockIdx.x == 0 && threadIdx.x == 0) publish(host_phase, 0, base->phase);
-    if (DIRS ? (!base->p_due || base->phase != CG_RUNNING) : !base->live) return;
-    const double a = base->alpha, b = base->beta;
-    const bool pdir = DIRS || !base->p_due;
-    double local = 0.0;
-    for (int cb = blockIdx.x * blockDim.x + threadIdx.x; cb < vh; cb += gridDim.x * blockDim.x) {
-        V3<double> pv = vcast<double>(SpinorIO<PI>::load(p0, vh, cb));
-        V3<double> rv = vcast<double>(SpinorIO<PR>::load(r, vh, cb));
+    typedef typename SpinorIO<PI>::Raw RawI;
+    typedef typename SpinorIO<PR>::Raw RawR;
+    struct Due {
+        char *x, *p;
+        double alpha, beta, zeta;
+        int act;  // p_i too
+    };
+    __shared__ Due due[MS_MAX];
+    __shared__ int ndue;
+    const int c0 = blockIdx.x * blockDim.x + threadIdx.x;
+    RawI praw, qraw{};
+    RawR rraw, xraw{};
+    auto load_base = [&](int cb) {
+        praw = SpinorIO<PI>::load_raw(p0, vh, cb);
+        rraw = SpinorIO<PR>::load_raw(r, vh, cb);
         if (!DIRS) {
-            const V3<double> qv = vcast<double>(SpinorIO<PI>::load(q, vh, cb));
-            V3<double> xv = vcast<double>(SpinorIO<PR>::load(x0, vh, cb));
+            qraw = SpinorIO<PI>::load_raw(q, vh, cb);
+            xraw = SpinorIO<PR>::load_raw(x0, vh, cb);
+        }
+    };
+    // the first site's vectors and the records in one memory round trip
+    load_base(c0 < vh ? c0 : vh - 1);
+    const int phase = base->phase;
+    const bool p_due = base->p_due != 0, on = DIRS ? p_due && phase == CG_RUNNING : base->live != 0;
+    const double a = base->alpha, b = base->beta;
+    const bool pdir = DIRS || !p_due;
+    if (threadIdx.x < 64) {
+        const int i = threadIdx.x;
+        Due d{};
+        bool is = false;
+        if (i < nshift) {
+            const ShiftState T = sh[i];
+            d = {ptr->x[i], ptr->p[i], T.alpha, T.beta, T.zeta, pdir && T.active != 0};
+            is = DIRS ? d.act != 0 : T.xupd != 0;  // (an active shift always has an x_i update due)
+        }
+        const unsigned long long m = __ballot(is);
+        if (is) due[__popcll(m & ((1ull << i) - 1))] = d;
+        if (i == 0) ndue = __popcll(m);
+    }
+    issue_here(praw);
+    issue_here(rraw);
+    if (!DIRS) {
+        issue_here(qraw);
+        issue_here(xraw);
+    }
+    if (DIRS && blockIdx.x == 0 && threadIdx.x == 0) publish(host_phase, 0, phase);
+    if (!on) return;
+    __syncthreads();
+    const int n = ndue;
+    double local = 0.0;
+    for (int cb = c0; cb < vh; cb += gridDim.x * blockDim.x) {
+        if (cb != c0) load_base(cb);
+        RawI pnext{};
+        RawR xnext{};
+        auto load_shift = [&](int i) {
+            pnext = SpinorIO<PI>::load_raw(due[i].p, vh, cb);
+            if (!DIRS) xnext = SpinorIO<PR>::load_raw(due[i].x, vh, cb);
+        };
+        if (n > 0) load_shift(0);
+        V3<double> pv = vcast<double>(SpinorIO<PI>::decode(praw));
+        V3<double> rv = vcast<double>(SpinorIO<PR>::decode(rraw));
+        if (!DIRS) {
+            const V3<double> qv = vcast<double>(SpinorIO<PI>::decode(qraw));
+            V3<double> xv = vcast<double>(SpinorIO<PR>::decode(xraw));
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 xv.c[c].re += a * pv.c[c].re;
@@ -228,28 +292,27 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, c
             }
             SpinorIO<PI>::store(p0, vh, cb, vcast<TI>(pv));
         }
-        for (int i = 0; i < nshift; ++i) {
-            const bool xu = !DIRS && sh[i].xupd != 0, act = pdir && sh[i].active != 0;
-            if (!xu && !act) continue;
-            V3<double> pi = vcast<double>(SpinorIO<PI>::load(ptr->p[i], vh, cb));
-            if (xu) {
-                const double ai = sh[i].alpha;
-                V3<double> xi = vcast<double>(SpinorIO<PR>::load(ptr->x[i], vh, cb));
+#pragma unroll 1
+        for (int i = 0; i < n; ++i) {
+            const Due d = due[i];
+            V3<double> pi = vcast<double>(SpinorIO<PI>::decode(pnext));
+            V3<double> xi = vcast<double>(SpinorIO<PR>::decode(xnext));
+            if (i + 1 < n) load_shift(i + 1);
+            if (!DIRS) {
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    xi.c[c].re += ai * pi.c[c].re;
-                    xi.c[c].im += ai * pi.c[c].im;
+                    xi.c[c].re += d.alpha * pi.c[c].re;
+                    xi.c[c].im += d.alpha * pi.c[c].im;
                 }
-                SpinorIO<PR>::store(ptr->x[i], vh, cb, vcast<TR>(xi));
+                SpinorIO<PR>::store(d.x, vh, cb, vcast<TR>(xi));
             }
-            if (!act) continue;
-            const double z = sh[i].zeta, bi = sh[i].beta;
+            if (!d.act) continue;
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                pi.c[c].re = z * rv.c[c].re + bi * pi.c[c].re;
-                pi.c[c].im = z * rv.c[c].im + bi * pi.c[c].im;
+                pi.c[c].re = d.zeta * rv.c[c].re + d.beta * pi.c[c].re;
+                pi.c[c].im = d.zeta * rv.c[c].im + d.beta * pi.c[c].im;
             }
-            SpinorIO<PI>::store(ptr->p[i], vh, cb, vcast<TI>(pi));
+            SpinorIO<PI>::store(d.p, vh, cb, vcast<TI>(pi));
         }
     }
     if (DIRS) return;
@@ -380,7 +443,9 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
 
     if (mixed)
         for (int i = 0; i < nmass; ++i) LQS_HIP(hipMemsetAsync(x[i], 0, field_bytes(g, F64, 1), s));
-    int blocks = (vh + MS_BLOCK - 1) / MS_BLOCK;
+    // threads per block as in the CG's vector kernels: 64 while 256 leave CUs idle
+    const int block = vh <= (1 << 16) ? 64 : MS_BLOCK;
+    int blocks = (vh + block - 1) / block;
     if (blocks > 1024) blocks = 1024;
 #define LQS_MS_PREC(STMT)                                                                                         \
     if (PI == F64) {                                                                                              \
@@ -393,7 +458,7 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
         constexpr int P_I = F16, P_R = F32;                                                                       \
         STMT;                                                                                                     \
     }
-    LQS_MS_PREC(hipLaunchKernelGGL((ms_init<P_I, P_R>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh, b, xr[base], (char *)v.r,
+    LQS_MS_PREC(hipLaunchKernelGGL((ms_init<P_I, P_R>), dim3(blocks), dim3(block), 0, s, vh, b, xr[base], (char *)v.r,
                                    (char *)v.p, (const ShiftPtrs *)dp, nshift, v.partials));
     hipLaunchKernelGGL(ms_finalize_init, dim3(1), dim3(1024), 0, s, v.state, (const double *)v.partials, blocks);
     LQS_HIP(hipGetLastError());
@@ -425,17 +490,17 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
             launch_normal_dot_shape(gauge, v, sh, s);
             hipLaunchKernelGGL(ms_scalars, dim3(1), dim3(1024), 0, s, v.state, dsh, nshift, (const double *)v.partials,
                                (const double *)v.partials2, nd_blocks, blocks, group, mixed ? nullptr : tell);
-            LQS_MS_PREC(hipLaunchKernelGGL((ms_step<P_I, P_R, false>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh, xr[base],
+            LQS_MS_PREC(hipLaunchKernelGGL((ms_step<P_I, P_R, false>), dim3(blocks), dim3(block), 0, s, vh, xr[base],
                                            (char *)v.r, (char *)v.p, (const char *)v.q, (const ShiftPtrs *)dp, nshift,
                                            (const CgState *)v.state, (const ShiftState *)dsh, v.partials2,
                                            (int32_t *)nullptr));
             if (group) {
                 // reliable update (gated on the base's pending flag)
-                hipLaunchKernelGGL((ms_accumulate<F32>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh, (const ShiftPtrs *)dp,
+                hipLaunchKernelGGL((ms_accumulate<F32>), dim3(blocks), dim3(block), 0, s, vh, (const ShiftPtrs *)dp,
                                    nshift, (const CgState *)v.state, 1);
                 cg_reliable_group(gauge, v, s);
                 hipLaunchKernelGGL(ms_rebeta, dim3(1), dim3(64), 0, s, (const CgState *)v.state, dsh, nshift);
-                LQS_MS_PREC(hipLaunchKernelGGL((ms_step<P_I, P_R, true>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh,
+                LQS_MS_PREC(hipLaunchKernelGGL((ms_step<P_I, P_R, true>), dim3(blocks), dim3(block), 0, s, vh,
                                                xr[base], (char *)v.r, (char *)v.p, (const char *)v.q,
                                                (const ShiftPtrs *)dp, nshift, (const CgState *)v.state,
                                                (const ShiftState *)dsh, v.partials2, tell));
@@ -455,7 +520,7 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
 
 #undef LQS_MS_PREC
     if (mixed) {
-        hipLaunchKernelGGL((ms_accumulate<F32>), dim3(blocks), dim3(MS_BLOCK), 0, s, vh, (const ShiftPtrs *)dall,
+        hipLaunchKernelGGL((ms_accumulate<F32>), dim3(blocks), dim3(block), 0, s, vh, (const ShiftPtrs *)dall,
                            nshift + 1, (const CgState *)v.state, 0);
         LQS_HIP(hipGetLastError());
     }

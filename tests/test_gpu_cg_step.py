@@ -61,3 +61,20 @@ def test_shifted_steps_follow_the_oracle(ctx, dims, prec):
         assert oracle.true_residual(dims, U, m, b, x) <= 1e-10
         xo, _, _, _ = oracle.cg(dims, U, m, b)
         assert rel(x, xo) <= (m * m + 64) / (m * m) * 1e-10
+
+
+@pytest.mark.parametrize("prec", [lqs.F64, lqs.F32])
+@pytest.mark.parametrize("dims", [(16, 16, 16, 32), (18, 16, 14, 34), (32, 32, 32, 18)])
+def test_shifted_steps_on_each_launch(ctx, dims, prec):
+    """2^16 sites per parity (blocks of 64), just above (256, a ragged last block), several sites per thread;
+    the shifts stop one after the other."""
+    masses = [0.8, 0.5, 5.0, 1.1, 2.0]
+    U = synth.gauge(dims, "smooth", seed=65, eps=0.3)
+    b = synth.source(dims, 0, seed=66)
+    g = gauge(ctx, dims, U)
+    bf = field(ctx, dims, b, 0)
+    xs = [bf.like() for _ in masses]
+    st = lqs.cg_solve_multishift(ctx, g, masses, bf, xs, tol=1e-10, inner_prec=prec)
+    for m, xf, s in zip(masses, xs, st):
+        assert s["status"] == 0, s
+        assert oracle.true_residual(dims, U, m, b, lex_of(ctx, xf)) <= 1e-10
