@@ -135,26 +135,22 @@ normal_dot_kernel(Geom g, LinkRef L, const char *t, const char *p, char *q, int6
 // every block of the step kernel instead, with the state record double
 // buffered, was slower: 20 us for that kernel at 32^3 x 8 in FP64 against 4.8
 // for this one and 9.3 for the step.)
+// Bound by its latencies: the record and the first 1024 pairs of partials come in
+// one round trip, further ones four at a time, and one wave alone adds the rows
+// (64^3 x 16, 8192 pairs: 7.1 -> 5.5 us; 24^4 solves 1 to 2.6 % faster).
 
 __global__ void __launch_bounds__(1024) step_finalize_kernel(CgState *st, const double *partials,
                                                             const double *rr_partials, int max_blocks, int nblocks,
                                                             int nr_blocks, int last, int32_t *host_phase)
 {
     const int r = blockIdx.x;
-    const double2 *pp = (const double2 *)(partials + (int64_t)r * max_blocks);
-    const double *rp = rr_partials + (int64_t)r * max_blocks;
+    const double *pp = partials + (int64_t)r * max_blocks;
+    const DotShare first = first_dots(pp, rr_partials + (int64_t)r * max_blocks, nblocks, nr_blocks);
     CgState S = st[r];
-    // (v[3]: padding to a power of two)
-    double v[4] = {0.0, 0.0, (int)threadIdx.x < nr_blocks ? rp[threadIdx.x] : 0.0, 0.0};  // nr_blocks <= 1024
-#pragma unroll 4
-    for (int i = threadIdx.x; i < nblocks; i += blockDim.x) {
-        const double2 a = pp[i];
-        v[0] += a.x;
-        v[1] += a.y;
-    }
+    double v[4];
+    add_dots(pp, nblocks, nr_blocks, first, v);
     __shared__ double red[16][4];
-    block_sums_all<4>(v, red);
-    if (threadIdx.x != 0) return;
+    if (!block_sums_first<4>(v, red) || threadIdx.x != 0) return;
     if (S.phase == CG_RUNNING) cg_step_scalars(S, v[0], v[1], v[2], last);
     else S.live = 0;
     st[r] = S;

@@ -93,6 +93,47 @@ __device__ inline void fin_residual(CgState &S, double r2, int mode)
     }
 }
 
+// A thread's share (of 1024 threads) of the block partials of <p,q> and <q,q>
+// (pairs, nblocks >= 1) and of |r|^2 (1 <= nr_blocks <= 1024).  `first` holds what is
+// requested before anything is waited for, so that a record loaded between the
+// two calls shares the round trip.
+struct DotShare {
+    double2 pq;
+    double rr;
+};
+__device__ __forceinline__ DotShare first_dots(const double *partials, const double *rr_partials, int nblocks,
+                                               int nr_blocks)
+{
+    const int i = threadIdx.x;
+    return {((const double2 *)partials)[i < nblocks ? i : nblocks - 1], rr_partials[i < nr_blocks ? i : nr_blocks - 1]};
+}
+__device__ __forceinline__ void add_dots(const double *partials, int nblocks, int nr_blocks, const DotShare &first,
+                                         double (&v)[4])
+{
+    const double2 *pp = (const double2 *)partials;
+    const int i0 = threadIdx.x;
+    v[0] = v[1] = v[2] = v[3] = 0.0;  // (v[3]: padding to a power of two)
+    if (i0 < nblocks) {
+        v[0] = first.pq.x;
+        v[1] = first.pq.y;
+    }
+    if (i0 < nr_blocks) v[2] = first.rr;
+    for (int b = 1024; b < nblocks; b += 4 * 1024) {
+        double2 a[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = b + 1024 * k + i0;
+            a[k] = pp[i < nblocks ? i : nblocks - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (b + 1024 * k + i0 < nblocks) {
+                v[0] += a[k].x;
+                v[1] += a[k].y;
+            }
+    }
+}
+
 // The phase of a right-hand side for the host, in pinned memory (null: not now).
 // Phases only move towards a final one while the host waits, so a word that a
 // later kernel overwrites meanwhile misleads nobody.  (A copy of the records on

@@ -760,8 +760,7 @@ template <int N> __device__ __forceinline__ double wave_sums(double (&v)[N], int
 }
 
 // Sums of N values over the block (blockDim.x a multiple of 64; red: one row
-// per wave).  block_sums: thread k < N gets sum k in v[0].  block_sums_all:
-// every thread gets all N.
+// per wave).  Thread k < N gets sum k in v[0].
 template <int N> __device__ __forceinline__ void block_sums(double (&v)[N], double (*red)[N])
 {
     int idx;
@@ -775,19 +774,30 @@ template <int N> __device__ __forceinline__ void block_sums(double (&v)[N], doub
         v[0] = t;
     }
 }
-template <int N> __device__ __forceinline__ void block_sums_all(double (&v)[N], double (*red)[N])
+// `v` of one lane, in every lane
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    struct I2 { int lo, hi; } w = bitcast<I2>(v);
+    w.lo = __builtin_amdgcn_readlane(w.lo, lane);
+    w.hi = __builtin_amdgcn_readlane(w.hi, lane);
+    return bitcast<double>(w);
+}
+// block_sums for a block of 16 waves, in every lane of its first wave (true);
+// the other waves are done (false).
+template <int N> __device__ __forceinline__ bool block_sums_first(double (&v)[N], double (*red)[N])
 {
     int idx;
     const double s = wave_sums<N>(v, idx);
-    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63;
     if ((lane & (64 / N - 1)) == 0) red[threadIdx.x >> 6][idx] = s;
     __syncthreads();
+    if (threadIdx.x >= 64) return false;
+    double t = 0.0;
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        double t = 0.0;
-        for (int w = 0; w < nw; ++w) t += red[w][k];
-        v[k] = t;
-    }
+    for (int w = 0; w < 16; ++w) t += red[w][lane & (N - 1)];
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = lane_value(t, k);
+    return true;
 }
 
 // Fixed-order sum of n partials by one block (valid in every thread); the

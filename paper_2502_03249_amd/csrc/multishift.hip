@@ -68,23 +68,16 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
                                                    const double *rr_partials, int nblocks, int nr_blocks, int last,
                                                    int32_t *host_phase)
 {
-    // the records and the partials are requested together
+    const DotShare first = first_dots(partials, rr_partials, nblocks, nr_blocks);
     CgState S = *base;
     const int phase = S.phase, i = threadIdx.x;
     const bool mine = i < nshift;
     ShiftState T{};
     if (mine) T = sh[i];
-    double v[4] = {0.0, 0.0, (int)threadIdx.x < nr_blocks ? rr_partials[threadIdx.x] : 0.0, 0.0};
-    const double2 *p2 = (const double2 *)partials;
-#pragma unroll 4
-    for (int k = threadIdx.x; k < nblocks; k += blockDim.x) {
-        const double2 a = p2[k];
-        v[0] += a.x;
-        v[1] += a.y;
-    }
+    double v[4];
+    add_dots(partials, nblocks, nr_blocks, first, v);
     __shared__ double red[16][4];
-    block_sums_all<4>(v, red);
-    if (threadIdx.x >= 64) return;
+    if (!block_sums_first<4>(v, red)) return;
     const double pq = v[0], qq = v[1], rr = S.rho_known ? S.rho : v[2];
     // lane i < nshift advances shift i; lane 0 the base
     const bool ok = phase == CG_RUNNING && isfinite(pq) && pq > 0.0;

@@ -167,14 +167,6 @@ template <int NW> __device__ __forceinline__ double quad_class_sum(double v, dou
     t += __shfl_xor(t, 32, 64);
     return t;
 }
-__device__ __forceinline__ double lane_value(double v, int lane)
-{
-    struct I2 { int lo, hi; } w = bitcast<I2>(v);
-    w.lo = __builtin_amdgcn_readlane(w.lo, lane);
-    w.hi = __builtin_amdgcn_readlane(w.hi, lane);
-    return bitcast<double>(w);
-}
-
 template <int P, int R, int BS, int S>
 __global__ void __launch_bounds__(BS) small_cg_kernel(const SmallLat *lats, CgState *states, int max_trips,
                                                       unsigned long long *clk)
