@@ -380,9 +380,11 @@ __global__ void __launch_bounds__(1024) finalize_kernel(CgState *st, const doubl
     double acc = 0.0;
     acc += i0 < nblocks ? first : 0.0;
     for (int i = i0 + blockDim.x; i < nblocks; i += blockDim.x) acc += p[i];
-    bool active = true;
-    if (mode == FIN_RESID) active = gate_state(S, gate_mode);
-    if (!active) return;
+    if (mode == FIN_RESID && !gate_state(S, gate_mode)) {
+        // sub 4: a direction left to a group before this one has been formed there
+        if (sub == 4 && S.phase == CG_RUNNING && threadIdx.x == 0) st[r].p_due = 0;
+        return;
+    }
     const double v = block_sum(acc);
     if (threadIdx.x != 0) return;
     if (mode == FIN_RESID) {
@@ -636,7 +638,7 @@ void cg_residual_group(Ctx &ctx, const Gauge &gauge, const CgVectors &v, int gat
 {
     (void)ctx;
     const bool mixed = v.acc_prec != F64;
-    if (mixed && mode == 0) launch_accumulate(gauge, v, gate_mode, s);
+    if (mixed && (mode == 0 || mode == 4)) launch_accumulate(gauge, v, gate_mode, s);
     residual_pass(gauge, v, 18, gate_mode, mode, s);
 }
 
@@ -713,10 +715,12 @@ static void cg_iteration(Ctx &ctx, const Gauge &gauge, CgVectors &v, hipStream_t
 // The FP64 check of the right-hand sides whose iterated residual met the target
 // or that reached the iteration cap, always with the stored 18-real links, so
 // the reported residual is that of the operator the caller passed; a side that
-// is above the target goes on.
+// is above the target goes on.  The others are left as they are: one that took a
+// reliable update at the end of the round before has its direction already
+// (formed a second time, it would no longer belong to the residual).
 static void cg_final_check(Ctx &ctx, const Gauge &gauge, CgVectors &v, hipStream_t s, int32_t *host_phase)
 {
-    cg_residual_group(ctx, gauge, v, 4, 0, s);
+    cg_residual_group(ctx, gauge, v, 4, 4, s);
     with_precs(v, [&](auto pa, auto pi) { launch_pdir<pa.value, pi.value>(gauge, v, host_phase, s); });
 }
 

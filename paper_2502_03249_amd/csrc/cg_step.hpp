@@ -52,7 +52,8 @@ __device__ inline void cg_step_scalars(CgState &S, double pq, double qq, double 
 // mode: 0 reliable update inside the iteration, 1 initial residual, 2 measure
 // only, 3 periodic update with the reconstructed FP64 links (a residual that
 // meets the target is handed on, still pending, to the mode-0 check with the
-// stored links instead of ending the solve)
+// stored links instead of ending the solve), 4 as 0, queued by the host after
+// a round has ended
 __device__ inline void fin_residual(CgState &S, double r2, int mode)
 {
     S.true_r2 = r2;
