@@ -113,8 +113,8 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
         }
     } published{S, base, host_phase};
     S.live = 0;
+    if (phase != CG_RUNNING) return;  // (a direction left to the FP64 group stays due until it has run)
     S.p_due = 0;
-    if (phase != CG_RUNNING) return;
     if (!ok) {
         S.phase = isfinite(pq) ? CG_BREAKDOWN : CG_NONFINITE;
         return;
