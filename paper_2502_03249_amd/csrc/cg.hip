@@ -239,7 +239,7 @@ __global__ void __launch_bounds__(BLAS_BLOCK) pdir_kernel(int vh, const char *r,
     const int rhs = blockIdx.y;
     const CgState &S = st[rhs];
     if (blockIdx.x == 0 && threadIdx.x == 0) publish(host_phase, rhs, S.phase);
-    if (!S.p_due || S.phase != CG_RUNNING) return;
+    if (!S.p_due || S.phase != CG_RUNNING || S.unsettled) return;
     const T beta = (T)S.beta;
     r += rhs * sa;
     p += rhs * si;
@@ -901,7 +901,7 @@ struct CgRun {
             LQS_HIP(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
             LQS_HIP(hipEventCreateWithFlags(&ev[1], hipEventDisableTiming));
         }
-        cap = (int64_t)prm.max_iter + 16 * chunk + 64;
+        cap = 2 * (int64_t)prm.max_iter + 16 * chunk + 64;  // (an iteration may be followed by one that settles it)
     }
 
     // queue the final check that a right-hand side waits for, or one round of

@@ -6,37 +6,69 @@
 
 namespace lqs {
 
+// A predicted |r|^2 that says nothing.  It is the difference of two numbers of
+// about |r|^2 before the step (rr), each a sum that is good to a few ulp: below
+// 16 ulp of rr it is their rounding, unless the target lies above that too.  It
+// is negative by more where <r,q> = <p,q> no longer holds (directions in 16
+// bits that have lost their conjugacy).  Either way it neither ends a solve nor
+// gives a beta.
+__device__ inline bool prediction_lost(double r2, double rr, double stop2)
+{
+    const double noise = 16.0 * 2.220446049250313e-16 * rr;
+    return r2 < 0.0 || (r2 <= noise && noise > stop2);
+}
+
 // Scalars of one iteration from its dots (rr: |r|^2 as the last step summed it,
 // unused while S.rho holds a measured one).  `live`: this iteration's update is
 // due; `p_due`: the direction update is left to the FP64 group that closes the
-// round (`last`: the group follows this iteration).
+// round (`last`: the group follows this iteration).  After a step whose
+// prediction is lost x and r are advanced and the direction is not; the next
+// iteration forms it with the |r|^2 that the step has summed (`unsettled`; its
+// own products of the old direction are not used).
 
 __device__ inline void cg_step_scalars(CgState &S, double pq, double qq, double rr, int last)
 {
     if (S.rho_known) rr = S.rho;
     S.live = 0;
     S.p_due = 0;
-    if (!isfinite(pq)) {
-        S.phase = CG_NONFINITE;
-        return;
+    double r2;
+    if (S.unsettled) {
+        S.unsettled = 0;
+        r2 = rr;
+        S.alpha = 0.0;
+        if (!isfinite(r2)) {
+            S.phase = CG_NONFINITE;
+            return;
+        }
+    } else {
+        if (!isfinite(pq)) {
+            S.phase = CG_NONFINITE;
+            return;
+        }
+        if (!(pq > 0.0)) {
+            S.phase = CG_BREAKDOWN;
+            return;
+        }
+        S.alpha = rr / pq;
+        r2 = fma(S.alpha * S.alpha, qq, -rr);
+        S.rho_known = 0;
+        S.iters += 1;
+        S.since_rel += 1;
+        if (!isfinite(r2)) {
+            S.phase = CG_NONFINITE;
+            return;
+        }
+        S.rho_old = rr;
+        if (prediction_lost(r2, rr, S.stop2) && S.iters < S.max_iter) {
+            S.unsettled = 1;
+            S.live = 1;
+            S.p_due = 1;
+            if (S.rel_interval > 0 && S.since_rel >= S.rel_interval) S.reliable_pending = 1;
+            return;
+        }
     }
-    if (!(pq > 0.0)) {
-        S.phase = CG_BREAKDOWN;
-        return;
-    }
-    S.alpha = rr / pq;
-    double r2 = fma(S.alpha * S.alpha, qq, -rr);
-    if (r2 < 0.0) r2 = 0.0;  // rounding, when the step removes the residual altogether
-    S.rho_known = 0;
-    S.iters += 1;
-    S.since_rel += 1;
-    if (!isfinite(r2)) {
-        S.phase = CG_NONFINITE;
-        return;
-    }
-    S.rho_old = rr;
     S.rho = r2;
-    S.beta = rr > 0.0 ? r2 / rr : 0.0;
+    S.beta = S.rho_old > 0.0 ? r2 / S.rho_old : 0.0;
     S.live = 1;
     if (r2 > S.max_rho) S.max_rho = r2;
     if (r2 <= S.stop2 || S.iters >= S.max_iter) {
@@ -58,6 +90,7 @@ __device__ inline void fin_residual(CgState &S, double r2, int mode)
 {
     S.true_r2 = r2;
     if (mode == 2) return;
+    S.unsettled = 0;
     if (mode == 3 && isfinite(r2) && r2 <= S.stop2) {
         S.phase = CG_INNER_DONE;
         return;

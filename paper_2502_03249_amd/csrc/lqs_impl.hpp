@@ -75,6 +75,7 @@ struct CgState {
     int32_t max_iter;
     int32_t rho_known;  // rho was measured (init, FP64 residual), not predicted by the last step
     int32_t live;       // the last step's scalars are valid: its vector update is due
+    int32_t unsettled;  // the last step's |r|^2 could not be predicted: beta and the direction are still to come
     int32_t p_due;      // that update leaves p = r + beta p to the FP64 group that closes the round, or to the
                         // final check (cleared by the next step, or by a check of other right-hand sides)
 };

@@ -80,14 +80,21 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
     if (!block_sums_first<4>(v, red)) return;
     const double pq = v[0], qq = v[1], rr = S.rho_known ? S.rho : v[2];
     // lane i < nshift advances shift i; lane 0 the base
-    const bool ok = phase == CG_RUNNING && isfinite(pq) && pq > 0.0;
-    const double a_prev = S.alpha, b_prev = S.beta, a = ok ? rr / pq : 0.0;
-    double r2 = fma(a * a, qq, -rr);
-    if (r2 < 0.0) r2 = 0.0;
-    const double b = rr > 0.0 ? r2 / rr : 0.0;
+    const bool settle = S.unsettled != 0;  // the last step's directions, with its measured |r|^2
+    const bool ok = phase == CG_RUNNING && (settle || (isfinite(pq) && pq > 0.0));
+    const double a_prev = S.alpha, b_prev = S.beta, a = ok && !settle ? rr / pq : 0.0;
+    const double r2 = settle ? rr : fma(a * a, qq, -rr), r2_old = settle ? S.rho_old : rr;
+    const double b = r2_old > 0.0 ? r2 / r2_old : 0.0;
     const bool finite = isfinite(r2);
+    const bool lost = !settle && prediction_lost(r2, rr, S.stop2) && S.iters + 1 < S.max_iter;
     T.xupd = 0;
-    if (mine && ok && finite && T.active) {
+    if (mine && ok && finite && T.active && settle) {
+        const double ratio = T.zeta / T.zeta_prev;
+        T.alpha = 0.0;
+        T.beta = b * ratio * ratio;
+        T.xupd = 1;
+        if (T.zeta * T.zeta * r2 <= S.stop2) T.active = 0;
+    } else if (mine && ok && finite && T.active) {
         const double z = T.zeta, zp = T.zeta_prev;
         const double den = zp * a_prev * (1.0 + a * T.sigma) + a * b_prev * (zp - z);
         const double zn = z * zp * a_prev / den, ratio = zn / z;
@@ -97,7 +104,7 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
         T.zeta = zn;
         T.iters += 1;
         T.xupd = 1;
-        if (zn * zn * r2 <= S.stop2) T.active = 0;
+        if (!lost && zn * zn * r2 <= S.stop2) T.active = 0;
     }
     if (mine) sh[i] = T;
     const bool any = __any(mine && T.active);
@@ -119,18 +126,29 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
         S.phase = isfinite(pq) ? CG_BREAKDOWN : CG_NONFINITE;
         return;
     }
-    S.rho_known = 0;
-    S.iters += 1;
-    S.since_rel += 1;
+    S.unsettled = 0;
+    if (!settle) {
+        S.rho_known = 0;
+        S.iters += 1;
+        S.since_rel += 1;
+    }
     if (!finite) {
         S.phase = CG_NONFINITE;
         return;
     }
-    S.alpha = a;
+    if (!settle) {
+        S.alpha = a;
+        S.rho_old = rr;
+    }
+    S.live = settle ? 2 : 1;
+    if (lost) {
+        S.unsettled = 1;
+        S.p_due = 1;
+        if (S.rel_interval > 0 && S.since_rel >= S.rel_interval) S.reliable_pending = 1;
+        return;
+    }
     S.beta = b;
-    S.rho_old = rr;
     S.rho = r2;
-    S.live = 1;
     if (r2 > S.max_rho) S.max_rho = r2;
     if ((r2 <= S.stop2 && !any) || S.iters >= S.max_iter) {
         S.phase = CG_INNER_DONE;
@@ -222,8 +240,10 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, c
     // the first site's vectors and the records in one memory round trip
     load_base(c0 < vh ? c0 : vh - 1);
     const int phase = base->phase;
-    const bool p_due = base->p_due != 0, on = DIRS ? p_due && phase == CG_RUNNING : base->live != 0;
-    const double a = base->alpha, b = base->beta;
+    const int live = base->live;  // 2: x and r stay as they are (alpha 0)
+    const bool p_due = base->p_due != 0,
+               on = DIRS ? p_due && phase == CG_RUNNING && !base->unsettled : live != 0;
+    const double a = live == 2 ? 0.0 : base->alpha, b = base->beta;
     const bool pdir = DIRS || !p_due;
     if (threadIdx.x < 64) {
         const int i = threadIdx.x;
@@ -474,7 +494,7 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
     } ev;
     for (hipEvent_t &e : ev.e) LQS_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     int64_t enqueued = 0;
-    const int64_t cap = (int64_t)prm.max_iter + 64;
+    const int64_t cap = 2 * (int64_t)prm.max_iter + 64;
     for (int round = 0;; ++round) {
         for (int i = 0; i < 8; ++i) {
             const int group = mixed && (i & 3) == 3;

@@ -289,7 +289,8 @@ __global__ void __launch_bounds__(BS) small_cg_kernel(const SmallLat *lats, CgSt
                     r[s] = {fused(-alpha, q[s].re, r[s].re), fused(-alpha, q[s].im, r[s].im)};
                     if (!sc.p_due) p[s] = {fused(beta, p[s].re, r[s].re), fused(beta, p[s].im, r[s].im)};
                 }
-                if (__builtin_expect(!sc.p_due, 1)) continue;
+                // (an unsettled direction is the next trip's, unless an FP64 residual is due anyway)
+                if (__builtin_expect(!sc.p_due, 1) || (sc.unsettled && !sc.reliable_pending)) continue;
             }
         }
         const bool due = run && sc.live;
@@ -419,7 +420,8 @@ void small_solve(Ctx &ctx, const std::vector<PersistentProblem> &probs, const lq
     LQS_HIP(hipMemcpyAsync(d, h, o_clk, hipMemcpyHostToDevice, s));
     CgState *st = (CgState *)(d + o_st);
     unsigned long long *dclk = (unsigned long long *)(d + o_clk);
-    const int trips = prm.max_iter + 8;
+    // every iteration may be followed by one that only settles its direction
+    const int trips = (int)std::min<int64_t>(2 * (int64_t)prm.max_iter + 8, INT32_MAX);
     try {
         if (prec == F64 && recon == 18) launch_small_pr<F64, 18>(vmax, n, (const SmallLat *)d, st, trips, dclk, s);
         else if (prec == F64) launch_small_pr<F64, 12>(vmax, n, (const SmallLat *)d, st, trips, dclk, s);
