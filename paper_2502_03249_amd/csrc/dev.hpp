@@ -774,6 +774,16 @@ template <int N> __device__ __forceinline__ void block_sums(double (&v)[N], doub
         v[0] = t;
     }
 }
+// Sum of v over the lanes of a row of 16 with the same lane & 3, the same bits in
+// each of them: the rotation by 8 pairs lane l with l ^ 8, and either adds the
+// same two numbers, so the rotation by 4 finds the same two pair sums in all
+// four.  (By 4 first, neighbouring quads would pair different numbers.)
+// Rows: by<N>(v) rotates v by N lanes.
+template <typename V, typename Rows> __host__ __device__ __forceinline__ V row_class_sum(V v, Rows)
+{
+    v = v + Rows::template by<8>(v);
+    return v + Rows::template by<4>(v);
+}
 // `v` of one lane, in every lane
 __device__ __forceinline__ double lane_value(double v, int lane)
 {

@@ -147,26 +147,29 @@ static size_t small_lds_bytes(int vh, int prec)
     return (size_t)vh * std::max((3 + SCAT) * (prec == F64 ? 16 : 8), 2 * 48);
 }
 
-// Sum of v over the threads of the block with the same tid & 3, in every thread
-// (red: four rows per wave).  Fixed order.
+struct DppRows {
+    template <int N> static __device__ __forceinline__ double by(double v) { return dpp<0x120 + N>(v); }  // row_ror
+};
+
+// Sum of v over the threads of the block with the same tid & 3, the same bits in
+// every one of them: the loop's control flow and its barriers hang on them (red:
+// four rows per wave).
 template <int NW> __device__ __forceinline__ double quad_class_sum(double v, double (*red)[4])
 {
-    constexpr int ROR4 = 0x124, ROR8 = 0x128;  // rotations of the rows of 16 lanes
     const int tid = threadIdx.x;
-    v += dpp<ROR4>(v);
-    v += dpp<ROR8>(v);
+    v = row_class_sum(v, DppRows());
     if ((tid & 15) < 4) red[tid >> 4][tid & 3] = v;
     __syncthreads();
     const int lane = tid & 63;
     double t = (&red[0][0])[lane];
 #pragma unroll
     for (int k = 1; k < NW / 4; ++k) t += (&red[0][0])[64 * k + lane];
-    t += dpp<ROR4>(t);
-    t += dpp<ROR8>(t);
+    t = row_class_sum(t, DppRows());
     t += __shfl_xor(t, 16, 64);
     t += __shfl_xor(t, 32, 64);
     return t;
 }
+
 template <int P, int R, int BS, int S>
 __global__ void __launch_bounds__(BS) small_cg_kernel(const SmallLat *lats, CgState *states, int max_trips,
                                                       unsigned long long *clk)
