@@ -10,7 +10,8 @@
 // beta and the stop decision need the norm of the residual before kernel 4 has
 // formed it.  It is predicted from the dots at hand,
 //   |r - alpha q|^2 = |r|^2 - 2 alpha <r,q> + alpha^2 <q,q> = alpha^2 <q,q> - |r|^2
-// (<r,q> = <p,q> as the directions are conjugate, alpha = |r|^2 / <p,q>), and
+// (<r,q> = <p,q> as the directions are conjugate, alpha = |r|^2 / <p,q>; with
+// directions in 16 bits corrected for what they are not, see cg_step.hpp), and
 // |r|^2 of the next step is the one kernel 4 sums from the residual it stores,
 // so the prediction's rounding does not accumulate: the predict-and-recompute
 // conjugate gradient of Chen and Carson (SIAM J. Matrix Anal. Appl. 2020).
@@ -56,6 +57,16 @@ __device__ __forceinline__ V3<typename RealOf<PA>::type> direction_of(const V3<t
         o.c[a].im = fused(beta, pv.c[a].im, rv.c[a].im);
     }
     return o;
+}
+
+// Re <a,b> of a site, summed in double
+template <typename T> __device__ __forceinline__ double re_dot(const V3<T> &a, const V3<T> &b)
+{
+    double s = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        s += (double)a.c[c].re * (double)b.c[c].re + (double)a.c[c].im * (double)b.c[c].im;
+    return s;
 }
 
 // ---------------------------------------------------------------------------
@@ -139,19 +150,20 @@ normal_dot_kernel(Geom g, LinkRef L, const char *t, const char *p, char *q, int6
 // one round trip, further ones four at a time, and one wave alone adds the rows
 // (64^3 x 16, 8192 pairs: 7.1 -> 5.5 us; 24^4 solves 1 to 2.6 % faster).
 
+template <bool CONJ>
 __global__ void __launch_bounds__(1024) step_finalize_kernel(CgState *st, const double *partials,
                                                             const double *rr_partials, int max_blocks, int nblocks,
                                                             int nr_blocks, int last, int32_t *host_phase)
 {
     const int r = blockIdx.x;
     const double *pp = partials + (int64_t)r * max_blocks;
-    const DotShare first = first_dots(pp, rr_partials + (int64_t)r * max_blocks, nblocks, nr_blocks);
+    const DotShare first = first_dots<CONJ>(pp, rr_partials + (int64_t)r * max_blocks, nblocks, nr_blocks);
     CgState S = st[r];
     double v[4];
     add_dots(pp, nblocks, nr_blocks, first, v);
     __shared__ double red[16][4];
     if (!block_sums_first<4>(v, red) || threadIdx.x != 0) return;
-    if (S.phase == CG_RUNNING) cg_step_scalars(S, v[0], v[1], v[2], last);
+    if (S.phase == CG_RUNNING) cg_step_scalars(S, v[0], v[1], v[2], v[3], last);
     else S.live = 0;
     st[r] = S;
     publish(host_phase, r, S.phase);
@@ -201,7 +213,8 @@ __global__ void __launch_bounds__(BLAS_BLOCK) step_kernel(int vh, char *x, char 
         issue_here(xraw);
     }
     if (!live) return;
-    double local = 0.0;
+    constexpr bool CONJ = corrects_prediction(PI);
+    double sums[2] = {0.0, 0.0};  // |r|^2; <q,p> of the new p
     auto site = [&](int cb, const V3<T> &qv, const V3<T> &pv, V3<T> rv, V3<T> xv) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -209,11 +222,14 @@ __global__ void __launch_bounds__(BLAS_BLOCK) step_kernel(int vh, char *x, char 
             xv.c[a].im = fused(alpha, pv.c[a].im, xv.c[a].im);
             rv.c[a].re = fused(-alpha, qv.c[a].re, rv.c[a].re);
             rv.c[a].im = fused(-alpha, qv.c[a].im, rv.c[a].im);
-            local += (double)rv.c[a].re * (double)rv.c[a].re + (double)rv.c[a].im * (double)rv.c[a].im;
+            sums[0] += (double)rv.c[a].re * (double)rv.c[a].re + (double)rv.c[a].im * (double)rv.c[a].im;
         }
         SpinorIO<PA>::store(x, vh, cb, xv);
         SpinorIO<PA>::store(r, vh, cb, rv);
-        if (pdir) SpinorIO<PI>::store(p, vh, cb, vcast<TI>(direction_of<PA>(rv, pv, beta)));
+        if (!pdir) return;
+        const V3<T> pn = direction_of<PA>(rv, pv, beta);
+        SpinorIO<PI>::store(p, vh, cb, vcast<TI>(pn));
+        if (CONJ) sums[1] += re_dot(qv, pn);
     };
     if (EARLY) {
         if (c0 < vh)
@@ -224,15 +240,23 @@ __global__ void __launch_bounds__(BLAS_BLOCK) step_kernel(int vh, char *x, char 
             site(cb, vcast<T>(SpinorIO<PI>::load(q, vh, cb)), vcast<T>(SpinorIO<PI>::load(p, vh, cb)),
                  SpinorIO<PA>::load(r, vh, cb), SpinorIO<PA>::load(x, vh, cb));
     }
-    const double s = block_sum(local);
-    if (threadIdx.x == 0) rr_partials[(int64_t)rhs * max_blocks + blockIdx.x] = s;
+    rr_partials += (int64_t)rhs * max_blocks + blockIdx.x;
+    if constexpr (CONJ) {
+        __shared__ double red[BLAS_BLOCK / 64][2];
+        block_sums<2>(sums, red);
+        if (threadIdx.x < 2) rr_partials[threadIdx.x * PE_PARTIALS] = sums[0];
+    } else {
+        const double s = block_sum(sums[0]);
+        if (threadIdx.x == 0) *rr_partials = s;
+    }
 }
 
 // FP64 group, last: the direction update the step kernel left out, with the
 // residual and beta the group has set.
 template <int PA, int PI>
-__global__ void __launch_bounds__(BLAS_BLOCK) pdir_kernel(int vh, const char *r, char *p, int64_t sa, int64_t si,
-                                                          const CgState *st, int32_t *host_phase)
+__global__ void __launch_bounds__(BLAS_BLOCK) pdir_kernel(int vh, const char *r, char *p, const char *q, int64_t sa,
+                                                          int64_t si, const CgState *st, double *rr_partials,
+                                                          int max_blocks, int32_t *host_phase)
 {
     typedef typename RealOf<PA>::type T;
     typedef typename RealOf<PI>::type TI;
@@ -243,10 +267,16 @@ __global__ void __launch_bounds__(BLAS_BLOCK) pdir_kernel(int vh, const char *r,
     const T beta = (T)S.beta;
     r += rhs * sa;
     p += rhs * si;
-    for (int cb = blockIdx.x * blockDim.x + threadIdx.x; cb < vh; cb += gridDim.x * blockDim.x)
-        SpinorIO<PI>::store(p, vh, cb,
-                            vcast<TI>(direction_of<PA>(SpinorIO<PA>::load(r, vh, cb),
-                                                       vcast<T>(SpinorIO<PI>::load(p, vh, cb)), beta)));
+    q += rhs * si;
+    double pe = 0.0;
+    for (int cb = blockIdx.x * blockDim.x + threadIdx.x; cb < vh; cb += gridDim.x * blockDim.x) {
+        const V3<T> pn = direction_of<PA>(SpinorIO<PA>::load(r, vh, cb), vcast<T>(SpinorIO<PI>::load(p, vh, cb)), beta);
+        SpinorIO<PI>::store(p, vh, cb, vcast<TI>(pn));
+        if (corrects_prediction(PI)) pe += re_dot(vcast<T>(SpinorIO<PI>::load(q, vh, cb)), pn);
+    }
+    if (!corrects_prediction(PI)) return;
+    const double s = block_sum(pe);
+    if (threadIdx.x == 0) rr_partials[(int64_t)rhs * max_blocks + PE_PARTIALS + blockIdx.x] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -443,12 +473,12 @@ void cg_fill_rates(lqs_cg_stats &o, const Gauge &gauge, int prec, int recon, int
 }
 
 // Doubles of partials per right-hand side: one per block of the init (at most
-// 1024) and residual kernels (64 threads or more), two per block of the normal
-// kernel.
+// 1024) and residual kernels (64 threads or more), two per block of the step
+// kernel (at most 1024) and of the normal kernel.
 int cg_partials_needed(const Gauge &gauge, int normal_block)
 {
     const int64_t dots = 2 * ((gauge.vh + normal_block - 1) / normal_block), one = (gauge.vh + 63) / 64;
-    return (int)std::max<int64_t>(1024, std::max(dots, one));
+    return (int)std::max<int64_t>(2 * PE_PARTIALS, std::max(dots, one));
 }
 
 template <int P, int R>
@@ -514,7 +544,7 @@ static void launch_step(const Gauge &gauge, const CgVectors &v, int nd_blocks, i
     const int vh = (int)gauge.vh;
     const int64_t sa = field_bytes(gauge.g, PA, 1), si = field_bytes(gauge.g, PI, 1);
     const dim3 grid(blas_blocks(vh, v.nrhs), v.nrhs);
-    hipLaunchKernelGGL(step_finalize_kernel, dim3(v.nrhs), dim3(1024), 0, s, v.state, (const double *)v.partials,
+    hipLaunchKernelGGL(step_finalize_kernel<corrects_prediction(PI)>, dim3(v.nrhs), dim3(1024), 0, s, v.state, (const double *)v.partials,
                        (const double *)v.partials2, v.max_blocks, nd_blocks, (int)grid.x, last, host_phase);
     const bool early = v.nrhs == 1 && vh <= (int)grid.x * blas_block(vh, v.nrhs);
 #define LQS_STEP(EARLY)                                                                                           \
@@ -534,7 +564,8 @@ static void launch_pdir(const Gauge &gauge, const CgVectors &v, int32_t *host_ph
     const int vh = (int)gauge.vh;
     const int64_t sa = field_bytes(gauge.g, PA, 1), si = field_bytes(gauge.g, PI, 1);
     hipLaunchKernelGGL((pdir_kernel<PA, PI>), dim3(blas_blocks(vh, v.nrhs), v.nrhs), dim3(blas_block(vh, v.nrhs)), 0, s, vh,
-                       (const char *)v.r, (char *)v.p, sa, si, (const CgState *)v.state, host_phase);
+                       (const char *)v.r, (char *)v.p, (const char *)v.q, sa, si, (const CgState *)v.state, v.partials2,
+                       v.max_blocks, host_phase);
     LQS_HIP(hipGetLastError());
 }
 
@@ -753,10 +784,11 @@ static void cg_initial_states(const lqs_cg_params &prm, int nrhs, const double *
 
 // Device workspace that a problem is charged with against the preallocated
 // region of the allocation-free solve (two reduction buffers of one double per
-// 64 sites).  The buffers of a solve whose normal kernel runs in blocks of 64 or
-// 128 threads (two sums a block) may need more, at most NOALLOC_SLACK_BYTES,
-// which the region holds in addition (a problem is charged at least 144 bytes a
-// site and side, so its sides have fewer than 2^19 sites together).
+// 64 sites, 1024 at least).  The buffers hold up to twice that (two sums a block
+// in the step kernel, and in the normal kernel in blocks of 64 or 128 threads):
+// at most NOALLOC_SLACK_BYTES more, which the region holds in addition (a problem
+// is charged at least 144 bytes a site and side, so its at most 16 sides have
+// fewer than 2^19 sites together).
 size_t cg_workspace_bytes(const Gauge &gauge, const lqs_cg_params &prm, int nrhs)
 {
     auto up = [](size_t b) { return (b + 255) & ~size_t(255); };

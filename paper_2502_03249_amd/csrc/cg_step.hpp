@@ -6,6 +6,13 @@
 
 namespace lqs {
 
+// |r - alpha q|^2 of a step; beta formed its direction (0: r alone, pe unused).
+__device__ inline double predicted_r2(double alpha, double beta, double qq, double rr, double pe)
+{
+    const double r2 = fma(alpha * alpha, qq, -rr);
+    return beta != 0.0 ? fma(2.0 * alpha * beta, pe, r2) : r2;
+}
+
 // A predicted |r|^2 that says nothing.  It is the difference of two numbers of
 // about |r|^2 before the step (rr), each a sum that is good to a few ulp: below
 // 16 ulp of rr it is their rounding, unless the target lies above that too.  It
@@ -18,15 +25,24 @@ __device__ inline bool prediction_lost(double r2, double rr, double stop2)
     return r2 < 0.0 || (r2 <= noise && noise > stop2);
 }
 
+// The prediction takes <r,q> for <p,q>.  With the directions in 16 bits the two
+// differ: <p,q> = <r,q> + beta <p_old,q>, and consecutive directions are
+// conjugate only as far as the roundings of p and q, and the jump of r in a
+// reliable update, leave them so.  <p_old,q> = <q_old,p> is summed where p is
+// formed, which has both at hand.  (Left out, the iterations stay the same and x
+// ends 6 to 25 % further from the solution at the same residual: error over
+// residual 3.8 on 16^4 with the norm measured as with this, 4.9 without.)
+constexpr bool corrects_prediction(int prec) { return prec == F16; }
+
 // Scalars of one iteration from its dots (rr: |r|^2 as the last step summed it,
-// unused while S.rho holds a measured one).  `live`: this iteration's update is
+// unused while S.rho holds a measured one; pe: <p_old,q>, or 0).  `live`: this iteration's update is
 // due; `p_due`: the direction update is left to the FP64 group that closes the
 // round (`last`: the group follows this iteration).  After a step whose
 // prediction is lost x and r are advanced and the direction is not; the next
 // iteration forms it with the |r|^2 that the step has summed (`unsettled`; its
 // own products of the old direction are not used).
 
-__device__ inline void cg_step_scalars(CgState &S, double pq, double qq, double rr, int last)
+__device__ inline void cg_step_scalars(CgState &S, double pq, double qq, double rr, double pe, int last)
 {
     if (S.rho_known) rr = S.rho;
     S.live = 0;
@@ -50,7 +66,7 @@ __device__ inline void cg_step_scalars(CgState &S, double pq, double qq, double 
             return;
         }
         S.alpha = rr / pq;
-        r2 = fma(S.alpha * S.alpha, qq, -rr);
+        r2 = predicted_r2(S.alpha, S.beta, qq, rr, pe);
         S.rho_known = 0;
         S.iters += 1;
         S.since_rel += 1;
@@ -128,30 +144,37 @@ __device__ inline void fin_residual(CgState &S, double r2, int mode)
 }
 
 // A thread's share (of 1024 threads) of the block partials of <p,q> and <q,q>
-// (pairs, nblocks >= 1) and of |r|^2 (1 <= nr_blocks <= 1024).  `first` holds what is
+// (pairs, nblocks >= 1), of |r|^2 (1 <= nr_blocks <= 1024) and, with CONJ, of
+// <p_old,q> (PE_PARTIALS after those).  `first` holds what is
 // requested before anything is waited for, so that a record loaded between the
 // two calls shares the round trip.
 struct DotShare {
     double2 pq;
-    double rr;
+    double rr, pe;
 };
+constexpr int PE_PARTIALS = 1024;
+template <bool CONJ>
 __device__ __forceinline__ DotShare first_dots(const double *partials, const double *rr_partials, int nblocks,
                                                int nr_blocks)
 {
-    const int i = threadIdx.x;
-    return {((const double2 *)partials)[i < nblocks ? i : nblocks - 1], rr_partials[i < nr_blocks ? i : nr_blocks - 1]};
+    const int i = threadIdx.x, ir = i < nr_blocks ? i : nr_blocks - 1;
+    return {((const double2 *)partials)[i < nblocks ? i : nblocks - 1], rr_partials[ir],
+            CONJ ? rr_partials[PE_PARTIALS + ir] : 0.0};
 }
 __device__ __forceinline__ void add_dots(const double *partials, int nblocks, int nr_blocks, const DotShare &first,
                                          double (&v)[4])
 {
     const double2 *pp = (const double2 *)partials;
     const int i0 = threadIdx.x;
-    v[0] = v[1] = v[2] = v[3] = 0.0;  // (v[3]: padding to a power of two)
+    v[0] = v[1] = v[2] = v[3] = 0.0;
     if (i0 < nblocks) {
         v[0] = first.pq.x;
         v[1] = first.pq.y;
     }
-    if (i0 < nr_blocks) v[2] = first.rr;
+    if (i0 < nr_blocks) {
+        v[2] = first.rr;
+        v[3] = first.pe;
+    }
     for (int b = 1024; b < nblocks; b += 4 * 1024) {
         double2 a[4];
 #pragma unroll

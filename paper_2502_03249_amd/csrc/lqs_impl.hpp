@@ -253,7 +253,7 @@ struct CgVectors {
     void *t64;              // FP64 odd scratch (residual hop)
     CgState *state;         // nrhs records
     double *partials;       // nrhs * max_blocks (normal kernel, residual, init)
-    double *partials2;      // nrhs * max_blocks (|r|^2 of the step kernel)
+    double *partials2;      // nrhs * max_blocks (|r|^2 and <p_old,q> of the step kernel)
     int max_blocks;         // doubles of partials per right-hand side
     LaunchShape hop_shape, normal_shape;
 };

@@ -63,12 +63,13 @@ struct ShiftPtrs {
 
 // Every scalar of one iteration from the base's <p,q>, <q,q> (partials) and
 // |r|^2 as the last step summed it (rr_partials, at most 1024; unused while
-// rho holds a measured one).  `last`: the FP64 group follows this iteration.
+// rho holds a measured one; CONJ: <p_old,q> after them).  `last`: the FP64 group follows this iteration.
+template <bool CONJ>
 __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh, int nshift, const double *partials,
                                                    const double *rr_partials, int nblocks, int nr_blocks, int last,
                                                    int32_t *host_phase)
 {
-    const DotShare first = first_dots(partials, rr_partials, nblocks, nr_blocks);
+    const DotShare first = first_dots<CONJ>(partials, rr_partials, nblocks, nr_blocks);
     CgState S = *base;
     const int phase = S.phase, i = threadIdx.x;
     const bool mine = i < nshift;
@@ -83,7 +84,7 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
     const bool settle = S.unsettled != 0;  // the last step's directions, with its measured |r|^2
     const bool ok = phase == CG_RUNNING && (settle || (isfinite(pq) && pq > 0.0));
     const double a_prev = S.alpha, b_prev = S.beta, a = ok && !settle ? rr / pq : 0.0;
-    const double r2 = settle ? rr : fma(a * a, qq, -rr), r2_old = settle ? S.rho_old : rr;
+    const double r2 = settle ? rr : predicted_r2(a, S.beta, qq, rr, v[3]), r2_old = settle ? S.rho_old : rr;
     const double b = r2_old > 0.0 ? r2 / r2_old : 0.0;
     const bool finite = isfinite(r2);
     const bool lost = !settle && prediction_lost(r2, rr, S.stop2) && S.iters + 1 < S.max_iter;
@@ -219,6 +220,7 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, c
     typedef typename RealOf<PR>::type TR;
     typedef typename SpinorIO<PI>::Raw RawI;
     typedef typename SpinorIO<PR>::Raw RawR;
+    constexpr bool CONJ = corrects_prediction(PI);
     struct Due {
         char *x, *p;
         double alpha, beta, zeta;
@@ -232,8 +234,8 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, c
     auto load_base = [&](int cb) {
         praw = SpinorIO<PI>::load_raw(p0, vh, cb);
         rraw = SpinorIO<PR>::load_raw(r, vh, cb);
+        if (!DIRS || CONJ) qraw = SpinorIO<PI>::load_raw(q, vh, cb);
         if (!DIRS) {
-            qraw = SpinorIO<PI>::load_raw(q, vh, cb);
             xraw = SpinorIO<PR>::load_raw(x0, vh, cb);
         }
     };
@@ -260,15 +262,13 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, c
     }
     issue_here(praw);
     issue_here(rraw);
-    if (!DIRS) {
-        issue_here(qraw);
-        issue_here(xraw);
-    }
+    if (!DIRS || CONJ) issue_here(qraw);
+    if (!DIRS) issue_here(xraw);
     if (DIRS && blockIdx.x == 0 && threadIdx.x == 0) publish(host_phase, 0, phase);
     if (!on) return;
     __syncthreads();
     const int n = ndue;
-    double local = 0.0;
+    double sums[2] = {0.0, 0.0};  // |r|^2; <q,p_0> of the new p_0
     for (int cb = c0; cb < vh; cb += gridDim.x * blockDim.x) {
         if (cb != c0) load_base(cb);
         RawI pnext{};
@@ -280,8 +280,8 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, c
         if (n > 0) load_shift(0);
         V3<double> pv = vcast<double>(SpinorIO<PI>::decode(praw));
         V3<double> rv = vcast<double>(SpinorIO<PR>::decode(rraw));
+        const V3<double> qv = DIRS && !CONJ ? vzero<double>() : vcast<double>(SpinorIO<PI>::decode(qraw));
         if (!DIRS) {
-            const V3<double> qv = vcast<double>(SpinorIO<PI>::decode(qraw));
             V3<double> xv = vcast<double>(SpinorIO<PR>::decode(xraw));
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
@@ -295,13 +295,14 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, c
             SpinorIO<PR>::store(r, vh, cb, rs);
             rv = vcast<double>(rs);  // the norm and the directions follow the stored residual
 #pragma unroll
-            for (int c = 0; c < 3; ++c) local += rv.c[c].re * rv.c[c].re + rv.c[c].im * rv.c[c].im;
+            for (int c = 0; c < 3; ++c) sums[0] += rv.c[c].re * rv.c[c].re + rv.c[c].im * rv.c[c].im;
         }
         if (pdir) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 pv.c[c].re = rv.c[c].re + b * pv.c[c].re;
                 pv.c[c].im = rv.c[c].im + b * pv.c[c].im;
+                if (CONJ) sums[1] += qv.c[c].re * pv.c[c].re + qv.c[c].im * pv.c[c].im;
             }
             SpinorIO<PI>::store(p0, vh, cb, vcast<TI>(pv));
         }
@@ -328,9 +329,16 @@ __global__ void __launch_bounds__(MS_BLOCK) ms_step(int vh, char *x0, char *r, c
             SpinorIO<PI>::store(d.p, vh, cb, vcast<TI>(pi));
         }
     }
-    if (DIRS) return;
-    const double s = block_sum(local);
-    if (threadIdx.x == 0) rr_partials[blockIdx.x] = s;
+    if constexpr (CONJ) {
+        __shared__ double red[MS_BLOCK / 64][2];
+        block_sums<2>(sums, red);
+        // (threads 0 and 1 hold a sum each; the group's |r|^2 is measured elsewhere)
+        if (threadIdx.x < 2 && (!DIRS || threadIdx.x == 1))
+            rr_partials[threadIdx.x * PE_PARTIALS + blockIdx.x] = sums[0];
+    } else if (!DIRS) {
+        const double s = block_sum(sums[0]);
+        if (threadIdx.x == 0) rr_partials[blockIdx.x] = s;
+    }
 }
 
 // x_0 = x_i = 0, r = p_0 = p_i = b, |b|^2 (of b in FP64)
@@ -418,7 +426,7 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
     const LaunchShape sh = default_hop_shape(g, PI, L, 1);
     v.max_blocks = cg_partials_needed(gauge, sh.block);
     v.partials = (double *)ctx.workspace("ms.partials", sizeof(double) * (size_t)v.max_blocks);
-    v.partials2 = (double *)ctx.workspace("ms.partials2", sizeof(double) * 1024);
+    v.partials2 = (double *)ctx.workspace("ms.partials2", sizeof(double) * 2 * PE_PARTIALS);
     v.state = (CgState *)ctx.workspace("ms.state", sizeof(CgState));
     ShiftPtrs hp{};
     std::vector<ShiftState> hsh(nshift);
@@ -481,6 +489,7 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
     // GPU does not idle between rounds; the kernels of a round queued after the
     // recurrence has ended return at once.
     const int nd_blocks = (vh + sh.block - 1) / sh.block;
+    const auto scalars = corrects_prediction(PI) ? ms_scalars<true> : ms_scalars<false>;
     CgState *hs1 = (CgState *)ctx.pinned("ms.host", sizeof(CgState) + sizeof(int32_t));
     int32_t *host_phase = (int32_t *)(hs1 + 1);
     *host_phase = CG_RUNNING;
@@ -501,7 +510,7 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
             int32_t *tell = i == 7 ? host_phase : nullptr;  // by the round's last kernel that settles the phase
             launch_hop_gated(g, L, PI, v.recon, 0, 1, 1, v.p, v.t, v.state, 1, sh, s);
             launch_normal_dot_shape(gauge, v, sh, s);
-            hipLaunchKernelGGL(ms_scalars, dim3(1), dim3(1024), 0, s, v.state, dsh, nshift, (const double *)v.partials,
+            hipLaunchKernelGGL(scalars, dim3(1), dim3(1024), 0, s, v.state, dsh, nshift, (const double *)v.partials,
                                (const double *)v.partials2, nd_blocks, blocks, group, mixed ? nullptr : tell);
             LQS_MS_PREC(hipLaunchKernelGGL((ms_step<P_I, P_R, false>), dim3(blocks), dim3(block), 0, s, vh, xr[base],
                                            (char *)v.r, (char *)v.p, (const char *)v.q, (const ShiftPtrs *)dp, nshift,

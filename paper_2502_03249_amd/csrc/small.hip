@@ -281,7 +281,7 @@ __global__ void __launch_bounds__(BS) small_cg_kernel(const SmallLat *lats, CgSt
             qq = quad_add(qq);
             rr = quad_add(rr);
             const double sum = quad_class_sum<NW>(mu == 0 ? pq : mu == 1 ? qq : rr, red[trip & 1]);
-            cg_step_scalars(sc, lane_value(sum, 0), lane_value(sum, 1), lane_value(sum, 2), 1);
+            cg_step_scalars(sc, lane_value(sum, 0), lane_value(sum, 1), lane_value(sum, 2), 0.0, 1);
             measure = !sc.live;
             if (__builtin_expect(sc.live, 1)) {
                 // ---- x += alpha p, r -= alpha q, p = r + beta p (left to the residual update when one is due)
