@@ -163,8 +163,10 @@ __global__ void __launch_bounds__(1024) step_finalize_kernel(CgState *st, const 
     add_dots(pp, nblocks, nr_blocks, first, v);
     __shared__ double red[16][4];
     if (!block_sums_first<4>(v, red) || threadIdx.x != 0) return;
-    if (S.phase == CG_RUNNING) cg_step_scalars(S, v[0], v[1], v[2], v[3], last);
-    else S.live = 0;
+    // (a step to settle: this iteration's products of the old direction are not used)
+    if (S.phase != CG_RUNNING) S.live = 0;
+    else if (S.unsettled) cg_settle(S, v[2], last);
+    else cg_step_scalars<CONJ>(S, v[0], v[1], v[2], v[3], last);
     st[r] = S;
     publish(host_phase, r, S.phase);
 }

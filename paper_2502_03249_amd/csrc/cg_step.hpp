@@ -6,25 +6,6 @@
 
 namespace lqs {
 
-// |r - alpha q|^2 of a step; beta formed its direction (0: r alone, pe unused).
-__device__ inline double predicted_r2(double alpha, double beta, double qq, double rr, double pe)
-{
-    const double r2 = fma(alpha * alpha, qq, -rr);
-    return beta != 0.0 ? fma(2.0 * alpha * beta, pe, r2) : r2;
-}
-
-// A predicted |r|^2 that says nothing.  It is the difference of two numbers of
-// about |r|^2 before the step (rr), each a sum that is good to a few ulp: below
-// 16 ulp of rr it is their rounding, unless the target lies above that too.  It
-// is negative by more where <r,q> = <p,q> no longer holds (directions in 16
-// bits that have lost their conjugacy).  Either way it neither ends a solve nor
-// gives a beta.
-__device__ inline bool prediction_lost(double r2, double rr, double stop2)
-{
-    const double noise = 16.0 * 2.220446049250313e-16 * rr;
-    return r2 < 0.0 || (r2 <= noise && noise > stop2);
-}
-
 // The prediction takes <r,q> for <p,q>.  With the directions in 16 bits the two
 // differ: <p,q> = <r,q> + beta <p_old,q>, and consecutive directions are
 // conjugate only as far as the roundings of p and q, and the jump of r in a
@@ -34,55 +15,29 @@ __device__ inline bool prediction_lost(double r2, double rr, double stop2)
 // residual 3.8 on 16^4 with the norm measured as with this, 4.9 without.)
 constexpr bool corrects_prediction(int prec) { return prec == F16; }
 
-// Scalars of one iteration from its dots (rr: |r|^2 as the last step summed it,
-// unused while S.rho holds a measured one; pe: <p_old,q>, or 0).  `live`: this iteration's update is
-// due; `p_due`: the direction update is left to the FP64 group that closes the
-// round (`last`: the group follows this iteration).  After a step whose
-// prediction is lost x and r are advanced and the direction is not; the next
-// iteration forms it with the |r|^2 that the step has summed (`unsettled`; its
-// own products of the old direction are not used).
-
-__device__ inline void cg_step_scalars(CgState &S, double pq, double qq, double rr, double pe, int last)
+// |r - alpha q|^2 of a step; beta formed its direction (0: r alone), pe = <p_old,q>.
+template <bool CONJ>
+__device__ __forceinline__ double predicted_r2(double alpha, double beta, double qq, double rr, double pe)
 {
-    if (S.rho_known) rr = S.rho;
-    S.live = 0;
-    S.p_due = 0;
-    double r2;
-    if (S.unsettled) {
-        S.unsettled = 0;
-        r2 = rr;
-        S.alpha = 0.0;
-        if (!isfinite(r2)) {
-            S.phase = CG_NONFINITE;
-            return;
-        }
-    } else {
-        if (!isfinite(pq)) {
-            S.phase = CG_NONFINITE;
-            return;
-        }
-        if (!(pq > 0.0)) {
-            S.phase = CG_BREAKDOWN;
-            return;
-        }
-        S.alpha = rr / pq;
-        r2 = predicted_r2(S.alpha, S.beta, qq, rr, pe);
-        S.rho_known = 0;
-        S.iters += 1;
-        S.since_rel += 1;
-        if (!isfinite(r2)) {
-            S.phase = CG_NONFINITE;
-            return;
-        }
-        S.rho_old = rr;
-        if (prediction_lost(r2, rr, S.stop2) && S.iters < S.max_iter) {
-            S.unsettled = 1;
-            S.live = 1;
-            S.p_due = 1;
-            if (S.rel_interval > 0 && S.since_rel >= S.rel_interval) S.reliable_pending = 1;
-            return;
-        }
-    }
+    const double r2 = fma(alpha * alpha, qq, -rr);
+    return CONJ && beta != 0.0 ? fma(2.0 * alpha * beta, pe, r2) : r2;
+}
+
+// A predicted |r|^2 that says nothing.  It is the difference of two numbers of
+// about |r|^2 before the step (rr), each a sum that is good to a few ulp: below
+// 16 ulp of rr it is their rounding, unless the target lies above that too.  It
+// is negative by more where <r,q> = <p,q> no longer holds.  Either way it neither
+// ends a solve nor gives a beta.
+__device__ __forceinline__ bool prediction_lost(double r2, double rr, double stop2)
+{
+    const double noise = 16.0 * 2.220446049250313e-16 * rr;
+    if (__builtin_expect(r2 > noise, 1)) return false;
+    return r2 < 0.0 || noise > stop2;
+}
+
+// The decisions that |r|^2 of a step leads to.
+__device__ __forceinline__ void cg_decide(CgState &S, double r2, int last)
+{
     S.rho = r2;
     S.beta = S.rho_old > 0.0 ? r2 / S.rho_old : 0.0;
     S.live = 1;
@@ -95,6 +50,58 @@ __device__ inline void cg_step_scalars(CgState &S, double pq, double qq, double 
     }
     if (S.rel_interval > 0 && (S.since_rel >= S.rel_interval || r2 < S.delta2 * S.max_rho)) S.reliable_pending = 1;
     if (last && S.reliable_pending) S.p_due = 1;
+}
+
+// Settles a step whose prediction was lost with the |r|^2 it left: the direction
+// is due, x and r have their updates (alpha 0).
+__device__ __forceinline__ void cg_settle(CgState &S, double rr, int last)
+{
+    S.unsettled = 0;
+    S.live = 0;
+    S.p_due = 0;
+    S.alpha = 0.0;
+    if (isfinite(rr)) cg_decide(S, rr, last);
+    else S.phase = CG_NONFINITE;
+}
+
+// Scalars of one iteration from its dots (rr: |r|^2 as the last step summed it,
+// unused while S.rho holds a measured one; pe with CONJ: <p_old,q>).  `live`:
+// this iteration's update is due; `p_due`: the direction update is left to the
+// FP64 group that closes the round (`last`: the group follows this iteration).
+// Where the prediction is lost (`unsettled`) x and r are advanced and the
+// direction is not: |r|^2 has to be summed first.
+template <bool CONJ>
+__device__ __forceinline__ void cg_step_scalars(CgState &S, double pq, double qq, double rr, double pe, int last)
+{
+    if (S.rho_known) rr = S.rho;
+    S.live = 0;
+    S.p_due = 0;
+    if (!isfinite(pq)) {
+        S.phase = CG_NONFINITE;
+        return;
+    }
+    if (!(pq > 0.0)) {
+        S.phase = CG_BREAKDOWN;
+        return;
+    }
+    S.alpha = rr / pq;
+    const double r2 = predicted_r2<CONJ>(S.alpha, S.beta, qq, rr, pe);
+    S.rho_known = 0;
+    S.iters += 1;
+    S.since_rel += 1;
+    if (!isfinite(r2)) {
+        S.phase = CG_NONFINITE;
+        return;
+    }
+    S.rho_old = rr;
+    if (prediction_lost(r2, rr, S.stop2) && S.iters < S.max_iter) {
+        S.unsettled = 1;
+        S.live = 1;
+        S.p_due = 1;
+        if (S.rel_interval > 0 && S.since_rel >= S.rel_interval) S.reliable_pending = 1;
+        return;
+    }
+    cg_decide(S, r2, last);
 }
 
 // mode: 0 reliable update inside the iteration, 1 initial residual, 2 measure

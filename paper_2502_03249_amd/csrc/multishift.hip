@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
     const bool settle = S.unsettled != 0;  // the last step's directions, with its measured |r|^2
     const bool ok = phase == CG_RUNNING && (settle || (isfinite(pq) && pq > 0.0));
     const double a_prev = S.alpha, b_prev = S.beta, a = ok && !settle ? rr / pq : 0.0;
-    const double r2 = settle ? rr : predicted_r2(a, S.beta, qq, rr, v[3]), r2_old = settle ? S.rho_old : rr;
+    const double r2 = settle ? rr : predicted_r2<CONJ>(a, S.beta, qq, rr, v[3]), r2_old = settle ? S.rho_old : rr;
     const double b = r2_old > 0.0 ? r2 / r2_old : 0.0;
     const bool finite = isfinite(r2);
     const bool lost = !settle && prediction_lost(r2, rr, S.stop2) && S.iters + 1 < S.max_iter;

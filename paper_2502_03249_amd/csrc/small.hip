@@ -170,6 +170,16 @@ template <int NW> __device__ __forceinline__ double quad_class_sum(double v, dou
     return t;
 }
 
+// A record that every thread holds alike, in scalar registers: the links leave the
+// vector registers no room for it, and its branches need no lane masks.
+__device__ __forceinline__ CgState uniform_record(const CgState &s)
+{
+    struct Words { int w[sizeof(CgState) / 4]; } v = bitcast<Words>(s);
+#pragma unroll
+    for (int &w : v.w) w = __builtin_amdgcn_readfirstlane(w);
+    return bitcast<CgState>(v);
+}
+
 template <int P, int R, int BS, int S>
 __global__ void __launch_bounds__(BS) small_cg_kernel(const SmallLat *lats, CgState *states, int max_trips,
                                                       unsigned long long *clk)
@@ -230,7 +240,7 @@ __global__ void __launch_bounds__(BS) small_cg_kernel(const SmallLat *lats, CgSt
         st.phase = b2 == 0.0 ? CG_CONVERGED : (isfinite(b2) ? CG_RUNNING : CG_NONFINITE);
     }
     __syncthreads();
-    CgState sc = st;  // the scalars, the same in every thread
+    CgState sc = uniform_record(st);  // the scalars, the same in every thread
 
     for (int trip = 0;; ++trip) {
         // A solve that stops without its FP64 check (breakdown, non-finite
@@ -281,7 +291,8 @@ __global__ void __launch_bounds__(BS) small_cg_kernel(const SmallLat *lats, CgSt
             qq = quad_add(qq);
             rr = quad_add(rr);
             const double sum = quad_class_sum<NW>(mu == 0 ? pq : mu == 1 ? qq : rr, red[trip & 1]);
-            cg_step_scalars(sc, lane_value(sum, 0), lane_value(sum, 1), lane_value(sum, 2), 0.0, 1);
+            cg_step_scalars<false>(sc, lane_value(sum, 0), lane_value(sum, 1), lane_value(sum, 2), 0.0, 1);
+            sc = uniform_record(sc);
             measure = !sc.live;
             if (__builtin_expect(sc.live, 1)) {
                 // ---- x += alpha p, r -= alpha q, p = r + beta p (left to the residual update when one is due)
@@ -292,8 +303,23 @@ __global__ void __launch_bounds__(BS) small_cg_kernel(const SmallLat *lats, CgSt
                     r[s] = {fused(-alpha, q[s].re, r[s].re), fused(-alpha, q[s].im, r[s].im)};
                     if (!sc.p_due) p[s] = {fused(beta, p[s].re, r[s].re), fused(beta, p[s].im, r[s].im)};
                 }
-                // (an unsettled direction is the next trip's, unless an FP64 residual is due anyway)
-                if (__builtin_expect(!sc.p_due, 1) || (sc.unsettled && !sc.reliable_pending)) continue;
+                if (__builtin_expect(!sc.p_due, 1)) continue;
+                if (sc.unsettled && !sc.reliable_pending) {
+                    rr = 0.0;
+#pragma unroll
+                    for (int s = 0; s < S; ++s)
+                        if (own && q0 + s * NQ < vh)
+                            rr += (double)r[s].re * (double)r[s].re + (double)r[s].im * (double)r[s].im;
+                    cg_settle(sc, quad_class_sum<NW>(quad_add(rr), red[(trip + 1) & 1]), 1);
+                    sc = uniform_record(sc);
+                    __syncthreads();  // the sums have been read
+                    if (sc.live && !sc.p_due) {
+                        const T b = (T)sc.beta;
+#pragma unroll
+                        for (int s = 0; s < S; ++s) p[s] = {fused(b, p[s].re, r[s].re), fused(b, p[s].im, r[s].im)};
+                        continue;
+                    }
+                }
             }
         }
         const bool due = run && sc.live;
@@ -338,6 +364,7 @@ __global__ void __launch_bounds__(BS) small_cg_kernel(const SmallLat *lats, CgSt
             r2 = quad_class_sum<NW>(quad_add(r2), red[(trip + 1) & 1]);
             if (due) fin_residual(sc, r2, 0);
             else sc.true_r2 = r2;
+            sc = uniform_record(sc);
             if (due && sc.phase == CG_RUNNING) {
                 const T beta = (T)sc.beta;
 #pragma unroll
@@ -423,8 +450,7 @@ void small_solve(Ctx &ctx, const std::vector<PersistentProblem> &probs, const lq
     LQS_HIP(hipMemcpyAsync(d, h, o_clk, hipMemcpyHostToDevice, s));
     CgState *st = (CgState *)(d + o_st);
     unsigned long long *dclk = (unsigned long long *)(d + o_clk);
-    // every iteration may be followed by one that only settles its direction
-    const int trips = (int)std::min<int64_t>(2 * (int64_t)prm.max_iter + 8, INT32_MAX);
+    const int trips = prm.max_iter + 8;
     try {
         if (prec == F64 && recon == 18) launch_small_pr<F64, 18>(vmax, n, (const SmallLat *)d, st, trips, dclk, s);
         else if (prec == F64) launch_small_pr<F64, 12>(vmax, n, (const SmallLat *)d, st, trips, dclk, s);
