@@ -474,15 +474,6 @@ void cg_fill_rates(lqs_cg_stats &o, const Gauge &gauge, int prec, int recon, int
     o.gbytes_per_s = bytes * n / t * 1e-9;
 }
 
-// Doubles of partials per right-hand side: one per block of the init (at most
-// 1024) and residual kernels (64 threads or more), two per block of the step
-// kernel (at most 1024) and of the normal kernel.
-int cg_partials_needed(const Gauge &gauge, int normal_block)
-{
-    const int64_t dots = 2 * ((gauge.vh + normal_block - 1) / normal_block), one = (gauge.vh + 63) / 64;
-    return (int)std::max<int64_t>(2 * PE_PARTIALS, std::max(dots, one));
-}
-
 template <int P, int R>
 static void launch_normal_dot(const Gauge &gauge, const CgVectors &v, LaunchShape sh, hipStream_t s)
 {
@@ -885,7 +876,7 @@ struct CgRun {
         v.mass = pb.mass;
         (void)gauge().ref(v.prec, v.recon);  // format must exist
         cg_shapes(ctx, gauge(), v);
-        v.max_blocks = cg_partials_needed(gauge(), v.normal_shape.block);
+        v.max_blocks = cg_partials_needed(gauge().vh, v.normal_shape.block);
         sbytes = sizeof(CgState) * nrhs;
         // every size is checked before the first launch
         const size_t need = cg_workspace_bytes(gauge(), prm, nrhs);

@@ -159,7 +159,6 @@ struct DotShare {
     double2 pq;
     double rr, pe;
 };
-constexpr int PE_PARTIALS = 1024;
 template <bool CONJ>
 __device__ __forceinline__ DotShare first_dots(const double *partials, const double *rr_partials, int nblocks,
                                                int nr_blocks)

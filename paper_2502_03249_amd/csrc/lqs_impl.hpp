@@ -258,7 +258,17 @@ struct CgVectors {
     LaunchShape hop_shape, normal_shape;
 };
 void cg_init(Ctx &ctx, const Gauge &gauge, CgVectors &v, bool use_x0, hipStream_t s);
-int cg_partials_needed(const Gauge &gauge, int normal_block);
+constexpr int PE_PARTIALS = 1024;  // most blocks of the step kernel; its second sums stand this far on
+// Doubles of partials per right-hand side: one per block of the init (at most
+// 1024) and residual kernels (64 threads or more), two per block of the step
+// kernel and of the normal kernel.  Even: pairs are read as 16 bytes, and the
+// partials of the sides follow one another.
+inline int cg_partials_needed(int64_t vh, int normal_block)
+{
+    const int64_t dots = 2 * ((vh + normal_block - 1) / normal_block), one = (vh + 63) / 64;
+    const int64_t n = dots > one ? dots : one;
+    return (int)(n > 2 * PE_PARTIALS ? (n + 1) & ~int64_t(1) : 2 * PE_PARTIALS);
+}
 // gflops and gbytes_per_s of one right-hand side's stats from its iterations
 // and times (inner precision and link format of the iteration; nrhs
 // right-hand sides share the link reads)

@@ -424,7 +424,7 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
     v.t64 = mixed ? ctx.workspace("ms.t64", field_bytes(g, F64, 1)) : nullptr;
     const LinkRef L = gauge.ref(PI, v.recon);
     const LaunchShape sh = default_hop_shape(g, PI, L, 1);
-    v.max_blocks = cg_partials_needed(gauge, sh.block);
+    v.max_blocks = cg_partials_needed(gauge.vh, sh.block);
     v.partials = (double *)ctx.workspace("ms.partials", sizeof(double) * (size_t)v.max_blocks);
     v.partials2 = (double *)ctx.workspace("ms.partials2", sizeof(double) * 2 * PE_PARTIALS);
     v.state = (CgState *)ctx.workspace("ms.state", sizeof(CgState));

@@ -148,7 +148,7 @@ void autotune(Ctx &ctx, const Gauge &gauge, const char *kernel, int prec, int re
         v.t = in;
         v.p = aux;
         v.q = out;
-        v.max_blocks = cg_partials_needed(gauge, 64);  // the smallest candidate block
+        v.max_blocks = cg_partials_needed(gauge.vh, 64);  // the smallest candidate block
         v.partials = (double *)ctx.workspace("tune.partials", sizeof(double) * (size_t)v.max_blocks * nrhs);
         st = (CgState *)ctx.workspace("tune.state", sizeof(CgState) * nrhs);
         for (auto &S : tmpl) {

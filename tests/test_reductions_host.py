@@ -1,4 +1,4 @@
-"""Reductions whose result the control flow of a kernel hangs on, checked on the CPU: small
+"""What the reductions rest on, checked on the CPU (their bits and their buffers): small
 host programs compiled against the library's own headers.  Nothing runs on a GPU."""
 import os
 import shutil
@@ -11,7 +11,7 @@ HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
-@pytest.mark.parametrize("name", ["row_sum_check"])
+@pytest.mark.parametrize("name", ["row_sum_check", "partials_check"])
 def test_host_program(tmp_path, name):
     exe = str(tmp_path / name)
     inc = [os.path.join(ROOT, "paper_2502_03249_amd", "csrc"), os.path.join(ROOT, "include")]
