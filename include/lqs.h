@@ -108,6 +108,12 @@ typedef struct {
 lqs_status lqs_ctx_create(int32_t device, const char *tune_cache_path, lqs_ctx **out);
 void lqs_ctx_destroy(lqs_ctx *ctx);
 
+/* Free the link storage of destroyed gauges that is kept for the next ones on
+ * this device (at most 1/64 of its memory; an allocation of a context that
+ * fails frees it first by itself).  For programs whose other allocators need
+ * the memory.  Nothing that is in use is touched. */
+lqs_status lqs_release_cached(int32_t device);
+
 /* Autotuning of launch shapes: 1 = sweep on first use of a (kernel, lattice,
  * format, right-hand sides) key and cache the fastest (block size, sides per
  * thread, streaming link loads, block-to-XCD map and its run of time slices,

@@ -90,7 +90,7 @@ EXPORTS = ["lqs_ctx_create", "lqs_ctx_destroy", "lqs_set_tuning", "lqs_gauge_cre
            "fermion_force", "lqs_strerror", "lqs_last_error", "lqs_profile_hops", "lqs_profile_hops_result",
            "lqs_field_dot", "cg_solve_multishift", "lqs_gauge_fix_temporal", "gauge_action", "gauge_force",
            "link_update", "kinetic_energy", "hmc_trajectory", "lqs_set_graphs", "lqs_field_unpack_scaled",
-           "cg_solve_noalloc"]
+           "cg_solve_noalloc", "lqs_release_cached"]
 
 
 def lib():
@@ -106,6 +106,7 @@ def lib():
     L.lqs_ctx_create.argtypes = [i32, ctypes.c_char_p, ctypes.POINTER(vp)]
     L.lqs_ctx_destroy.argtypes = [vp]
     L.lqs_ctx_destroy.restype = None
+    L.lqs_release_cached.argtypes = [i32]
     L.lqs_set_tuning.argtypes = [vp, i32]
     L.lqs_set_graphs.argtypes = [vp, i32]
     L.lqs_gauge_create.argtypes = [vp, i32p, vp, ctypes.c_uint32, vp, ctypes.POINTER(vp)]
@@ -200,6 +201,20 @@ class Context:
         return torch.device("cuda", self.device)
 
 
+def release_cached(device=0):
+    """Free the link storage of closed gauges that the library keeps for the next ones on this device."""
+    _check(lib().lqs_release_cached(int(device)))
+
+
+def _allocate(make, device):
+    """make(); when torch is out of memory, once more without the link storage of closed gauges."""
+    try:
+        return make()
+    except torch.cuda.OutOfMemoryError:
+        release_cached(device if isinstance(device, int) else device.index)
+        return make()
+
+
 def field_bytes(dims, prec, nrhs=1):
     n = ctypes.c_size_t()
     _check(lib().lqs_field_bytes(_dims(dims), PREC[prec], int(nrhs), ctypes.byref(n)))
@@ -235,8 +250,8 @@ class Gauge:
 def gauge_fix_temporal(ctx, dims, links, stream=None):
     """Temporal gauge (U_t = 1 off the last slice): returns (fixed links, G), canonical complex128 tensors."""
     assert links.is_cuda and links.dtype == torch.complex128 and links.is_contiguous()
-    out = torch.empty_like(links)
-    G = torch.empty(links.shape[1:], dtype=torch.complex128, device=links.device)
+    out = _allocate(lambda: torch.empty_like(links), links.device)
+    G = _allocate(lambda: torch.empty(links.shape[1:], dtype=torch.complex128, device=links.device), links.device)
     _check(lib().lqs_gauge_fix_temporal(ctx.handle, _dims(dims), ctypes.c_void_p(links.data_ptr()),
                                         ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(G.data_ptr()),
                                         _stream(stream)))
@@ -253,7 +268,7 @@ class Field:
         self.nrhs = int(nrhs)
         nbytes = field_bytes(self.dims, self.prec, self.nrhs)
         if data is None:
-            data = torch.empty(nbytes, dtype=torch.uint8, device=torch.device("cuda", device))
+            data = _allocate(lambda: torch.empty(nbytes, dtype=torch.uint8, device=torch.device("cuda", device)), device)
         assert data.is_cuda and data.numel() * data.element_size() >= nbytes and data.is_contiguous()
         self.data = data
 
@@ -295,7 +310,8 @@ class Field:
         with scale, every value is multiplied by that real number inside the library."""
         nx, ny, nz, nt = self.dims
         if out is None:
-            out = torch.zeros((self.nrhs, nt, nz, ny, nx, 3), dtype=torch.complex128, device=self.data.device)
+            out = _allocate(lambda: torch.zeros((self.nrhs, nt, nz, ny, nx, 3), dtype=torch.complex128,
+                                                device=self.data.device), self.data.device)
         c = self.c()
         if scale is None:
             _check(lib().lqs_field_unpack(ctx.handle, _dims(self.dims), ctypes.byref(c),
@@ -384,7 +400,8 @@ def fermion_force(ctx, gauge, X, Y=None, coeff=1.0, mode=0, out=None, stream=Non
     """Link derivative (mode 0: su(3) force, mode 1: Euclidean gradient), canonical complex128 links."""
     nx, ny, nz, nt = gauge.dims
     if out is None:
-        out = torch.empty((4, nt, nz, ny, nx, 3, 3), dtype=torch.complex128, device=X.data.device)
+        out = _allocate(lambda: torch.empty((4, nt, nz, ny, nx, 3, 3), dtype=torch.complex128, device=X.data.device),
+                        X.data.device)
     assert X.prec == F64 and X.parity == 0 and X.nrhs == 1
     yp = None
     if Y is not None:
@@ -399,7 +416,7 @@ def field_dot(ctx, a, b, out=None, stream=None):
     """sum_sites a^dag b per right-hand side (FP64 fields) as a complex128 device tensor of nrhs entries."""
     assert a.prec == F64 and b.prec == F64
     if out is None:
-        out = torch.empty(a.nrhs, dtype=torch.complex128, device=a.data.device)
+        out = _allocate(lambda: torch.empty(a.nrhs, dtype=torch.complex128, device=a.data.device), a.data.device)
     ca, cb = a.c(), b.c()
     _check(lib().lqs_field_dot(ctx.handle, _dims(a.dims), ctypes.byref(ca), ctypes.byref(cb),
                                ctypes.c_void_p(out.data_ptr()), _stream(stream)))
@@ -423,7 +440,7 @@ def gauge_action(ctx, dims, links, beta, stream=None):
 def gauge_force(ctx, dims, links, beta, coeff=1.0, out=None, accumulate=False, stream=None):
     """coeff * (beta/3) TA(U V) per link (out = or out +=); returns out."""
     if out is None:
-        out = torch.empty_like(links)
+        out = _allocate(lambda: torch.empty_like(links), links.device)
     _check(lib().gauge_force(ctx.handle, _dims(dims), _links_tensor(dims, links, "links"), float(beta), float(coeff),
                              1 if accumulate else 0, _links_tensor(dims, out, "out"), _stream(stream)))
     return out

@@ -47,6 +47,34 @@ void *Ctx::workspace(const std::string &slot, size_t bytes)
     return p;
 }
 
+static std::mutex pools_mu;
+static std::map<int, std::weak_ptr<LinkPool>> pools;
+
+LinkPool::LinkPool(int dev) : device(dev)
+{
+    hipDeviceProp_t prop{};
+    LQS_HIP(hipGetDeviceProperties(&prop, dev));
+    limit = prop.totalGlobalMem / 64;
+}
+
+std::shared_ptr<LinkPool> LinkPool::existing(int device)
+{
+    std::lock_guard<std::mutex> lock(pools_mu);
+    auto it = pools.find(device);
+    return it == pools.end() ? nullptr : it->second.lock();
+}
+
+std::shared_ptr<LinkPool> LinkPool::of(int device)
+{
+    std::lock_guard<std::mutex> lock(pools_mu);
+    std::shared_ptr<LinkPool> p = pools[device].lock();
+    if (!p) {
+        p = std::make_shared<LinkPool>(device);
+        pools[device] = p;
+    }
+    return p;
+}
+
 void *LinkPool::take(size_t bytes, size_t &got)
 {
     bytes = (bytes + 65535) & ~size_t(65535);
@@ -78,7 +106,7 @@ void LinkPool::give(void *p, size_t size)
 {
     std::lock_guard<std::mutex> lock(mu);
     try {
-        if (open && size <= LINK_POOL_BYTES) {
+        if (contexts > 0 && size <= limit) {
             blocks.emplace_back(p, size);
             cached += size;
             p = nullptr;
@@ -86,7 +114,7 @@ void LinkPool::give(void *p, size_t size)
     } catch (const std::bad_alloc &) {
     }
     if (p) (void)hipFree(p);
-    while (cached > LINK_POOL_BYTES) {
+    while (cached > limit) {
         (void)hipFree(blocks.front().first);
         cached -= blocks.front().second;
         blocks.pop_front();
@@ -106,11 +134,16 @@ void LinkPool::drain()
     drain_locked();
 }
 
-void LinkPool::close()
+void LinkPool::attach()
 {
     std::lock_guard<std::mutex> lock(mu);
-    open = false;
-    drain_locked();
+    ++contexts;
+}
+
+void LinkPool::detach()
+{
+    std::lock_guard<std::mutex> lock(mu);
+    if (--contexts == 0) drain_locked();
 }
 
 void *Ctx::pinned(const std::string &slot, size_t bytes)
@@ -149,7 +182,7 @@ Ctx::~Ctx()
         (void)hipEventDestroy(e.first);
         (void)hipEventDestroy(e.second);
     }
-    if (links) links->close();
+    if (links) links->detach();
     if (tuner) tuner->save();
 }
 
@@ -263,7 +296,9 @@ lqs_status lqs_ctx_create(int32_t device, const char *tune_cache_path, lqs_ctx *
         try {
             c->noalloc_scratch = noalloc_scratch(device);
             c->tuner.reset(new Tuner(tune_cache_path));
-            c->links = std::make_shared<LinkPool>(device);
+            std::shared_ptr<LinkPool> pool = LinkPool::of(device);
+            pool->attach();
+            c->links = pool;
         } catch (...) {
             delete c;
             throw;
@@ -273,6 +308,16 @@ lqs_status lqs_ctx_create(int32_t device, const char *tune_cache_path, lqs_ctx *
 }
 
 void lqs_ctx_destroy(lqs_ctx *ctx) { delete ctx; }
+
+lqs_status lqs_release_cached(int32_t device)
+{
+    return guard([&] {
+        int n = 0;
+        LQS_HIP(hipGetDeviceCount(&n));
+        LQS_REQUIRE(device >= 0 && device < n, LQS_EINVAL, "no such device");
+        if (auto pool = LinkPool::existing(device)) pool->drain();
+    });
+}
 
 lqs_status lqs_set_tuning(lqs_ctx *ctx, int32_t enable)
 {

@@ -112,29 +112,35 @@ struct FieldRef {
 
 struct Tuner;
 
-// Link storage of closed gauges, kept for the next ones of the context.  A
+// Link storage of closed gauges, kept for the next ones on the device.  A
 // hipMalloc and hipFree of 200 MB cost 5 ms, against 0.1 ms to pack the links.
 // A block enters the pool only after the device has been synchronised, so any
-// stream may use it next.  Bounded by LINK_POOL_BYTES (the oldest blocks go
-// first); given back when the context is destroyed or when an allocation of
-// the context fails.  Gauges share ownership: one that outlives its context
-// frees its block itself.  Safe to use from several threads.
-constexpr size_t LINK_POOL_BYTES = (size_t)8 << 30;
+// stream may use it next.  One pool per device, shared by its contexts and
+// gauges and bounded by 1/64 of the device's memory (4.5 GB of 288: the formats
+// of one 64^3 x 16 configuration; the oldest blocks go first).  Given back when
+// the device's last context is destroyed, when an allocation of a context fails,
+// and by lqs_release_cached (other allocators of the process cannot reach it
+// when they run out).  A gauge that outlives the contexts frees its block itself.
+// Safe to use from several threads.
 struct LinkPool {
-    explicit LinkPool(int dev) : device(dev) {}
+    static std::shared_ptr<LinkPool> of(int device);      // the device's pool
+    static std::shared_ptr<LinkPool> existing(int device);  // null where there is none
+    explicit LinkPool(int dev);
+    ~LinkPool() { drain(); }
     // a block of at least `bytes`, its size in `got`; throws when the device is out of memory
     void *take(size_t bytes, size_t &got);
     // `p` is idle: no queued work uses it
     void give(void *p, size_t size);
-    void drain();  // free every cached block
-    void close();  // drain, and free what is given from now on
+    void drain();   // free every cached block
+    void attach();  // a context more,
+    void detach();  // a context less: without one, drain, and free what is given from now on
     const int device;
 
   private:
     std::mutex mu;
     std::list<std::pair<void *, size_t>> blocks;  // oldest first
-    size_t cached = 0;
-    bool open = true;
+    size_t cached = 0, limit = 0;
+    int contexts = 0;
     void drain_locked();
 };
 
