@@ -926,7 +926,9 @@ struct CgRun {
             LQS_HIP(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
             LQS_HIP(hipEventCreateWithFlags(&ev[1], hipEventDisableTiming));
         }
-        cap = 2 * (int64_t)prm.max_iter + 16 * chunk + 64;  // (an iteration may be followed by one that settles it)
+        // never reached: an iteration may be followed by one that settles it and by
+        // a failed check, behind what is left of its round and two more
+        cap = (3 * chunk + 2) * (int64_t)prm.max_iter + 16 * chunk + 64;
     }
 
     // queue the final check that a right-hand side waits for, or one round of
@@ -1073,51 +1075,42 @@ static constexpr int64_t GRAPH_SITES = 1 << 15;
 void cg_solve_one(Ctx &ctx, const lqs_problem &pb, const lqs_cg_params &prm, lqs_cg_stats *stats, hipStream_t s,
                   const std::vector<double> *masses)
 {
-    // graphs are captured on a side stream (the caller's stream may be the
-    // null stream, which cannot be captured), forked from and joined into s
-    const bool graphs = ctx.graphs && !ctx.profiling && pb.gauge->vh * pb.nrhs < GRAPH_SITES;
-    hipStream_t rs = graphs ? ctx.side_stream(0) : s;
-    hipEvent_t fork = nullptr, join = nullptr;
-    if (graphs) {
-        LQS_HIP(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
-        LQS_HIP(hipEventCreateWithFlags(&join, hipEventDisableTiming));
-    }
-    auto cleanup = [&]() {
-        if (fork) (void)hipEventDestroy(fork);
-        if (join) (void)hipEventDestroy(join);
-    };
-    try {
-        if (graphs) {
-            LQS_HIP(hipEventRecord(fork, s));
-            LQS_HIP(hipStreamWaitEvent(rs, fork, 0));
+    // The solve runs on a side stream that waits for s (and has nothing left to
+    // do when the call returns): the caller's stream may be the null stream,
+    // which cannot be captured, and on which every launch would wait for, and
+    // hold up, the process's blocking streams.
+    const bool side = ctx.graphs && !ctx.profiling;
+    hipStream_t rs = side ? ctx.side_stream(0) : s;
+    struct Event {
+        hipEvent_t e = nullptr;
+        ~Event()
+        {
+            if (e) (void)hipEventDestroy(e);
         }
-        CgRun run(ctx, pb, prm, stats, rs, "", std::chrono::steady_clock::now());
-        run.use_graph = graphs;
-        if (masses) run.masses = *masses;
+    } fork;
+    if (side) {
+        LQS_HIP(hipEventCreateWithFlags(&fork.e, hipEventDisableTiming));
+        LQS_HIP(hipEventRecord(fork.e, s));
+        LQS_HIP(hipStreamWaitEvent(rs, fork.e, 0));
+    }
+    CgRun run(ctx, pb, prm, stats, rs, "", std::chrono::steady_clock::now());
+    run.use_graph = side && pb.gauge->vh * pb.nrhs < GRAPH_SITES;
+    if (masses) run.masses = *masses;
+    try {
         run.setup();
-        try {
-            // one mass per column: the multi-shift solver's check of solutions
-            // that mostly meet the target already; two rounds of gated launches
-            // cost more than waiting for the initial residuals
-            if (masses && prm.use_x0) run.check_initial();
-            while (!run.done) {
-                run.enqueue();
-                run.check();
-            }
-        } catch (...) {
-            (void)hipStreamSynchronize(rs);
-            throw;
+        // one mass per column: the multi-shift solver's check of solutions
+        // that mostly meet the target already; two rounds of gated launches
+        // cost more than waiting for the initial residuals
+        if (masses && prm.use_x0) run.check_initial();
+        while (!run.done) {
+            run.enqueue();
+            run.check();
         }
         run.finish();
-        if (graphs) {
-            LQS_HIP(hipEventRecord(join, rs));
-            LQS_HIP(hipStreamWaitEvent(s, join, 0));
-        }
     } catch (...) {
-        cleanup();
+        (void)hipStreamSynchronize(rs);
         throw;
     }
-    cleanup();
 }
 
 // Problems of different sizes each get a side stream (forked from and joined

@@ -503,7 +503,7 @@ void multishift_solve(Ctx &ctx, const Gauge &gauge, int nmass, const double *mas
     } ev;
     for (hipEvent_t &e : ev.e) LQS_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     int64_t enqueued = 0;
-    const int64_t cap = 2 * (int64_t)prm.max_iter + 64;
+    const int64_t cap = 8 * (int64_t)prm.max_iter + 64;
     for (int round = 0;; ++round) {
         for (int i = 0; i < 8; ++i) {
             const int group = mixed && (i & 3) == 3;
