@@ -562,9 +562,7 @@ __global__ void __launch_bounds__(256) link_force_kernel(Geom g, SweepMap sm, co
 
 // U = exp(eps Q) U on every link.  A block takes 128 consecutive sites of one
 // direction (64 of each parity) and moves the canonical records through LDS in
-// contiguous runs (see pack.hip).  WM: U is the word-major FP64 18-real array
-// (Q canonical) and the updated links are written in the formats of `out` as
-// well.  Bound by memory: 127 us at 24^4 for 573 MB, the card's copy rate; 174 us
+// contiguous runs (see pack.hip).  Bound by memory: 127 us at 24^4 for 573 MB, the card's copy rate; 174 us
 // with a matrix product per Horner step and a lane reading its own 144-byte record.
 constexpr int LU_SITES = 128;
 
@@ -578,8 +576,7 @@ __device__ __forceinline__ void lu_stage(double2 *sh, const double2 *src, int n)
     __syncthreads();
 }
 
-template <bool WM>
-__global__ void __launch_bounds__(LU_SITES) link_update_kernel(Geom g, double2 *U, const double2 *Q, double eps, LinkOut out)
+__global__ void __launch_bounds__(LU_SITES) link_update_kernel(Geom g, double2 *U, const double2 *Q, double eps)
 {
     __shared__ double2 sh[9 * LU_SITES];
     const int64_t V = 2 * (int64_t)g.vh, first = (int64_t)blockIdx.x * LU_SITES;
@@ -589,32 +586,22 @@ __global__ void __launch_bounds__(LU_SITES) link_update_kernel(Geom g, double2 *
     const int parity = threadIdx.x >> 6, cb = (int)(first >> 1) + (threadIdx.x & 63);
     const bool valid = cb < g.vh;
     double2 *own = sh + (valid ? 9 * (lex_of(g, cb, parity) - (int)first) : 0);
-    Mat u = mat_zero();
-    if (WM && valid) u = wm_load(U, g.vh, 2 * mu + parity, cb);
     lu_stage(sh, Q + rec, n);
     Mat q = mat_load(own);
-    if constexpr (!WM) {
-        __syncthreads();
-        lu_stage(sh, U + rec, n);
-        u = mat_load(own);
-    }
+    __syncthreads();
+    lu_stage(sh, U + rec, n);
+    const Mat u = mat_load(own);
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) q.e[i][j] = {eps * q.e[i][j].re, eps * q.e[i][j].im};
     const Mat w = mat_mul<false, false>(mat_exp(q), u);
-    if constexpr (WM) {
-        if (!valid) return;
-        const int blk = 2 * mu + parity;
-        lu_store_all(w, out, blk, g.vh, cb);
-    } else {
-        if (valid) mat_store(own, w);  // own record only: read by this thread alone
-        __syncthreads();
+    if (valid) mat_store(own, w);  // own record only: read by this thread alone
+    __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const int i = threadIdx.x + k * LU_SITES;
-            if (i < n) U[rec + i] = sh[i];
-        }
+    for (int k = 0; k < 9; ++k) {
+        const int i = threadIdx.x + k * LU_SITES;
+        if (i < n) U[rec + i] = sh[i];
     }
 }
 
@@ -696,17 +683,10 @@ void launch_gauge_force(const Geom &g, const double *U, double beta, double coef
     launch_link_force<false, false>(g, U, nullptr, nullptr, 1.0, coeff * beta / 3.0, accumulate ? 1 : 0, out, s);
 }
 
-static void link_update_grid(const Geom &g, dim3 &grid)
-{
-    grid = dim3((unsigned)((2 * (int64_t)g.vh + LU_SITES - 1) / LU_SITES), 4);
-}
-
 void launch_link_update(const Geom &g, double *U, const double *Q, double eps, hipStream_t s)
 {
-    dim3 grid;
-    link_update_grid(g, grid);
-    hipLaunchKernelGGL(link_update_kernel<false>, grid, dim3(LU_SITES), 0, s, g, (double2 *)U, (const double2 *)Q, eps,
-                       LinkOut());
+    const dim3 grid((unsigned)((2 * (int64_t)g.vh + LU_SITES - 1) / LU_SITES), 4);
+    hipLaunchKernelGGL(link_update_kernel, grid, dim3(LU_SITES), 0, s, g, (double2 *)U, (const double2 *)Q, eps);
     LQS_HIP(hipGetLastError());
 }
 
@@ -761,15 +741,8 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
     Gauge &gauge = wg.g;
     LinkRef L64 = gauge.ref(F64, 18);
     double *U1 = (double *)gauge.fmt[F64][0];
-    // where a momentum step that goes on to the link step writes the new links;
-    // without room for it the two steps are separate kernels
-    double *U2 = nullptr;
-    try {
-        U2 = (double *)ctx.workspace("hmc.links.next", (size_t)link_block_bytes_per_site(F64, 18) * gauge.pitch * 8);
-    } catch (const Error &e) {
-        if (e.status != LQS_ENOMEM) throw;
-        (void)hipGetLastError();
-    }
+    // where a momentum step that goes on to the link step writes the new links
+    double *U2 = (double *)ctx.workspace("hmc.links.next", (size_t)link_block_bytes_per_site(F64, 18) * gauge.pitch * 8);
     LinkOut fmts;
     for (int prec = 0; prec < 3; ++prec)
         for (int rc = 0; rc < 2; ++rc) fmts.fmt[prec][rc] = (char *)gauge.fmt[prec][rc];
@@ -839,7 +812,7 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
             launch_hop_gated(g, L64, F64, 18, 0, 1, 1, chi, psx, nullptr, 0, sh, s);
         }
         const double gb = prm.beta / 3.0, c = -0.5 * eps;
-        if (drift > 0 && U2) {
+        if (drift > 0) {
             LinkOut next = fmts;
             next.fmt[F64][0] = (char *)U2;
             if (ferm) launch_link_force<true, true, true>(g, U1, chi, psx, gb, c, 1, mom, s, drift, next);
@@ -852,13 +825,6 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
         }
         if (ferm) launch_link_force<true, true>(g, U1, chi, psx, gb, c, 1, mom, s);
         else launch_link_force<true, false>(g, U1, nullptr, nullptr, gb, c, 1, mom, s);
-        if (drift > 0) {
-            dim3 grid;
-            link_update_grid(g, grid);
-            hipLaunchKernelGGL(link_update_kernel<true>, grid, dim3(LU_SITES), 0, s, g, (double2 *)U1,
-                               (const double2 *)mom, drift, fmts);
-            LQS_HIP(hipGetLastError());
-        }
     };
 
     // H at the start: scal[0..1] = K0, Sg0 / beta, scal[8] = Sf0
