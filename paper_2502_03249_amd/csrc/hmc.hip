@@ -737,7 +737,8 @@ void hmc_trajectory_impl(Ctx &ctx, const Geom &g, double *links, double *mom, co
     // the links of the trajectory live in the word-major FP64 18-real format
     // alone (U1), which the force, the link update and the solver's FP64 hops
     // read; the inner format is written along with each link update
-    WsGauge wg(ctx, g, prm.cg.inner_prec, prm.cg.inner_recon);
+    // (the solver's parameters mean nothing without fermions)
+    WsGauge wg(ctx, g, ferm ? prm.cg.inner_prec : F64, ferm ? prm.cg.inner_recon : 18);
     Gauge &gauge = wg.g;
     LinkRef L64 = gauge.ref(F64, 18);
     double *U1 = (double *)gauge.fmt[F64][0];
