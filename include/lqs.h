@@ -238,8 +238,9 @@ typedef struct {
                                   per hop the links once (8 per site, 6 + 2/Nt in temporal
                                   gauge, shared by the right-hand sides of one problem) and
                                   each colour vector once per kernel of the iteration (hop,
-                                  normal operator, update, p-update); reliable updates and
-                                  the final check are not counted                            */
+                                  normal operator, step); reliable updates and the final
+                                  check are not counted.  The same count with persistent = 1,
+                                  also where a small lattice stays on chip and moves none    */
 } lqs_cg_stats;
 
 /* Solve nprob systems.  stats receives one entry per (problem, right-hand

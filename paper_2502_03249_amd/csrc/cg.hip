@@ -467,8 +467,8 @@ void cg_fill_rates(lqs_cg_stats &o, const Gauge &gauge, int prec, int recon, int
     const double lps = gauge.temporal ? 6.0 + 2.0 / gauge.g.n[3] : 8.0;
     const double L = lps * real * recon / (nrhs > 0 ? nrhs : 1);
     const double sv = (double)spinor_bytes_per_site(prec), a = (double)spinor_bytes_per_site(prec == F64 ? F64 : F32);
-    // t = D_oe p; q = m^2 p - D_eo t; r updated from q; x and p updated from r and p
-    const double bytes = (L + 2 * sv) + (L + 3 * sv) + (2 * a + sv) + (3 * a + 2 * sv);
+    // t = D_oe p; q = m^2 p - D_eo t; x, r and p updated from one another and q
+    const double bytes = (L + 2 * sv) + (L + 3 * sv) + (4 * a + 3 * sv);
     const double n = (double)gauge.vh * o.iters;
     o.gflops = 1140.0 * n / t * 1e-9;
     o.gbytes_per_s = bytes * n / t * 1e-9;

@@ -45,12 +45,11 @@ def arithmetic_intensity(prec, recon=18, nrhs=1, links_per_site=8):
 
 
 def cg_iteration_bytes(prec, acc_prec, recon=18, links_per_site=8):
-    """Algorithmic HBM bytes per even site of one CG iteration (four kernels).
+    """Algorithmic HBM bytes per even site of one CG iteration.
 
     hop t = D_oe p: links + p + t; hop q = m^2 p - D_eo t: links + t + p + q;
-    update: r read and written, q read; x += alpha p and p = r + beta p: x read and
-    written, r and p read, p written.
+    step x += alpha p, r -= alpha q, p = r + beta p: x, r and p read and written, q read.
     """
     L = links_per_site * link_bytes(prec, recon)
     s, a = spinor_bytes(prec), spinor_bytes(acc_prec)
-    return (L + 2 * s) + (L + 3 * s) + (2 * a + s) + (3 * a + 2 * s)
+    return (L + 2 * s) + (L + 3 * s) + (4 * a + 3 * s)
