@@ -14,7 +14,7 @@
 // directions in 16 bits corrected for what they are not, see cg_step.hpp), and
 // |r|^2 of the next step is the one kernel 4 sums from the residual it stores,
 // so the prediction's rounding does not accumulate: the predict-and-recompute
-// conjugate gradient of Chen and Carson (SIAM J. Matrix Anal. Appl. 2020).
+// conjugate gradient of Chen and Carson (SIAM J. Sci. Comput. 42, 2020).
 // The x, r and p updates then share one kernel and one read of each vector.
 // The dot products are reduced in two fixed-order stages and alpha, beta stay
 // on the device; the host only polls the state record.
@@ -59,13 +59,12 @@ __device__ __forceinline__ V3<typename RealOf<PA>::type> direction_of(const V3<t
     return o;
 }
 
-// Re <a,b> of a site, summed in double
-template <typename T> __device__ __forceinline__ double re_dot(const V3<T> &a, const V3<T> &b)
+// Re <a,b> of a site (of vectors in T, for the sums over sites in double)
+template <typename T> __device__ __forceinline__ T re_dot(const V3<T> &a, const V3<T> &b)
 {
-    double s = 0.0;
+    T s = T(0);
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-        s += (double)a.c[c].re * (double)b.c[c].re + (double)a.c[c].im * (double)b.c[c].im;
+    for (int c = 0; c < 3; ++c) s = fused(a.c[c].re, b.c[c].re, fused(a.c[c].im, b.c[c].im, s));
     return s;
 }
 
@@ -228,10 +227,9 @@ __global__ void __launch_bounds__(BLAS_BLOCK) step_kernel(int vh, char *x, char 
         }
         SpinorIO<PA>::store(x, vh, cb, xv);
         SpinorIO<PA>::store(r, vh, cb, rv);
-        if (!pdir) return;
         const V3<T> pn = direction_of<PA>(rv, pv, beta);
-        SpinorIO<PI>::store(p, vh, cb, vcast<TI>(pn));
         if (CONJ) sums[1] += re_dot(qv, pn);
+        if (pdir) SpinorIO<PI>::store(p, vh, cb, vcast<TI>(pn));
     };
     if (EARLY) {
         if (c0 < vh)
