@@ -198,8 +198,10 @@ __device__ __forceinline__ void add_dots(const double *partials, int nblocks, in
 }
 
 // The phase of a right-hand side for the host, in pinned memory (null: not now).
-// Phases only move towards a final one while the host waits, so a word that a
-// later kernel overwrites meanwhile misleads nobody.  (A copy of the records on
+// The host may read it before or after a later kernel has moved the phase on, or
+// back from CG_INNER_DONE to CG_RUNNING where a check failed: it then queues a
+// round or a check that finds nothing to do, and looks again.  A final phase
+// stays.  (A copy of the records on
 // the stream instead held the next round back by 12 us.)
 __device__ __forceinline__ void publish(int32_t *host_phase, int rhs, int32_t phase)
 {

@@ -562,8 +562,10 @@ __global__ void __launch_bounds__(256) link_force_kernel(Geom g, SweepMap sm, co
 
 // U = exp(eps Q) U on every link.  A block takes 128 consecutive sites of one
 // direction (64 of each parity) and moves the canonical records through LDS in
-// contiguous runs (see pack.hip).  Bound by memory: 127 us at 24^4 for 573 MB, the card's copy rate; 174 us
-// with a matrix product per Horner step and a lane reading its own 144-byte record.
+// contiguous runs (see pack.hip).  Bound by memory: 137 us
+// at 24^4 for 573 MB without a squaring, 4.2 TB/s; 140 at norms of a trajectory and
+// 151 above norm 2 (180 to 217 with a matrix product per Horner step and squaring
+// and a lane reading its own 144-byte record).
 constexpr int LU_SITES = 128;
 
 __device__ __forceinline__ void lu_stage(double2 *sh, const double2 *src, int n)
@@ -644,7 +646,13 @@ void launch_kinetic(Ctx &ctx, const Geom &g, const double *Q, double *out, int s
     LQS_HIP(hipGetLastError());
 }
 
-// Time slices an XCD takes at one chunk position before its next chunk.
+// Time slices an XCD takes at one chunk position before its next chunk: enough
+// that a slice's t neighbours are its own, few enough that what it has read of z
+// is still in its L2 at the next position.  Pure-gauge trajectories in ms with
+// runs of 1, 2, 3, 4, 6, 8, 24 slices: 24^4 5.45 5.13 4.86 5.04 4.92 5.08 5.09,
+// 16^3 x 32 1.67 1.64 1.59 1.63 1.61 1.77 1.91, 32^4 16.7 16.1 16.0 15.5 16.2
+// 15.7 17.0, 48^3 x 16 27.0 26.1 27.6 27.3 28.1 28.2 28.0, 32^3 x 8 4.00 3.99 4.12
+// 4.06 4.12 4.17 4.16.
 constexpr int SWEEP_RUN = 3;
 
 // out[slot] (device) = beta * sum_x sum_{mu<nu} (1 - Re tr P / 3)

@@ -44,7 +44,8 @@ void launch_unit_link(const Geom &g, int prec, int recon, int64_t pitch, void *l
 // contiguous runs.  Bound by memory: 576 B read and the formats written per
 // site.  One thread per link that gathered its 144 B from memory (64 lines per
 // load), once per format, took 129 us for FP64 18 + FP32 12 + FP16 12 reals on
-// 32^3 x 8; this takes 75 us (264 MB, 3.5 TB/s).
+// 32^3 x 8; this takes 75-82 us (377 MB read and written,
+// 4.6-5.0 TB/s).
 constexpr int PACK_SITES = 128;
 
 template <int P, int R> __device__ __forceinline__ void pack_one(const M3<double> &u, char *out, int blk, int64_t pitch, int cb)

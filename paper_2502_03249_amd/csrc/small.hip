@@ -396,16 +396,20 @@ static void launch_small(int nlat, int vmax, const SmallLat *lats, CgState *st, 
 // lattice has vmax: blocks of 512 threads, whose 256 registers each hold the
 // links of up to two sites per quad in FP64 and four in FP32.  Fewer, fuller
 // threads win over more waves that all wait at the same barriers and repeat the
-// scalars: 4^3 x 6 in FP64 4.36 us per iteration with 512 threads and two sites
-// per quad, 4.73 with 768 and one; FP32 arithmetic in 1024 threads of 128
-// registers spills, 5.9 against 3.3.
+// scalars: 4^3 x 6 in FP64 4.4 us per iteration with 512 threads and two sites
+// per quad, 4.7 with 768 and one; FP32 arithmetic in 1024 threads of 128
+// registers spills, 5.9 against 3.3 (before the scalars left the vector registers:
+// now 3.9 and 3.2).
 //
 // us per iteration, 64 lattices at once, here and in the kernel for lattices
 // that several blocks may share (which keeps the larger ones):
-//   FP64 18-real   4^4  3.0, 13.1   4^3 x 6  4.4, 14.0   4^3 x 8  5.2, 15.2
-//   FP32 12-real   4^4  2.9, 11.7   4^3 x 6  3.3, 11.9   4^2 x 6^2  4.8, 12.8
-//                  4^2 x 6 x 8  5.4, 13.2   4 x 8^2 x 4  12.2, 15.6
-//   FP16 12-real   4^4  3.0, 12.5   4^2 x 6^2  5.1, 15.8   4 x 8^2 x 4  13.8, 17.8
+//   FP64 18-real   4^4  2.9, 13.1   4^3 x 6  3.9, 14.0   4^3 x 8  4.7, 15.2
+//   FP32 12-real   4^4  2.9, 11.7   4^3 x 6  3.2, 11.9   4^2 x 6^2  4.3, 12.8
+//                  4^2 x 6 x 8  5.1, 13.2   4 x 8^2 x 4  10.0, 15.6
+//   FP16 12-real   4^4  3.0, 12.5   4^2 x 6^2  4.7, 15.8   4 x 8^2 x 4  11.5, 17.8
+// A batch with one larger member goes there as a whole: that member's chain of
+// group barriers is its time either way (63 of 4^4 and one 6^4 in FP64 3.24 ms,
+// the 6^4 alone 3.13).
 static int small_max_vh(int prec) { return prec == F64 ? 256 : 512; }
 
 template <int P, int R>
