@@ -1076,8 +1076,11 @@ void cg_solve_one(Ctx &ctx, const lqs_problem &pb, const lqs_cg_params &prm, lqs
     // The solve runs on a side stream that waits for s (and has nothing left to
     // do when the call returns): the caller's stream may be the null stream,
     // which cannot be captured, and on which every launch would wait for, and
-    // hold up, the process's blocking streams.
-    const bool side = ctx.graphs && !ctx.profiling;
+    // hold up, the process's blocking streams.  (The refinement of a multi-shift
+    // solve, one mass per column, stays on the stream of its recurrence where it
+    // replays no graph: crossing over costs 50 to 100 us.)
+    const bool graph = ctx.graphs && !ctx.profiling && pb.gauge->vh * pb.nrhs < GRAPH_SITES;
+    const bool side = graph || (ctx.graphs && !ctx.profiling && !masses);
     hipStream_t rs = side ? ctx.side_stream(0) : s;
     struct Event {
         hipEvent_t e = nullptr;
@@ -1092,7 +1095,7 @@ void cg_solve_one(Ctx &ctx, const lqs_problem &pb, const lqs_cg_params &prm, lqs
         LQS_HIP(hipStreamWaitEvent(rs, fork.e, 0));
     }
     CgRun run(ctx, pb, prm, stats, rs, "", std::chrono::steady_clock::now());
-    run.use_graph = side && pb.gauge->vh * pb.nrhs < GRAPH_SITES;
+    run.use_graph = graph;
     if (masses) run.masses = *masses;
     try {
         run.setup();

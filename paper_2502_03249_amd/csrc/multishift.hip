@@ -61,6 +61,48 @@ struct ShiftPtrs {
                                      // (entry nshift: the base, for the final flush)
 };
 
+// What |r|^2 of a step leads to for the base (any: a shift is still active).
+__device__ __forceinline__ void ms_decide(CgState &S, double r2, double b, bool any, int last)
+{
+    S.beta = b;
+    S.rho = r2;
+    if (r2 > S.max_rho) S.max_rho = r2;
+    if ((r2 <= S.stop2 && !any) || S.iters >= S.max_iter) {
+        S.phase = CG_INNER_DONE;
+        S.p_due = 1;
+        // mixed: the FP64 residual of the base decides (and resumes when it is above the target)
+        if (S.rel_interval > 0) S.reliable_pending = 1;
+        return;
+    }
+    if (S.rel_interval > 0 && (S.since_rel >= S.rel_interval || r2 < S.delta2 * S.max_rho)) S.reliable_pending = 1;
+    if (last && S.reliable_pending) S.p_due = 1;
+}
+
+// Settles a step whose |r|^2 could not be predicted (cg_step.hpp) with the one
+// that it left, rr: every direction is due, no solution is.
+__device__ __forceinline__ void ms_settle(CgState &S, ShiftState &T, bool mine, double rr, int last)
+{
+    S.unsettled = 0;
+    S.live = 0;
+    S.p_due = 0;
+    const bool on = mine && T.active;
+    T.xupd = 0;
+    if (!isfinite(rr)) {
+        S.phase = CG_NONFINITE;
+        return;
+    }
+    const double b = S.rho_old > 0.0 ? rr / S.rho_old : 0.0;
+    if (on) {
+        const double ratio = T.zeta / T.zeta_prev;
+        T.alpha = 0.0;
+        T.beta = b * ratio * ratio;
+        T.xupd = 1;
+        if (T.zeta * T.zeta * rr <= S.stop2) T.active = 0;
+    }
+    S.live = 2;
+    ms_decide(S, rr, b, __any(mine && T.active), last);
+}
+
 // Every scalar of one iteration from the base's <p,q>, <q,q> (partials) and
 // |r|^2 as the last step summed it (rr_partials, at most 1024; unused while
 // rho holds a measured one; CONJ: <p_old,q> after them).  `last`: the FP64 group follows this iteration.
@@ -79,23 +121,23 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
     add_dots(partials, nblocks, nr_blocks, first, v);
     __shared__ double red[16][4];
     if (!block_sums_first<4>(v, red)) return;
+    if (__builtin_expect(phase == CG_RUNNING && S.unsettled, 0)) {
+        ms_settle(S, T, mine, v[2], last);
+        if (mine) sh[i] = T;
+        if (i != 0) return;
+        *base = S;
+        publish(host_phase, 0, S.phase);
+        return;
+    }
     const double pq = v[0], qq = v[1], rr = S.rho_known ? S.rho : v[2];
     // lane i < nshift advances shift i; lane 0 the base
-    const bool settle = S.unsettled != 0;  // the last step's directions, with its measured |r|^2
-    const bool ok = phase == CG_RUNNING && (settle || (isfinite(pq) && pq > 0.0));
-    const double a_prev = S.alpha, b_prev = S.beta, a = ok && !settle ? rr / pq : 0.0;
-    const double r2 = settle ? rr : predicted_r2<CONJ>(a, S.beta, qq, rr, v[3]), r2_old = settle ? S.rho_old : rr;
-    const double b = r2_old > 0.0 ? r2 / r2_old : 0.0;
-    const bool finite = isfinite(r2);
-    const bool lost = !settle && prediction_lost(r2, rr, S.stop2) && S.iters + 1 < S.max_iter;
+    const bool ok = phase == CG_RUNNING && isfinite(pq) && pq > 0.0;
+    const double a_prev = S.alpha, b_prev = S.beta, a = ok ? rr / pq : 0.0;
+    const double r2 = predicted_r2<CONJ>(a, S.beta, qq, rr, v[3]);
+    const double b = rr > 0.0 ? r2 / rr : 0.0;
+    const bool finite = isfinite(r2), lost = prediction_lost(r2, rr, S.stop2) && S.iters + 1 < S.max_iter;
     T.xupd = 0;
-    if (mine && ok && finite && T.active && settle) {
-        const double ratio = T.zeta / T.zeta_prev;
-        T.alpha = 0.0;
-        T.beta = b * ratio * ratio;
-        T.xupd = 1;
-        if (T.zeta * T.zeta * r2 <= S.stop2) T.active = 0;
-    } else if (mine && ok && finite && T.active) {
+    if (mine && ok && finite && T.active) {
         const double z = T.zeta, zp = T.zeta_prev;
         const double den = zp * a_prev * (1.0 + a * T.sigma) + a * b_prev * (zp - z);
         const double zn = z * zp * a_prev / den, ratio = zn / z;
@@ -105,7 +147,7 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
         T.zeta = zn;
         T.iters += 1;
         T.xupd = 1;
-        if (!lost && zn * zn * r2 <= S.stop2) T.active = 0;
+        if (zn * zn * r2 <= S.stop2 && !lost) T.active = 0;
     }
     if (mine) sh[i] = T;
     const bool any = __any(mine && T.active);
@@ -127,39 +169,23 @@ __global__ void __launch_bounds__(1024) ms_scalars(CgState *base, ShiftState *sh
         S.phase = isfinite(pq) ? CG_BREAKDOWN : CG_NONFINITE;
         return;
     }
-    S.unsettled = 0;
-    if (!settle) {
-        S.rho_known = 0;
-        S.iters += 1;
-        S.since_rel += 1;
-    }
+    S.rho_known = 0;
+    S.iters += 1;
+    S.since_rel += 1;
     if (!finite) {
         S.phase = CG_NONFINITE;
         return;
     }
-    if (!settle) {
-        S.alpha = a;
-        S.rho_old = rr;
-    }
-    S.live = settle ? 2 : 1;
-    if (lost) {
+    S.alpha = a;
+    S.rho_old = rr;
+    S.live = 1;
+    if (__builtin_expect(lost, 0)) {
         S.unsettled = 1;
         S.p_due = 1;
         if (S.rel_interval > 0 && S.since_rel >= S.rel_interval) S.reliable_pending = 1;
         return;
     }
-    S.beta = b;
-    S.rho = r2;
-    if (r2 > S.max_rho) S.max_rho = r2;
-    if ((r2 <= S.stop2 && !any) || S.iters >= S.max_iter) {
-        S.phase = CG_INNER_DONE;
-        S.p_due = 1;
-        // mixed: the FP64 residual of the base decides (and resumes when it is above the target)
-        if (S.rel_interval > 0) S.reliable_pending = 1;
-        return;
-    }
-    if (S.rel_interval > 0 && (S.since_rel >= S.rel_interval || r2 < S.delta2 * S.max_rho)) S.reliable_pending = 1;
-    if (last && S.reliable_pending) S.p_due = 1;
+    ms_decide(S, r2, b, any, last);
 }
 
 // Mixed recurrence, reliable update: add every FP32 solution into its FP64
